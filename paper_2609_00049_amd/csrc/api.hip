@@ -328,11 +328,10 @@ int realq_chol_inverse(realq_ctx* ctx, const double* H_acc, int64_t n, int64_t T
     if (!(damp > 0.f) || !std::isfinite(damp))
         return set_error(ctx, REALQ_ERR_INVALID_ARG, "chol_inverse: damp must be finite and > 0");
     const int64_t np = ((n + 63) / 64) * 64;
-    void *A, *L, *D, *F, *S;
+    void *A, *L, *F, *S;
     int rc;
     if ((rc = get_ws(ctx, "c_A", (size_t)np * np * 8, &A))) return rc;
     if ((rc = get_ws(ctx, "c_L", (size_t)np * np * 8, &L))) return rc;
-    if ((rc = get_ws(ctx, "c_D", (size_t)np * 64 * 8, &D))) return rc;
     if ((rc = get_ws(ctx, "c_F", 64, &F))) return rc;
     if ((rc = get_ws(ctx, "c_S", 64, &S))) return rc;
     // two flag words (not positive definite; non-finite accumulator) cleared by one double fill
@@ -347,7 +346,6 @@ int realq_chol_inverse(realq_ctx* ctx, const double* H_acc, int64_t n, int64_t T
     c.dead = dead;
     c.A = (double*)A;
     c.Linv = (double*)L;
-    c.diaginv = (double*)D;
     c.flag = (int*)F;
     c.scratch = (double*)S;
     c.U = U;

@@ -292,8 +292,6 @@ struct CholArgs {
     uint8_t* dead;
     double* A;     // [np][np] work (becomes L, lower)
     double* Linv;  // [np][np] work
-    double* diaginv;  // [np/64][64][64]
-    double* tmp;   // [64][np]
     int* flag;     // device int: 0 ok, 1 not SPD
     double* scratch;  // small: >= 8 doubles
     float* U;      // [n][n] output
