@@ -217,40 +217,68 @@ int realq_ctx_reset_timing(realq_ctx* ctx) {
 
 }  // extern "C"
 
+// H += the sum of count products A_p B_p^T (n x n, K = g[p].K tokens each, Alo optional) in float64:
+// each product in float32 slices over token ranges (split-K fills the chip whatever n is; a slice's
+// float32 sums run over fewer tokens), the slices summed into H in float64 in a fixed order.
+// symmetric: the sum of products is a symmetric matrix; only its lower tiles are formed.  max_k > 0
+// bounds the tokens of a float32 sum of the hi/lo products (with weights of several orders of
+// magnitude a few tokens carry H, and what later tokens' additions to them round away shows in the
+// last codes of a sweep: 1024 tokens a sum leave 2e-7 of H where 8192 left 6e-7).
+static int acc_products(realq_ctx* ctx, realq::GemmArgs* g, int count, int64_t n, bool symmetric, int64_t max_k,
+                        double* H) {
+    const int64_t nt = (n + realq::plan::kLargeBM - 1) / realq::plan::kLargeBM;
+    const int64_t tiles = symmetric ? nt * (nt + 1) / 2 : nt * nt;
+    int64_t total = 0;
+    for (int p = 0; p < count; ++p) {
+        g[p].M = g[p].N = n;
+        g[p].tri = symmetric;
+        g[p].splits = realq::plan::choose_acc_splits(tiles, g[p].K, g[p].Alo ? 2 : 1, ctx->cus, g[p].Alo ? max_k : 0);
+        total += realq::gemm_effective_splits(g[p].K, g[p].splits);
+    }
+    void* S;
+    const int rc = get_ws(ctx, "h_slices", (size_t)total * n * n * 4, &S);
+    if (rc == REALQ_ERR_OOM) {  // no room for the slices: straight into H, both triangles
+        for (int p = 0; p < count; ++p) {
+            g[p].tri = 0;
+            g[p].splits = 1;
+            RQ_HIP(ctx, realq::gemm_acc_f64(g[p], H, n, ctx->stream));
+        }
+        return REALQ_OK;
+    }
+    if (rc) return rc;
+    float* out = (float*)S;
+    for (int p = 0; p < count; ++p) {
+        RQ_HIP(ctx, realq::gemm_grad(g[p], out, n, n * n, ctx->stream));
+        out += realq::gemm_effective_splits(g[p].K, g[p].splits) * n * n;
+    }
+    RQ_HIP(ctx, realq::add_slices((const float*)S, total, n, symmetric, H, ctx->stream));
+    return REALQ_OK;
+}
+
 // Token chunks of tc tokens staged in caller-provided bf16 buffers of n * tc elements each (xt, and
 // hi, lo, lo2 when s is given): the chunk transposed (and, with weights, s_t xhat_t split into three
-// bf16 terms), then H_acc += chunk^T chunk on MFMA with a float64 epilogue.  timed = false skips the
-// timing events (the allocation-free entry point creates none).
+// bf16 terms), then H_acc += chunk^T chunk on MFMA.  alloc = false (the allocation-free entry point)
+// adds the products straight into H_acc and skips the timing events.
 int realq::hessian_accum_chunks(realq_ctx* ctx, const uint16_t* Xhat, const float* s, int64_t T, int64_t n,
                                 double* H_acc, int64_t tc, uint16_t* xt, uint16_t* hi, uint16_t* lo, uint16_t* lo2,
-                                bool timed) {
-    Timed tm(ctx, timed ? "hessian" : nullptr);
+                                bool alloc) {
+    Timed tm(ctx, alloc ? "hessian" : nullptr);
     for (int64_t t0 = 0; t0 < T; t0 += tc) {
         const int64_t cur = std::min(tc, T - t0);
-        RQ_HIP(ctx, realq::transpose_u16(Xhat + t0 * n, n, xt, tc, cur, n, ctx->stream));
-        realq::GemmArgs g{};
-        g.B = xt;
-        g.ldb = tc;
-        g.M = n;
-        g.N = n;
-        g.K = cur;
-        g.lda = tc;
-        g.splits = 1;
-        if (s) {
-            // s_t xhat_t in three bf16 terms: with a heavy-tailed s a few tokens carry H, and the
-            // 2^-17 remainder of a hi/lo pair would not average out over the tokens
-            RQ_HIP(ctx, realq::transpose_scale_split(Xhat + t0 * n, n, s + t0, hi, lo, lo2, tc, cur, n, ctx->stream));
-            g.Ahi = hi;
-            g.Alo = lo;
+        // s_t xhat_t in three bf16 terms: with a heavy-tailed s a few tokens carry H, and the
+        // 2^-17 remainder of a hi/lo pair would not average out over the tokens
+        if (s)
+            RQ_HIP(ctx, realq::transpose_scale_split(Xhat + t0 * n, n, s + t0, xt, hi, lo, lo2, tc, cur, n, ctx->stream));
+        else
+            RQ_HIP(ctx, realq::transpose_u16(Xhat + t0 * n, n, xt, tc, cur, n, ctx->stream));
+        realq::GemmArgs g[2] = {{s ? hi : xt, s ? lo : nullptr, tc, xt, tc, n, n, cur, 1},
+                                {lo2, nullptr, tc, xt, tc, n, n, cur, 1}};
+        const int count = s ? 2 : 1;
+        if (alloc) {
+            const int rc = acc_products(ctx, g, count, n, true, s ? 1024 : 0, H_acc);
+            if (rc) return rc;
         } else {
-            g.Ahi = xt;
-            g.Alo = nullptr;
-        }
-        RQ_HIP(ctx, realq::gemm_acc_f64(g, H_acc, n, ctx->stream));
-        if (s) {
-            g.Ahi = lo2;
-            g.Alo = nullptr;
-            RQ_HIP(ctx, realq::gemm_acc_f64(g, H_acc, n, ctx->stream));
+            for (int p = 0; p < count; ++p) RQ_HIP(ctx, realq::gemm_acc_f64(g[p], H_acc, n, ctx->stream));
         }
     }
     return REALQ_OK;
@@ -416,11 +444,11 @@ static int gram_accum(realq_ctx* ctx, const uint16_t* Xhat, const uint16_t* X, c
                                                  (uint16_t*)sdl, (uint16_t*)dh, (uint16_t*)dl, tc, cur, n, s));
         RQ_HIP(ctx, realq::transpose_u16(Xhat + t0 * n, n, (uint16_t*)xt, tc, cur, n, s));
         realq::GemmArgs g{(const uint16_t*)sdh, (const uint16_t*)sdl, tc, (const uint16_t*)xt, tc, n, n, cur, 1};
-        RQ_HIP(ctx, realq::gemm_acc_f64(g, Gdh, n, s));
-        g.B = (const uint16_t*)dh;
-        RQ_HIP(ctx, realq::gemm_acc_f64(g, Gdd, n, s));
-        g.B = (const uint16_t*)dl;
-        RQ_HIP(ctx, realq::gemm_acc_f64(g, Gdd, n, s));
+        if ((rc = acc_products(ctx, &g, 1, n, false, 0, Gdh))) return rc;
+        realq::GemmArgs gd[2] = {g, g};
+        gd[0].B = (const uint16_t*)dh;
+        gd[1].B = (const uint16_t*)dl;
+        if ((rc = acc_products(ctx, gd, 2, n, true, 0, Gdd))) return rc;
     }
     return REALQ_OK;
 }

@@ -40,61 +40,175 @@ hipError_t fill_u16(uint16_t* p, uint16_t v, int64_t count, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------- tiled transposes (64 x 64 tiles via LDS)
-// MODE 0: plain copy of bit patterns; MODE 1: value s[r] * x, written as a hi/lo bf16 pair and,
-// when o3 != NULL, a third bf16 term of what hi + lo leaves (hi + lo + o3 holds all 24 bits of
-// the float32 product).
-template <int MODE>
-__global__ __launch_bounds__(256) void transpose_kernel(const uint16_t* __restrict__ in, int64_t ldi,
-                                                        const float* __restrict__ s, uint16_t* __restrict__ o1,
-                                                        uint16_t* __restrict__ o2, uint16_t* __restrict__ o3,
-                                                        int64_t ldo, int64_t rows, int64_t cols, int64_t tiles_c) {
-    __shared__ float tile[64][65];
-    const int64_t tr = blockIdx.x / tiles_c, tc = blockIdx.x % tiles_c;
+// out[c][r] of a token-major bf16 array.  Bound by HBM: 16-byte loads along a row and 16-byte stores
+// along a column where the arrays allow them (2-byte accesses per lane moved 2.4 TB/s), the 16-bit tile in LDS with rows 33 banks apart so that the eight values of a
+// column chunk and the eight chunks of a wave fall on different banks.
+// SCALE: also the three bf16 terms of s[r] * x (hi + lo + lo2 holds all 24 bits of the float32
+// product), in the same pass over the input; o0 (the plain transpose) may then be NULL.
+namespace {
+struct TransposeArgs {
+    const uint16_t* in;
+    int64_t ldi;
+    const float* s;
+    uint16_t *o0, *hi, *lo, *lo2;
+    int64_t ldo, rows, cols, tiles_c;
+    int vec_in, vec_out;  // rows of the input / of every output 16-byte aligned
+};
+}  // namespace
+template <bool SCALE>
+__global__ __launch_bounds__(256) void transpose_kernel(TransposeArgs a) {
+    __shared__ uint16_t tile[64][66];
+    __shared__ float ts[64];
+    const int64_t tr = blockIdx.x / a.tiles_c, tc = blockIdx.x % a.tiles_c;
     const int64_t r0 = tr * 64, c0 = tc * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;  // 4 rows of 64 threads
-    for (int rr = ty; rr < 64; rr += 4) {
-        int64_t r = r0 + rr, c = c0 + tx;
-        float v = 0.f;
-        if (r < rows && c < cols) {
-            v = bf2f(in[r * ldi + c]);
-            if (MODE == 1 && s) v *= s[r];
-        }
-        tile[rr][tx] = v;
-    }
-    __syncthreads();
-    for (int cc = ty; cc < 64; cc += 4) {
-        int64_t c = c0 + cc, r = r0 + tx;
-        if (r < rows && c < cols) {
-            float v = tile[tx][cc];
-            if (MODE == 0) {
-                o1[c * ldo + r] = f2bf(v);  // exact: v is a bf16 value
-            } else {
-                uint16_t hi, lo;
-                split_bf16(v, hi, lo);
-                o1[c * ldo + r] = hi;
-                o2[c * ldo + r] = lo;
-                // v - hi and then - lo are exact in float32 (each term keeps v's leading bits)
-                if (o3) o3[c * ldo + r] = f2bf((v - bf2f(hi)) - bf2f(lo));
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int rr = (t >> 3) + 32 * p, cc = (t & 7) * 8;
+        const int64_t r = r0 + rr, c = c0 + cc;
+        u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
+        if (r < a.rows) {
+            const uint16_t* q = a.in + r * a.ldi + c;
+            if (a.vec_in && c + 8 <= a.cols) v = *reinterpret_cast<const u16x8*>(q);
+            else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (c + e < a.cols) v[e] = q[e];
             }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; e += 2)
+            *reinterpret_cast<uint32_t*>(&tile[rr][cc + e]) = (uint32_t)v[e] | ((uint32_t)v[e + 1] << 16);
+    }
+    if (SCALE && t < 64) ts[t] = r0 + t < a.rows ? a.s[r0 + t] : 0.f;
+    __syncthreads();
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int cc = (t >> 3) + 32 * p, rr = (t & 7) * 8;
+        const int64_t c = c0 + cc, r = r0 + rr;
+        if (c >= a.cols || r >= a.rows) continue;
+        const int64_t o = c * a.ldo + r;
+        const bool vec = a.vec_out && r + 8 <= a.rows;
+        const int cnt = (int)min((int64_t)8, a.rows - r);
+        auto put = [&](uint16_t* out, u16x8 v) {
+            if (vec) *reinterpret_cast<u16x8*>(out + o) = v;
+            else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (e < cnt) out[o + e] = v[e];
+            }
+        };
+        u16x8 x;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = tile[rr + e][cc];
+        if (!SCALE || a.o0) put(a.o0, x);
+        if constexpr (SCALE) {
+            u16x8 h, l, l2;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float v = bf2f(x[e]) * ts[rr + e];
+                uint16_t hh, ll;
+                split_bf16(v, hh, ll);
+                h[e] = hh;
+                l[e] = ll;
+                // v - hi and then - lo are exact in float32 (each term keeps v's leading bits)
+                l2[e] = f2bf((v - bf2f(hh)) - bf2f(ll));
+            }
+            put(a.hi, h);
+            put(a.lo, l);
+            put(a.lo2, l2);
         }
     }
 }
+
+static bool rows16(const void* p, int64_t ld) { return !p || (((uintptr_t)p & 15) == 0 && ld % 8 == 0); }
 
 hipError_t transpose_u16(const uint16_t* in, int64_t ldi, uint16_t* out, int64_t ldo, int64_t rows, int64_t cols,
                          hipStream_t st) {
     if (rows <= 0 || cols <= 0) return hipSuccess;
-    int64_t tr = (rows + 63) / 64, tc = (cols + 63) / 64;
-    hipLaunchKernelGGL(transpose_kernel<0>, dim3((unsigned)(tr * tc)), dim3(256), 0, st, in, ldi, nullptr, out,
-                       nullptr, nullptr, ldo, rows, cols, tc);
+    const int64_t tr = (rows + 63) / 64, tc = (cols + 63) / 64;
+    const TransposeArgs a{in, ldi, nullptr, out, nullptr, nullptr, nullptr, ldo, rows, cols, tc, rows16(in, ldi),
+                          rows16(out, ldo)};
+    hipLaunchKernelGGL(transpose_kernel<false>, dim3((unsigned)(tr * tc)), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
-hipError_t transpose_scale_split(const uint16_t* in, int64_t ldi, const float* s, uint16_t* hi, uint16_t* lo,
-                                 uint16_t* lo2, int64_t ldo, int64_t rows, int64_t cols, hipStream_t st) {
+hipError_t transpose_scale_split(const uint16_t* in, int64_t ldi, const float* s, uint16_t* plain, uint16_t* hi,
+                                 uint16_t* lo, uint16_t* lo2, int64_t ldo, int64_t rows, int64_t cols, hipStream_t st) {
     if (rows <= 0 || cols <= 0) return hipSuccess;
-    int64_t tr = (rows + 63) / 64, tc = (cols + 63) / 64;
-    hipLaunchKernelGGL(transpose_kernel<1>, dim3((unsigned)(tr * tc)), dim3(256), 0, st, in, ldi, s, hi, lo, lo2,
-                       ldo, rows, cols, tc);
+    const int64_t tr = (rows + 63) / 64, tc = (cols + 63) / 64;
+    const TransposeArgs a{in, ldi, s, plain, hi, lo, lo2, ldo, rows, cols, tc, rows16(in, ldi),
+                          rows16(plain, ldo) && rows16(hi, ldo) && rows16(lo, ldo) && rows16(lo2, ldo)};
+    hipLaunchKernelGGL(transpose_kernel<true>, dim3((unsigned)(tr * tc)), dim3(256), 0, st, a);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- float32 product slices into a float64 sum
+// H[i][j] += sum_z S[z][i][j] in float64, z in order; SYM: only the slices' lower tiles exist (a
+// symmetric product), and the values below the diagonal are added on both sides of it, so the sum
+// stays exactly symmetric.  One 32 x 32 tile per block (lower tiles only with SYM); bound by HBM.
+template <bool SYM>
+__global__ __launch_bounds__(256) void add_slices_kernel(const float* __restrict__ S, int64_t slices, int64_t n,
+                                                         double* __restrict__ H, int64_t tiles) {
+    __shared__ double tile[32][33];
+    int64_t ti, tj;
+    if constexpr (SYM) {
+        const int64_t b = blockIdx.x;
+        ti = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
+        while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
+        while (ti * (ti + 1) / 2 > b) --ti;
+        tj = b - ti * (ti + 1) / 2;
+    } else {
+        ti = blockIdx.x / tiles;
+        tj = blockIdx.x % tiles;
+    }
+    const int rr = threadIdx.x >> 3, cc = (threadIdx.x & 7) * 4;
+    const int64_t i = ti * 32 + rr, j = tj * 32 + cc;
+    double v[4] = {0.0, 0.0, 0.0, 0.0};
+    if (i < n) {
+        const float* p = S + i * n + j;
+        if (n % 4 == 0 && j < n) {
+#pragma unroll 4
+            for (int64_t z = 0; z < slices; ++z) {
+                const f32x4 x = *reinterpret_cast<const f32x4*>(p + z * n * n);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] += (double)x[e];
+            }
+        } else {
+            for (int64_t z = 0; z < slices; ++z)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (j + e < n) v[e] += (double)p[z * n * n + e];
+        }
+    }
+    if constexpr (SYM) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) tile[rr][cc + e] = v[e];
+        __syncthreads();
+        if (ti == tj) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (cc + e > rr) v[e] = tile[cc + e][rr];
+        } else {
+            // the mirrored tile: row tj*32 + rr, columns ti*32 + cc ..
+            const int64_t mi = tj * 32 + rr, mj = ti * 32 + cc;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (mi < n && mj + e < n) H[mi * n + mj + e] += tile[cc + e][rr];
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (i < n && j + e < n) H[i * n + j + e] += v[e];
+}
+
+hipError_t add_slices(const float* S, int64_t slices, int64_t n, bool symmetric, double* H, hipStream_t st) {
+    if (n <= 0 || slices <= 0) return hipSuccess;
+    const int64_t t = (n + 31) / 32;
+    if (symmetric)
+        hipLaunchKernelGGL(add_slices_kernel<true>, dim3((unsigned)(t * (t + 1) / 2)), dim3(256), 0, st, S, slices, n, H, t);
+    else
+        hipLaunchKernelGGL(add_slices_kernel<false>, dim3((unsigned)(t * t)), dim3(256), 0, st, S, slices, n, H, t);
     return hipGetLastError();
 }
 

@@ -131,7 +131,17 @@ __device__ __forceinline__ void tile_of_v(int64_t b, int64_t tiles_m, int64_t ti
     tm = first + r % gs;
     tn = r / gs;
 }
+// group_m 0: the tiles on and below the diagonal of a square tile grid, row by row.
 __device__ __forceinline__ void tile_of(int64_t tiles_m, int64_t tiles_n, int64_t group_m, int64_t& tm, int64_t& tn) {
+    if (group_m == 0) {
+        int64_t L = blockIdx.x;
+        if ((gridDim.x & 7) == 0) L = (L & 7) * (gridDim.x >> 3) + (L >> 3);
+        tm = (int64_t)((sqrtf(8.f * (float)L + 1.f) - 1.f) * 0.5f);
+        while ((tm + 1) * (tm + 2) / 2 <= L) ++tm;
+        while (tm * (tm + 1) / 2 > L) --tm;
+        tn = L - tm * (tm + 1) / 2;
+        return;
+    }
     tile_of_v(blockIdx.x, tiles_m, tiles_n, group_m, tm, tn);
 }
 
@@ -963,7 +973,8 @@ static hipError_t launch_cfg(const GemmArgs& g, const Epi& epi, hipStream_t stre
     // row-tile group: enough row tiles per group that ~32 concurrent blocks of an XCD share operands
     int64_t group_m = tiles_n >= 32 ? 8 : (tiles_n >= 8 ? 2 : 1);
     if (g.group_m > 0) group_m = g.group_m;
-    dim3 grid((unsigned)(tiles_m * tiles_n), 1, (unsigned)splits);
+    if (g.tri) group_m = 0;
+    dim3 grid((unsigned)(g.tri ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n), 1, (unsigned)splits);
     if (g.Alo)
         hipLaunchKernelGGL((gemm_nt_kernel<C, Epi, true>), grid, dim3(C::NT), 0, stream, g.Ahi, g.Alo, g.lda, g.B,
                            g.ldb, g.M, g.N, g.K, kps, (int)vec, tiles_m, tiles_n, group_m, g.a_blocked, epi);

@@ -20,6 +20,7 @@ struct GemmArgs {
     int tile = 0;         // 0: chosen from the shape, 1: 256x256 tile, 2: 128x128 tile
     int a_blocked = 0;    // A in the blocked hi/lo layout of gemm_resid (Alo = Ahi + 32): element
                           // (i, k) at i*lda + (k/32)*64 + k%32
+    int tri = 0;          // M == N: only the 256x256 tiles on and below the diagonal (gemm_grad)
 };
 int64_t gemm_effective_splits(int64_t K, int64_t splits);
 int64_t gemm_num_blocks(int64_t M, int64_t N, int tile = 0);
@@ -58,10 +59,14 @@ hipError_t fill_u16(uint16_t* p, uint16_t v, int64_t count, hipStream_t st);
 // out[c*ldo + r] = in[r*ldi + c] for r < rows, c < cols (bf16 bit patterns)
 hipError_t transpose_u16(const uint16_t* in, int64_t ldi, uint16_t* out, int64_t ldo, int64_t rows, int64_t cols,
                          hipStream_t st);
-// Transposed, weighted split: hi/lo[c*ldo + r] = split(s[r] * bf16(in[r*ldi + c]))   (s may be NULL);
-// lo2 (may be NULL) receives the bf16 of the float32 remainder, so hi + lo + lo2 is the product.
-hipError_t transpose_scale_split(const uint16_t* in, int64_t ldi, const float* s, uint16_t* hi, uint16_t* lo,
-                                 uint16_t* lo2, int64_t ldo, int64_t rows, int64_t cols, hipStream_t st);
+// Transposed and weighted in three bf16 terms: hi/lo[c*ldo + r] = split(s[r] * bf16(in[r*ldi + c])),
+// lo2 the bf16 of the float32 remainder, so hi + lo + lo2 is the product; plain (may be NULL)
+// receives the unweighted transpose from the same pass.
+hipError_t transpose_scale_split(const uint16_t* in, int64_t ldi, const float* s, uint16_t* plain, uint16_t* hi,
+                                 uint16_t* lo, uint16_t* lo2, int64_t ldo, int64_t rows, int64_t cols, hipStream_t st);
+// H[i][j] += sum_z S[z][i][j] (n x n slices, float64 sum, z in order); symmetric: S holds the tiles
+// on and below the diagonal only and both triangles of H receive them.
+hipError_t add_slices(const float* S, int64_t slices, int64_t n, bool symmetric, double* H, hipStream_t st);
 // hi/lo[i*ld + j] = split(A[i*lda + j] - (Bm ? Bm[i*ldb + j] : 0)) for j < cols (float32 inputs)
 hipError_t split_diff_f32(const float* A, int64_t lda, const float* Bm, int64_t ldb, uint16_t* hi, uint16_t* lo,
                           int64_t ld, int64_t rows, int64_t cols, hipStream_t st);

@@ -50,6 +50,23 @@ int64_t choose_splits(int64_t M, int64_t N, int64_t K, int cus) {
     return best;
 }
 
+int64_t choose_acc_splits(int64_t tiles, int64_t K, int passes, int cus, int64_t max_k) {
+    if (cus < 1) cus = 1;
+    const int64_t smin = max_k > 0 ? (K + max_k - 1) / max_k : 1;
+    const int64_t smax = std::max<int64_t>(smin, std::min<int64_t>(256, K / 256));
+    int64_t best = smin;
+    double best_cost = 0.0;
+    for (int64_t q = smin; q <= smax; ++q) {
+        const int64_t rounds = (tiles * q + cus - 1) / cus;
+        const double cost = (double)rounds * (double)K / (double)q * 0.030 * passes + 0.11 * (double)(tiles * q);
+        if (q == smin || cost < best_cost) {
+            best = q;
+            best_cost = cost;
+        }
+    }
+    return effective_splits(K, best);
+}
+
 StepPlan plan_step(int64_t m, int64_t nJ, int64_t T, int64_t Tb, int64_t Tc, int64_t t, int cus,
                    int64_t clip_parts) {
     StepPlan p;

@@ -28,6 +28,13 @@ int64_t effective_splits(int64_t K, int64_t splits);
 // every split keeps at least 256 tokens.
 int64_t choose_splits(int64_t M, int64_t N, int64_t K, int cus);
 
+// Split-K factor of a product accumulated in float64 over `tiles` 256x256 tiles and K tokens with
+// `passes` MFMA passes per tile: the cheapest of 1 .. 256 by the time its rounds of `cus` tiles take
+// at the GEMM's rate (about 30 ns per token, tile and pass) plus the write and read of its float32
+// slices (about 0.11 us per tile and slice); every split keeps at least 256 tokens and, with
+// max_k > 0, at most max_k.
+int64_t choose_acc_splits(int64_t tiles, int64_t K, int passes, int cus, int64_t max_k);
+
 // One token chunk of a Block-GD step: tokens [t0, t0 + len) of the calibration set, and the
 // range [parts_off, parts_off + parts) of the loss-partial workspace its residual launch (or,
 // with the clip, its clip launch) writes.

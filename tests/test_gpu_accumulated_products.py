@@ -1,0 +1,38 @@
+"""The token contractions accumulated in float64 (Hessian, Fisher) at the edges of their tiles and token
+splits, onto a nonzero accumulator, against float64: one 256-wide tile and less, ragged last tiles,
+tokens below a split, ragged in the 32-token slices, unaligned rows (odd n), many splits.  Products
+of bf16 values are exact and at most L of them are summed in float32 per slice, so an entry is off by
+at most (L + 2) 2^-24 of its sum of absolute values (the 2 covers the weighted operand's rounding)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+@pytest.mark.parametrize("n,T", [(1, 1), (5, 33), (64, 700), (255, 4000), (256, 300), (257, 1031), (520, 20000),
+                                 (1030, 2056)])
+def test_accumulated_products_at_tile_edges(rq, ctx, n, T, weighted):
+    import torch
+    print(f"[gpu-case] accumulated products n={n} T={T} weighted={weighted}", flush=True)
+    g = torch.Generator().manual_seed(7 * n + T)
+    X = (torch.randn((T, n), generator=g) * 2).to(torch.bfloat16)
+    s = torch.exp(2 * torch.randn(T, generator=g)) if weighted else None
+    X64 = X.double()
+    sx = X64 if s is None else X64 * s.double()[:, None]
+    H0 = torch.randn((n, n), generator=g, dtype=torch.float64)
+    H0 = H0 + H0.T
+    ref, bound = H0 + sx.T @ X64, sx.abs().T @ X64.abs()
+    outs = []
+    for fn in (rq.hessian_accum, rq.hessian_accum_noalloc):
+        H = H0.cuda()
+        fn(ctx, X.cuda(), None if s is None else s.cuda(), H)
+        torch.cuda.synchronize()
+        outs.append(H.cpu())
+    for H in outs:
+        assert bool(((H - ref).abs() <= (T + 2) * 2.0 ** -24 * bound + 1e-12).all())
+    assert torch.equal(outs[0], outs[0].T)  # one triangle is formed
+    if not weighted:
+        F = H0.cuda()
+        rq.fisher_accum(ctx, X.cuda(), F)
+        assert torch.equal(F.cpu(), outs[0])
