@@ -85,16 +85,25 @@ struct realq_bgd_state {
     int64_t t = 0;  // Adam step counter (one per module)
     int64_t locked = 0;  // columns [0, locked) are folded into the residual base
     bool owns = true;
-    float* B = nullptr;  // [m,T] residual base
+    // Rows of every GEMM operand start on 16 bytes whatever n and T are (the direct-to-LDS loads need
+    // it; the checked register path is about 6x slower): columns padded to ldn, tokens to Tp.  When
+    // the steps' token chunks do not start on multiples of 8 tokens each chunk starts on a multiple of
+    // 64 in the token-minor arrays instead (chunk_pos), and Xg / sg are padded copies where the
+    // caller's rows or chunk starts are not aligned.
+    int64_t ldn = 0, Tp = 0;
+    bool chunked = false;
+    const uint16_t* Xg = nullptr;  // [T,ldn] Xhat as the GEMMs read it
+    const float* sg = nullptr;     // [Tp] token weights at their chunk positions, or NULL
+    float* B = nullptr;  // [m,Tp] residual base
     float* mA = nullptr;
     float* vA = nullptr;  // [m,n]
     uint16_t* Dhi = nullptr;
-    uint16_t* Dlo = nullptr;  // [m,n] split(W - W0)
-    uint16_t* XhT = nullptr;  // [n,T]
+    uint16_t* Dlo = nullptr;  // [m,ldn] split(W - W0)
+    uint16_t* XhT = nullptr;  // [n,Tp]
     uint16_t* Rhi = nullptr;  // split(R o s): blocked layout [m, r_ld(Tc)], or with the clip
-    uint16_t* Rlo = nullptr;  // two arrays Rhi/Rlo [m, Tc]
+    uint16_t* Rlo = nullptr;  // two arrays Rhi/Rlo [m, q_ld(Tc)]
     int64_t Tb = 0, nbatch = 1;  // tokens per step and number of batches (mini-batch BGD)
-    float* Rf = nullptr;         // [m,Tc] residual kept whole for the clip
+    float* Rf = nullptr;         // [m,q_ld(Tc)] residual kept whole for the clip
     float* tau = nullptr;        // [Tc] per-token clip thresholds
     // increments within a column block: L0 the loss of the block's first step (device scalar),
     // G0 its gradient ([m, n - c1], unscaled sum over tokens), Dacc [m,n] the weight change since
@@ -111,11 +120,11 @@ struct realq_bgd_state {
     // Gram form
     bool gram = false;
     uint16_t* Ghi = nullptr;
-    uint16_t* Glo = nullptr;  // [n,n] split(Xhat^T S Xhat)
+    uint16_t* Glo = nullptr;  // [n,ldn] split(Xhat^T S Xhat)
     float* C0 = nullptr;      // [m,n] W0 Delta^T S Xhat
     float* Pm = nullptr;      // [m,n] D Xhat^T S Xhat (per step)
     double* cconst = nullptr; // <W0 Delta^T S Delta, W0> (device scalar)
-    // blended metric alpha M + (1 - alpha) P as a bf16 pair [m,m], formed once per alpha
+    // blended metric alpha M + (1 - alpha) P as a bf16 pair [m, pad8(m)], formed once per alpha
     uint16_t* Mah = nullptr;
     uint16_t* Mal = nullptr;
     float Ma_alpha = -1.f;
@@ -399,6 +408,31 @@ static int64_t r_ld(int64_t cur) { return 2 * ((cur + 31) / 32) * 32; }
 // row stride of bf16(acc o s) on a later step of a column block (row-major, in the same buffer)
 static int64_t q_ld(int64_t cur) { return ((cur + 31) / 32) * 32; }
 
+static int64_t pad8(int64_t v) { return (v + 7) / 8 * 8; }
+// Position of the token chunk that starts at t0 in the token-minor arrays (B, XhT, sg).
+static int64_t chunk_pos(const realq_bgd_state* st, int64_t t0) {
+    if (!st->chunked) return t0;
+    const int64_t cs = (st->Tc + 63) / 64 * 64, per_batch = (st->Tb + st->Tc - 1) / st->Tc;
+    return (t0 / st->Tb * per_batch + t0 % st->Tb / st->Tc) * cs;
+}
+// Calls f(t0, len, pos) for token ranges that are contiguous in the token-minor arrays: all tokens,
+// or with chunked positions every chunk.
+extern "C++" {
+template <class F>
+static int each_range(const realq_bgd_state* st, F f) {
+    if (!st->chunked) return f((int64_t)0, st->T, (int64_t)0);
+    for (int64_t b0 = 0; b0 < st->T; b0 += st->Tb) {
+        const int64_t b1 = std::min(st->T, b0 + st->Tb);
+        for (int64_t t0 = b0; t0 < b1; t0 += st->Tc)
+            if (int rc = f(t0, std::min(st->Tc, b1 - t0), chunk_pos(st, t0))) return rc;
+    }
+    return REALQ_OK;
+}
+}  // extern "C++"
+static const float* chunk_s(const realq_bgd_state* st, int64_t t0) {
+    return st->sg ? st->sg + chunk_pos(st, t0) : nullptr;
+}
+
 static int state_alloc(realq_bgd_state* st, void** p, size_t bytes, const char* slot) {
     realq_ctx* ctx = st->ctx;
     if (!st->owns) return get_ws(ctx, slot, bytes, p);
@@ -513,7 +547,7 @@ static int inc_init(realq_bgd_state* st) {
     st->L0 = (double*)q;
     if ((rc = state_alloc(st, &q, (size_t)m * n * 4, "s_Dacc"))) return rc;
     st->Dacc = (float*)q;
-    if ((rc = state_alloc(st, &q, (size_t)m * n * 2, "s_Dinc"))) return rc;
+    if ((rc = state_alloc(st, &q, (size_t)m * st->ldn * 2, "s_Dinc"))) return rc;
     st->Dinc = (uint16_t*)q;
     if ((rc = state_alloc(st, &q, (size_t)m * n * 4, "s_G0"))) return rc;
     st->G0 = (float*)q;
@@ -531,25 +565,29 @@ static int state_init(realq_bgd_state* st) {
     st->nbatch = (T + st->Tb - 1) / st->Tb;
     int64_t Tc = st->prm.tok_chunk > 0 ? std::min<int64_t>(st->prm.tok_chunk, st->Tb) : st->Tb;
     st->Tc = Tc;
+    const int64_t ldn = st->ldn = pad8(n);
+    st->chunked = (Tc < T && Tc % 8) || (st->Tb < T && st->Tb % 8);
+    const int64_t per_batch = (st->Tb + Tc - 1) / Tc;
+    const int64_t Tp = st->Tp = st->chunked ? st->nbatch * per_batch * ((Tc + 63) / 64 * 64) : pad8(T);
     int rc;
     void* p;
-    if ((rc = state_alloc(st, &p, (size_t)m * T * 4, "s_B"))) return rc;
+    if ((rc = state_alloc(st, &p, (size_t)m * Tp * 4, "s_B"))) return rc;
     st->B = (float*)p;
     if ((rc = state_alloc(st, &p, (size_t)m * n * 4, "s_m"))) return rc;
     st->mA = (float*)p;
     if ((rc = state_alloc(st, &p, (size_t)m * n * 4, "s_v"))) return rc;
     st->vA = (float*)p;
-    if ((rc = state_alloc(st, &p, (size_t)m * n * 2, "s_Dh"))) return rc;
+    if ((rc = state_alloc(st, &p, (size_t)m * ldn * 2, "s_Dh"))) return rc;
     st->Dhi = (uint16_t*)p;
-    if ((rc = state_alloc(st, &p, (size_t)m * n * 2, "s_Dl"))) return rc;
+    if ((rc = state_alloc(st, &p, (size_t)m * ldn * 2, "s_Dl"))) return rc;
     st->Dlo = (uint16_t*)p;
-    if ((rc = state_alloc(st, &p, (size_t)n * T * 2, "s_XT"))) return rc;
+    if ((rc = state_alloc(st, &p, (size_t)n * Tp * 2, "s_XT"))) return rc;
     st->XhT = (uint16_t*)p;
     if (st->prm.loss_clip > 0.f) {
         // the clip writes split(R o s) as two arrays
-        if ((rc = state_alloc(st, &p, (size_t)m * Tc * 2, "s_Rh"))) return rc;
+        if ((rc = state_alloc(st, &p, (size_t)m * q_ld(Tc) * 2, "s_Rh"))) return rc;
         st->Rhi = (uint16_t*)p;
-        if ((rc = state_alloc(st, &p, (size_t)m * Tc * 2, "s_Rl"))) return rc;
+        if ((rc = state_alloc(st, &p, (size_t)m * q_ld(Tc) * 2, "s_Rl"))) return rc;
         st->Rlo = (uint16_t*)p;
     } else {
         // one array of 128-byte lines (32 tokens' hi, then their lo): whole-line stores
@@ -558,7 +596,7 @@ static int state_init(realq_bgd_state* st) {
         st->Rlo = nullptr;
     }
     if (st->prm.loss_clip > 0.f) {
-        if ((rc = state_alloc(st, &p, (size_t)m * Tc * 4, "s_Rf"))) return rc;
+        if ((rc = state_alloc(st, &p, (size_t)m * q_ld(Tc) * 4, "s_Rf"))) return rc;
         st->Rf = (float*)p;
         if ((rc = state_alloc(st, &p, (size_t)Tc * 4, "s_tau"))) return rc;
         st->tau = (float*)p;
@@ -567,30 +605,54 @@ static int state_init(realq_bgd_state* st) {
     Timed tm(ctx, "init");
     RQ_HIP(ctx, realq::fill_f32(st->mA, 0.f, m * n, s));
     RQ_HIP(ctx, realq::fill_f32(st->vA, 0.f, m * n, s));
-    RQ_HIP(ctx, realq::transpose_u16(st->Xhat, n, st->XhT, T, T, n, s));
+    st->Xg = st->Xhat;
+    if (ldn != n) {
+        if ((rc = state_alloc(st, &p, (size_t)T * ldn * 2, "s_Xg"))) return rc;
+        st->Xg = (const uint16_t*)p;
+        RQ_HIP(ctx, realq::copy_rows_u16(st->Xhat, n, (uint16_t*)p, ldn, T, n, s));
+    }
+    st->sg = st->s;
+    if (st->s && st->chunked) {
+        if ((rc = state_alloc(st, &p, (size_t)Tp * 4, "s_sg"))) return rc;
+        st->sg = (const float*)p;
+        if ((rc = each_range(st, [&](int64_t t0, int64_t len, int64_t pos) -> int {
+                 RQ_HIP(ctx, hipMemcpyAsync((float*)p + pos, st->s + t0, (size_t)len * 4, hipMemcpyDeviceToDevice, s));
+                 return REALQ_OK;
+             })))
+            return rc;
+    }
+    if ((rc = each_range(st, [&](int64_t t0, int64_t len, int64_t pos) -> int {
+             RQ_HIP(ctx, realq::transpose_u16(st->Xg + t0 * ldn, ldn, st->XhT + pos, Tp, len, n, s));
+             return REALQ_OK;
+         })))
+        return rc;
     // Residual base before any block is locked: B = W0 (Xhat - X)^T.
     if (st->X == st->Xhat) {
-        RQ_HIP(ctx, realq::fill_f32(st->B, 0.f, m * T, s));
+        RQ_HIP(ctx, realq::fill_f32(st->B, 0.f, m * Tp, s));
     } else {
         // W0 = W0hi + W0lo (in the D buffers for now), Xhat - X = Dxh + Dxl (bf16 pairs, exact
         // difference in float32 first): B = W0 Dxh^T (both halves of W0) + W0hi Dxl^T.
-        RQ_HIP(ctx, realq::split_diff_f32(st->W0, n, nullptr, 0, st->Dhi, st->Dlo, n, m, n, s));
-        const int64_t tcx = std::max<int64_t>(8, std::min<int64_t>(T, ((int64_t)(256ll << 20) / (2 * n) / 8) * 8));
+        RQ_HIP(ctx, realq::split_diff_f32(st->W0, n, nullptr, 0, st->Dhi, st->Dlo, ldn, m, n, s));
+        const int64_t tcx = std::max<int64_t>(8, std::min<int64_t>(T, ((int64_t)(256ll << 20) / (2 * ldn) / 8) * 8));
         void *xh, *xl;
-        if ((rc = get_ws(ctx, "i_xh", (size_t)tcx * n * 2, &xh))) return rc;
-        if ((rc = get_ws(ctx, "i_xl", (size_t)tcx * n * 2, &xl))) return rc;
-        for (int64_t t0 = 0; t0 < T; t0 += tcx) {
-            const int64_t cur = std::min(tcx, T - t0);
-            RQ_HIP(ctx, realq::split_diff_bf16(st->Xhat + t0 * n, st->X + t0 * n, (uint16_t*)xh, (uint16_t*)xl,
-                                               cur * n, s));
-            realq::GemmArgs g{st->Dhi, st->Dlo, n, (const uint16_t*)xh, n, m, cur, n, 1};
-            RQ_HIP(ctx, realq::gemm_store_f32(g, st->B + t0, T, 0, 1.f, s));
-            realq::GemmArgs g2{st->Dhi, nullptr, n, (const uint16_t*)xl, n, m, cur, n, 1};
-            RQ_HIP(ctx, realq::gemm_acc_f32(g2, st->B + t0, T, 1.f, s));
-        }
+        if ((rc = get_ws(ctx, "i_xh", (size_t)tcx * ldn * 2, &xh))) return rc;
+        if ((rc = get_ws(ctx, "i_xl", (size_t)tcx * ldn * 2, &xl))) return rc;
+        if ((rc = each_range(st, [&](int64_t r0, int64_t len, int64_t pos) -> int {
+                 for (int64_t t0 = 0; t0 < len; t0 += tcx) {
+                     const int64_t cur = std::min(tcx, len - t0);
+                     RQ_HIP(ctx, realq::split_diff_bf16(st->Xhat + (r0 + t0) * n, st->X + (r0 + t0) * n, (uint16_t*)xh,
+                                                        (uint16_t*)xl, ldn, cur, n, s));
+                     realq::GemmArgs g{st->Dhi, st->Dlo, ldn, (const uint16_t*)xh, ldn, m, cur, n, 1};
+                     RQ_HIP(ctx, realq::gemm_store_f32(g, st->B + pos + t0, Tp, 0, 1.f, s));
+                     realq::GemmArgs g2{st->Dhi, nullptr, ldn, (const uint16_t*)xl, ldn, m, cur, n, 1};
+                     RQ_HIP(ctx, realq::gemm_acc_f32(g2, st->B + pos + t0, Tp, 1.f, s));
+                 }
+                 return REALQ_OK;
+             })))
+            return rc;
     }
-    RQ_HIP(ctx, realq::fill_u16(st->Dhi, 0, m * n, s));
-    RQ_HIP(ctx, realq::fill_u16(st->Dlo, 0, m * n, s));
+    RQ_HIP(ctx, realq::fill_u16(st->Dhi, 0, m * ldn, s));
+    RQ_HIP(ctx, realq::fill_u16(st->Dlo, 0, m * ldn, s));
     st->t = 0;
     st->locked = 0;
     return inc_init(st);
@@ -606,19 +668,20 @@ static int state_init_gram(realq_bgd_state* st) {
     st->Tc = T;
     st->Tb = T;
     st->nbatch = 1;
+    const int64_t ldn = st->ldn = pad8(n);
     int rc;
     void* p;
     if ((rc = state_alloc(st, &p, (size_t)m * n * 4, "s_m"))) return rc;
     st->mA = (float*)p;
     if ((rc = state_alloc(st, &p, (size_t)m * n * 4, "s_v"))) return rc;
     st->vA = (float*)p;
-    if ((rc = state_alloc(st, &p, (size_t)m * n * 2, "s_Dh"))) return rc;
+    if ((rc = state_alloc(st, &p, (size_t)m * ldn * 2, "s_Dh"))) return rc;
     st->Dhi = (uint16_t*)p;
-    if ((rc = state_alloc(st, &p, (size_t)m * n * 2, "s_Dl"))) return rc;
+    if ((rc = state_alloc(st, &p, (size_t)m * ldn * 2, "s_Dl"))) return rc;
     st->Dlo = (uint16_t*)p;
-    if ((rc = state_alloc(st, &p, (size_t)n * n * 2, "s_Gh"))) return rc;
+    if ((rc = state_alloc(st, &p, (size_t)n * ldn * 2, "s_Gh"))) return rc;
     st->Ghi = (uint16_t*)p;
-    if ((rc = state_alloc(st, &p, (size_t)n * n * 2, "s_Gl"))) return rc;
+    if ((rc = state_alloc(st, &p, (size_t)n * ldn * 2, "s_Gl"))) return rc;
     st->Glo = (uint16_t*)p;
     if ((rc = state_alloc(st, &p, (size_t)m * n * 4, "s_C0"))) return rc;
     st->C0 = (float*)p;
@@ -640,9 +703,9 @@ static int state_init_gram(realq_bgd_state* st) {
     Timed tm(ctx, "init");
     RQ_HIP(ctx, realq::fill_f32(st->mA, 0.f, m * n, s));
     RQ_HIP(ctx, realq::fill_f32(st->vA, 0.f, m * n, s));
-    RQ_HIP(ctx, realq::fill_u16(st->Dhi, 0, m * n, s));
-    RQ_HIP(ctx, realq::fill_u16(st->Dlo, 0, m * n, s));
-    RQ_HIP(ctx, realq::split_f64((const double*)ghh, st->Ghi, st->Glo, n * n, s));
+    RQ_HIP(ctx, realq::fill_u16(st->Dhi, 0, m * ldn, s));
+    RQ_HIP(ctx, realq::fill_u16(st->Dlo, 0, m * ldn, s));
+    RQ_HIP(ctx, realq::split_f64((const double*)ghh, st->Ghi, st->Glo, ldn, n, n, s));
     double* Ad = (double*)A;
     double* Ed = (double*)E;
     RQ_HIP(ctx, realq::widen_f32(st->W0, Ad, m * n, s));
@@ -658,12 +721,12 @@ static int state_init_gram(realq_bgd_state* st) {
 
 // P = D G_hh on columns [p0, n) (three MFMA passes: D_hi G_hi + D_lo G_hi + D_hi G_lo).
 static int gram_product(realq_ctx* ctx, realq_bgd_state* st, int64_t p0) {
-    const int64_t m = st->m, n = st->n, pw = n - p0;
+    const int64_t m = st->m, n = st->n, ldn = st->ldn, pw = n - p0;
     if (pw <= 0) return REALQ_OK;
     Timed tm(ctx, "gram_step");
-    realq::GemmArgs g{st->Dhi, st->Dlo, n, st->Ghi + p0 * n, n, m, pw, n, 1};
+    realq::GemmArgs g{st->Dhi, st->Dlo, ldn, st->Ghi + p0 * ldn, ldn, m, pw, n, 1};
     RQ_HIP(ctx, realq::gemm_store_f32(g, st->Pm + p0, n, 0, 1.f, ctx->stream));
-    realq::GemmArgs g2{st->Dhi, nullptr, n, st->Glo + p0 * n, n, m, pw, n, 1};
+    realq::GemmArgs g2{st->Dhi, nullptr, ldn, st->Glo + p0 * ldn, ldn, m, pw, n, 1};
     RQ_HIP(ctx, realq::gemm_acc_f32(g2, st->Pm + p0, n, 1.f, ctx->stream));
     return REALQ_OK;
 }
@@ -796,8 +859,9 @@ static int quantize_rows(realq_ctx* ctx, double* W, int64_t m, int64_t n, int64_
     q.ngroups = ngroups;
     q.E = (double*)E;
     q.W0 = st ? st->W0 + r0 * n : nullptr;
-    q.Dhi = st ? st->Dhi + r0 * n : nullptr;
-    q.Dlo = st ? st->Dlo + r0 * n : nullptr;
+    q.Dhi = st ? st->Dhi + r0 * st->ldn : nullptr;
+    q.Dlo = st ? st->Dlo + r0 * st->ldn : nullptr;
+    q.ldd = st ? st->ldn : 0;
     {
         Timed tm(ctx, "quantize");
         RQ_HIP(ctx, realq::quantize_block(q, s));
@@ -817,9 +881,9 @@ static int quantize_rows(realq_ctx* ctx, double* W, int64_t m, int64_t n, int64_
         if (st) {
             a.W0 = st->W0 + r0 * n + c1;
             a.ldw0 = n;
-            a.Dhi = st->Dhi + r0 * n + c1;
-            a.Dlo = st->Dlo + r0 * n + c1;
-            a.ldd = n;
+            a.Dhi = st->Dhi + r0 * st->ldn + c1;
+            a.Dlo = st->Dlo + r0 * st->ldn + c1;
+            a.ldd = st->ldn;
         }
         Timed tm(ctx, "obs");
         RQ_HIP(ctx, realq::obs_update(a, s));
@@ -836,9 +900,14 @@ static int lock_block(realq_ctx* ctx, realq_bgd_state* st, int64_t c0, int64_t b
     st->inc_c1 = -1;  // the residual base moves: the next step starts a block
     st->inc_ready = false;
     if (!st->gram) {
-        realq::GemmArgs g{st->Dhi + c0, st->Dlo + c0, n, st->Xhat + c0, n, st->m, st->T, bs, 1};
+        const int64_t ldn = st->ldn;
         Timed tm(ctx, "lock");
-        RQ_HIP(ctx, realq::gemm_acc_f32(g, st->B, st->T, 1.f, ctx->stream));
+        const int rc = each_range(st, [&](int64_t t0, int64_t len, int64_t pos) -> int {
+            realq::GemmArgs g{st->Dhi + c0, st->Dlo + c0, ldn, st->Xg + t0 * ldn + c0, ldn, st->m, len, bs, 1};
+            RQ_HIP(ctx, realq::gemm_acc_f32(g, st->B + pos, st->Tp, 1.f, ctx->stream));
+            return REALQ_OK;
+        });
+        if (rc) return rc;
     }
     st->locked = c0 + bs;
     return REALQ_OK;
@@ -874,7 +943,7 @@ int realq_bgd_step(realq_ctx* ctx, realq_bgd_state* st, double* W, int64_t c1, f
     if (c1 < 0 || c1 > st->n) return set_error(ctx, REALQ_ERR_SHAPE, "bgd_step: need 0 <= c1 <= n");
     if (!std::isfinite(alpha) || alpha < 0.f || alpha > 1.f)
         return set_error(ctx, REALQ_ERR_INVALID_ARG, "bgd_step: alpha must lie in [0, 1]");
-    const int64_t m = st->m, n = st->n, T = st->T, Tc = st->Tc, nJ = n - c1;
+    const int64_t m = st->m, n = st->n, T = st->T, Tc = st->Tc, nJ = n - c1, ldn = st->ldn, Tp = st->Tp;
     hipStream_t s = ctx->stream;
     if (nJ == 0) {
         if (loss_out) RQ_HIP(ctx, realq::fill_f64(loss_out, NAN, 1, s));
@@ -926,28 +995,30 @@ int realq_bgd_step(realq_ctx* ctx, realq_bgd_state* st, double* W, int64_t c1, f
         for (int64_t ch = 0; ch < nchunks; ++ch) {
             const int64_t t0 = pl.chunks[ch].t0, cur = pl.chunks[ch].len;
             double* const pch = pbase + pl.chunks[ch].parts_off;
-            realq::GemmArgs g{st->Dhi + c1, st->Dlo + c1, n, st->Xhat + t0 * n + c1, n, m, cur, nJ, 1};
+            const int64_t pos = chunk_pos(st, t0);
+            const float* sc = chunk_s(st, t0);
+            realq::GemmArgs g{st->Dhi + c1, st->Dlo + c1, ldn, st->Xg + t0 * ldn + c1, ldn, m, cur, nJ, 1};
             if (inc_step) {
-                realq::GemmArgs gi{st->Dinc + c1, nullptr, n, st->Xhat + t0 * n + c1, n, m, cur, nJ, 1};
+                realq::GemmArgs gi{st->Dinc + c1, nullptr, ldn, st->Xg + t0 * ldn + c1, ldn, m, cur, nJ, 1};
                 Timed tm(ctx, "resid_inc");
-                RQ_HIP(ctx, realq::gemm_resid_inc(gi, st->s ? st->s + t0 : nullptr, st->Rhi, q_ld(cur), pch, s));
+                RQ_HIP(ctx, realq::gemm_resid_inc(gi, sc, st->Rhi, q_ld(cur), pch, s));
             } else if (!clip) {
                 Timed tm(ctx, "resid");
-                RQ_HIP(ctx, realq::gemm_resid(g, st->B + t0, T, st->s ? st->s + t0 : nullptr, st->Rhi, nullptr,
+                RQ_HIP(ctx, realq::gemm_resid(g, st->B + pos, Tp, sc, st->Rhi, nullptr,
                                               r_ld(cur), pch, s, true));
             } else {
                 // residual kept whole, per-token thresholds over the m channels, then the
                 // clipped, weighted split for the gradient GEMM and the loss partials
                 Timed tm(ctx, "resid");
-                RQ_HIP(ctx, realq::gemm_resid_f32(g, st->B + t0, T, st->Rf, cur, s));
+                RQ_HIP(ctx, realq::gemm_resid_f32(g, st->B + pos, Tp, st->Rf, q_ld(cur), s));
                 const int64_t k = std::max<int64_t>(1, (int64_t)std::ceil((double)st->prm.loss_clip * (double)m));
-                RQ_HIP(ctx, realq::clip_select(st->Rf, cur, m, cur, std::min(k, m), st->tau, s));
-                RQ_HIP(ctx, realq::clip_apply(st->Rf, cur, m, cur, st->tau, st->s ? st->s + t0 : nullptr, st->Rhi,
+                RQ_HIP(ctx, realq::clip_select(st->Rf, q_ld(cur), m, cur, std::min(k, m), st->tau, s));
+                RQ_HIP(ctx, realq::clip_apply(st->Rf, q_ld(cur), m, cur, st->tau, sc, st->Rhi,
                                               st->Rlo, pch, s));
             }
             {
-                realq::GemmArgs g{st->Rhi, clip ? st->Rlo : st->Rhi + 32, clip ? cur : r_ld(cur),
-                                  st->XhT + c1 * T + t0, T, m, nJ, cur, pl.splits};
+                realq::GemmArgs g{st->Rhi, clip ? st->Rlo : st->Rhi + 32, clip ? q_ld(cur) : r_ld(cur),
+                                  st->XhT + c1 * Tp + pos, Tp, m, nJ, cur, pl.splits};
                 g.a_blocked = clip ? 0 : 1;
                 if (inc_step) {  // bf16(Q o s) alone, row-major
                     g.Alo = nullptr;
@@ -975,7 +1046,7 @@ int realq_bgd_step(realq_ctx* ctx, realq_bgd_state* st, double* W, int64_t c1, f
             } else if (inc_step) {
                 void* dots;
                 if ((rc = get_ws(ctx, "b_incdots", (size_t)realq::inc_loss_partials() * 8, &dots))) return rc;
-                RQ_HIP(ctx, realq::inc_loss(st->L0, st->G0, st->Dinc + c1, n, m, nJ, pbase, pl.parts_total,
+                RQ_HIP(ctx, realq::inc_loss(st->L0, st->G0, st->Dinc + c1, ldn, m, nJ, pbase, pl.parts_total,
                                             (double)Tn, (double*)dots, loss_out, s));
             } else {
                 RQ_HIP(ctx, realq::reduce_partials(pbase, pl.parts_total, 0.5 / (double)Tn, loss_out, s));
@@ -993,6 +1064,7 @@ int realq_bgd_step(realq_ctx* ctx, realq_bgd_state* st, double* W, int64_t c1, f
     a.m = m;
     a.n = n;
     a.c1 = c1;
+    a.ldd = ldn;
     a.Gp = (const float*)Gp;
     a.splits = splits_used;
     a.gscale = (float)(1.0 / (double)Tn);
@@ -1027,28 +1099,29 @@ int realq_bgd_step(realq_ctx* ctx, realq_bgd_state* st, double* W, int64_t c1, f
         // (the lo*lo term is below float32 rounding of the product).
         if (!st->Mah) {
             void* p;
-            if ((rc = state_alloc(st, &p, (size_t)m * m * 2, "s_Mah"))) return rc;
+            if ((rc = state_alloc(st, &p, (size_t)m * pad8(m) * 2, "s_Mah"))) return rc;
             st->Mah = (uint16_t*)p;
-            if ((rc = state_alloc(st, &p, (size_t)m * m * 2, "s_Mal"))) return rc;
+            if ((rc = state_alloc(st, &p, (size_t)m * pad8(m) * 2, "s_Mal"))) return rc;
             st->Mal = (uint16_t*)p;
             st->Ma_alpha = -1.f;
         }
         if (st->Ma_alpha != alpha) {
-            RQ_HIP(ctx, realq::blend_split(st->M, alpha < 1.f ? st->P : nullptr, alpha, m, st->Mah, st->Mal, s));
+            RQ_HIP(ctx, realq::blend_split(st->M, alpha < 1.f ? st->P : nullptr, alpha, m, st->Mah, st->Mal, pad8(m), s));
             st->Ma_alpha = alpha;
         }
         void *Gm, *gth, *gtl;
         if ((rc = get_ws(ctx, "b_Gm", (size_t)m * nJ * 4, &Gm))) return rc;
-        if ((rc = get_ws(ctx, "b_GTh", (size_t)m * nJ * 2, &gth))) return rc;
-        if ((rc = get_ws(ctx, "b_GTl", (size_t)m * nJ * 2, &gtl))) return rc;
+        if ((rc = get_ws(ctx, "b_GTh", (size_t)pad8(m) * nJ * 2, &gth))) return rc;
+        if ((rc = get_ws(ctx, "b_GTl", (size_t)pad8(m) * nJ * 2, &gtl))) return rc;
         const float invT = (float)(1.0 / (double)Tn);
+        const int64_t mp = pad8(m);
         {
             Timed tm(ctx, "metric");
             RQ_HIP(ctx,
-                   realq::transpose_split_f32((const float*)Gacc, nJ, (uint16_t*)gth, (uint16_t*)gtl, m, m, nJ, s));
-            realq::GemmArgs g1{st->Mah, st->Mal, m, (const uint16_t*)gth, m, m, nJ, m, 1};
+                   realq::transpose_split_f32((const float*)Gacc, nJ, (uint16_t*)gth, (uint16_t*)gtl, mp, m, nJ, s));
+            realq::GemmArgs g1{st->Mah, st->Mal, mp, (const uint16_t*)gth, mp, m, nJ, m, 1};
             RQ_HIP(ctx, realq::gemm_store_f32(g1, (float*)Gm, nJ, 0, invT, s));
-            realq::GemmArgs g2{st->Mah, nullptr, m, (const uint16_t*)gtl, m, m, nJ, m, 1};
+            realq::GemmArgs g2{st->Mah, nullptr, mp, (const uint16_t*)gtl, mp, m, nJ, m, 1};
             RQ_HIP(ctx, realq::gemm_acc_f32(g2, (float*)Gm, nJ, invT, s));
         }
         Timed tm(ctx, "adam");
@@ -1067,18 +1140,28 @@ int realq_bgd_loss(realq_ctx* ctx, realq_bgd_state* st, const double* W, double*
         return gram_loss(ctx, st, W, loss_out);
     }
     // R = B + (W - W0)[:, J] Xhat[:, J]^T with J the columns not yet folded into B.
-    const int64_t m = st->m, T = st->T, Tc = st->Tc, n = st->n, c1 = st->locked, nJ = n - c1;
+    const int64_t m = st->m, T = st->T, Tc = st->Tc, n = st->n, c1 = st->locked, nJ = n - c1, ldn = st->ldn;
     int64_t nparts = 0;
-    const std::vector<realq::plan::Chunk> chunks = realq::plan::plan_loss(m, T, Tc, &nparts);
+    std::vector<realq::plan::Chunk> chunks;
+    // all tokens in chunks; with chunked positions no chunk crosses a batch
+    for (int64_t b0 = 0, Tl = st->chunked ? st->Tb : T; b0 < T; b0 += Tl) {
+        int64_t np = 0;
+        for (realq::plan::Chunk c : realq::plan::plan_loss(m, std::min(Tl, T - b0), Tc, &np)) {
+            c.t0 += b0;
+            c.parts_off += nparts;
+            chunks.push_back(c);
+        }
+        nparts += np;
+    }
     void* parts;
     int rc;
     if ((rc = get_ws(ctx, "b_parts", (size_t)nparts * 8, &parts))) return rc;
-    if (nJ > 0) RQ_HIP(ctx, realq::split_diff_f64(W + c1, n, st->W0 + c1, n, st->Dhi + c1, st->Dlo + c1, n, m, nJ,
+    if (nJ > 0) RQ_HIP(ctx, realq::split_diff_f64(W + c1, n, st->W0 + c1, n, st->Dhi + c1, st->Dlo + c1, ldn, m, nJ,
                                                   ctx->stream));
     for (const auto& c : chunks) {
-        realq::GemmArgs g{st->Dhi + c1, st->Dlo + c1, n, st->Xhat + c.t0 * n + c1, n, m, c.len, nJ, 1};
-        RQ_HIP(ctx, realq::gemm_loss(g, st->B + c.t0, T, st->s ? st->s + c.t0 : nullptr, (double*)parts + c.parts_off,
-                                     ctx->stream));
+        realq::GemmArgs g{st->Dhi + c1, st->Dlo + c1, ldn, st->Xg + c.t0 * ldn + c1, ldn, m, c.len, nJ, 1};
+        RQ_HIP(ctx, realq::gemm_loss(g, st->B + chunk_pos(st, c.t0), st->Tp, chunk_s(st, c.t0),
+                                     (double*)parts + c.parts_off, ctx->stream));
     }
     RQ_HIP(ctx, realq::reduce_partials((const double*)parts, nparts, 0.5 / (double)T, loss_out, ctx->stream));
     return REALQ_OK;
@@ -1137,22 +1220,29 @@ int realq_handoff(realq_ctx* ctx, const float* Wa, const float* Wb, const uint16
     if (T == 0) return REALQ_OK;
     if (!Wa || !X || !Y) return set_error(ctx, REALQ_ERR_INVALID_ARG, "handoff: NULL Wa, X or Y");
     hipStream_t s = ctx->stream;
-    void *hi, *lo;
+    void *hi, *lo, *xg;
     int rc;
-    if ((rc = get_ws(ctx, "h_wh", (size_t)m * n * 2, &hi))) return rc;
-    if ((rc = get_ws(ctx, "h_wl", (size_t)m * n * 2, &lo))) return rc;
+    const int64_t ldn = pad8(n);  // 16-byte operand rows whatever n is
+    if ((rc = get_ws(ctx, "h_wh", (size_t)m * ldn * 2, &hi))) return rc;
+    if ((rc = get_ws(ctx, "h_wl", (size_t)m * ldn * 2, &lo))) return rc;
+    const uint16_t* Xg = X;
+    if (ldn != n) {
+        if ((rc = get_ws(ctx, "h_xg", (size_t)T * ldn * 2, &xg))) return rc;
+        RQ_HIP(ctx, realq::copy_rows_u16(X, n, (uint16_t*)xg, ldn, T, n, s));
+        Xg = (const uint16_t*)xg;
+    }
     // acc[i][t] = sum_j W[i][j] X[t][j], stored token-major
-    realq::GemmArgs g{(const uint16_t*)hi, (const uint16_t*)lo, n, X, n, m, T, n, 1};
+    realq::GemmArgs g{(const uint16_t*)hi, (const uint16_t*)lo, ldn, Xg, ldn, m, T, n, 1};
     if (!Wb) {
-        RQ_HIP(ctx, realq::split_diff_f32(Wa, n, nullptr, 0, (uint16_t*)hi, (uint16_t*)lo, n, m, n, s));
+        RQ_HIP(ctx, realq::split_diff_f32(Wa, n, nullptr, 0, (uint16_t*)hi, (uint16_t*)lo, ldn, m, n, s));
         RQ_HIP(ctx, realq::gemm_store_bf16_t(g, Y, m, s));
         return REALQ_OK;
     }
     void* G;
     if ((rc = get_ws(ctx, "h_gate", (size_t)T * m * 4, &G))) return rc;
-    RQ_HIP(ctx, realq::split_diff_f32(Wa, n, nullptr, 0, (uint16_t*)hi, (uint16_t*)lo, n, m, n, s));
+    RQ_HIP(ctx, realq::split_diff_f32(Wa, n, nullptr, 0, (uint16_t*)hi, (uint16_t*)lo, ldn, m, n, s));
     RQ_HIP(ctx, realq::gemm_store_f32_t(g, (float*)G, m, s));  // gate pre-activation, token-major
-    RQ_HIP(ctx, realq::split_diff_f32(Wb, n, nullptr, 0, (uint16_t*)hi, (uint16_t*)lo, n, m, n, s));
+    RQ_HIP(ctx, realq::split_diff_f32(Wb, n, nullptr, 0, (uint16_t*)hi, (uint16_t*)lo, ldn, m, n, s));
     RQ_HIP(ctx, realq::gemm_swiglu_t(g, (const float*)G, m, Y, m, s));
     return REALQ_OK;
 }

@@ -261,20 +261,39 @@ hipError_t transpose_delta_split(const uint16_t* Xh, const uint16_t* X, int64_t 
     return hipGetLastError();
 }
 
-// hi/lo bf16 pair of float(in[i])
+// hi/lo bf16 pair of float(in[i][j]), rows of `cols` values written with stride ldo
 __global__ void split_f64_kernel(const double* __restrict__ in, uint16_t* __restrict__ hi, uint16_t* __restrict__ lo,
-                                 int64_t count) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < count; e += (int64_t)gridDim.x * blockDim.x) {
+                                 int64_t cols, int64_t ldo, int64_t total) {
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t o = (e / cols) * ldo + e % cols;
         uint16_t h, l;
         split_bf16((float)in[e], h, l);
-        hi[e] = h;
-        lo[e] = l;
+        hi[o] = h;
+        lo[o] = l;
     }
 }
 
-hipError_t split_f64(const double* in, uint16_t* hi, uint16_t* lo, int64_t count, hipStream_t st) {
-    if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(split_f64_kernel, dim3(grid_for(count, 4)), dim3(TB), 0, st, in, hi, lo, count);
+hipError_t split_f64(const double* in, uint16_t* hi, uint16_t* lo, int64_t ldo, int64_t rows, int64_t cols,
+                     hipStream_t st) {
+    const int64_t total = rows * cols;
+    if (total <= 0) return hipSuccess;
+    hipLaunchKernelGGL(split_f64_kernel, dim3(grid_for(total, 4)), dim3(TB), 0, st, in, hi, lo, cols, ldo, total);
+    return hipGetLastError();
+}
+
+// Rows of `cols` bf16 values copied to stride ldo: activations whose rows are not a multiple of 16
+// bytes, laid out once for the GEMMs' direct-to-LDS loads.  One row per blockIdx.x.
+__global__ __launch_bounds__(256) void copy_rows_kernel(const uint16_t* __restrict__ in, int64_t ldi,
+                                                        uint16_t* __restrict__ out, int64_t ldo, int64_t cols) {
+    const uint16_t* p = in + (int64_t)blockIdx.x * ldi;
+    uint16_t* q = out + (int64_t)blockIdx.x * ldo;
+    for (int64_t c = threadIdx.x; c < cols; c += 256) q[c] = p[c];
+}
+
+hipError_t copy_rows_u16(const uint16_t* in, int64_t ldi, uint16_t* out, int64_t ldo, int64_t rows, int64_t cols,
+                         hipStream_t st) {
+    if (rows <= 0 || cols <= 0) return hipSuccess;
+    hipLaunchKernelGGL(copy_rows_kernel, dim3((unsigned)rows), dim3(256), 0, st, in, ldi, out, ldo, cols);
     return hipGetLastError();
 }
 
@@ -504,9 +523,9 @@ hipError_t split_diff_f32(const float* A, int64_t lda, const float* Bm, int64_t 
 }
 
 // Blended metric of Eq. slide_window as a bf16 pair: x = alpha (M or I)[i][k] + (1 - alpha) P[i][k]
-// (P may be NULL), hi = bf16(x), lo = bf16(x - hi); m x m, row-major.
+// (P may be NULL), hi = bf16(x), lo = bf16(x - hi); m x m, written with row stride ldo.
 __global__ void blend_split_kernel(const float* __restrict__ M, const float* __restrict__ P, float alpha, int64_t m,
-                                   uint16_t* __restrict__ hi, uint16_t* __restrict__ lo) {
+                                   uint16_t* __restrict__ hi, uint16_t* __restrict__ lo, int64_t ldo) {
     const int64_t total = m * m;
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
         const int64_t i = e / m, k = e % m;
@@ -514,33 +533,37 @@ __global__ void blend_split_kernel(const float* __restrict__ M, const float* __r
         if (P) v += (1.f - alpha) * P[e];
         uint16_t h, l;
         split_bf16(v, h, l);
-        hi[e] = h;
-        lo[e] = l;
+        hi[i * ldo + k] = h;
+        lo[i * ldo + k] = l;
     }
 }
 
-hipError_t blend_split(const float* M, const float* P, float alpha, int64_t m, uint16_t* hi, uint16_t* lo,
+hipError_t blend_split(const float* M, const float* P, float alpha, int64_t m, uint16_t* hi, uint16_t* lo, int64_t ldo,
                        hipStream_t st) {
     if (m <= 0) return hipSuccess;
-    hipLaunchKernelGGL(blend_split_kernel, dim3(grid_for(m * m, 4)), dim3(TB), 0, st, M, P, alpha, m, hi, lo);
+    hipLaunchKernelGGL(blend_split_kernel, dim3(grid_for(m * m, 4)), dim3(TB), 0, st, M, P, alpha, m, hi, lo, ldo);
     return hipGetLastError();
 }
 
 __global__ void split_diff_bf16_kernel(const uint16_t* __restrict__ a, const uint16_t* __restrict__ b,
-                                       uint16_t* __restrict__ hi, uint16_t* __restrict__ lo, int64_t count) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < count; e += (int64_t)gridDim.x * blockDim.x) {
-        float v = bf2f(a[e]) - bf2f(b[e]);  // exact in float32 for bf16 inputs of similar magnitude
+                                       uint16_t* __restrict__ hi, uint16_t* __restrict__ lo, int64_t cols, int64_t ldo,
+                                       int64_t total) {
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
+        const float v = bf2f(a[e]) - bf2f(b[e]);  // exact in float32 for bf16 inputs of similar magnitude
+        const int64_t o = ldo == cols ? e : (e / cols) * ldo + e % cols;
         uint16_t h, l;
         split_bf16(v, h, l);
-        hi[e] = h;
-        lo[e] = l;
+        hi[o] = h;
+        lo[o] = l;
     }
 }
 
-hipError_t split_diff_bf16(const uint16_t* a, const uint16_t* b, uint16_t* hi, uint16_t* lo, int64_t count,
-                           hipStream_t st) {
-    if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(split_diff_bf16_kernel, dim3(grid_for(count, 4)), dim3(TB), 0, st, a, b, hi, lo, count);
+hipError_t split_diff_bf16(const uint16_t* a, const uint16_t* b, uint16_t* hi, uint16_t* lo, int64_t ldo, int64_t rows,
+                           int64_t cols, hipStream_t st) {
+    const int64_t total = rows * cols;
+    if (total <= 0) return hipSuccess;
+    hipLaunchKernelGGL(split_diff_bf16_kernel, dim3(grid_for(total, 4)), dim3(TB), 0, st, a, b, hi, lo, cols, ldo,
+                       total);
     return hipGetLastError();
 }
 
@@ -579,16 +602,17 @@ __device__ __forceinline__ void adam_elem(const AdamArgs& a, int64_t i, int64_t 
     const float step = a.lr * mh / (sqrtf(vh) + a.eps);
     const double w = a.W[idx] - (double)step;
     a.W[idx] = w;
+    const int64_t di = i * a.ldd + j;
     if (a.Dacc) {
         const float d = (a.inc_reset ? 0.f : a.Dacc[idx]) - step;
         a.Dacc[idx] = d;
-        a.Dinc[idx] = f2bf(d);
+        a.Dinc[di] = f2bf(d);
     }
     if (!a.Dhi) return;
     uint16_t h, l;
     split_bf16((float)(w - (double)a.W0[idx]), h, l);
-    a.Dhi[idx] = h;
-    a.Dlo[idx] = l;
+    a.Dhi[di] = h;
+    a.Dlo[di] = l;
 }
 
 __global__ void adam_kernel(AdamArgs a) {

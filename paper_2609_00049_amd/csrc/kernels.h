@@ -78,8 +78,12 @@ hipError_t split_diff_f64(const double* A, int64_t lda, const float* Bm, int64_t
 hipError_t transpose_delta_split(const uint16_t* Xh, const uint16_t* X, int64_t ldi, const float* s, uint16_t* sdh,
                                  uint16_t* sdl, uint16_t* dh, uint16_t* dl, int64_t ldo, int64_t rows, int64_t cols,
                                  hipStream_t st);
-// hi/lo = split(float(in))
-hipError_t split_f64(const double* in, uint16_t* hi, uint16_t* lo, int64_t count, hipStream_t st);
+// hi/lo[i*ldo + j] = split(float(in[i*cols + j]))
+hipError_t split_f64(const double* in, uint16_t* hi, uint16_t* lo, int64_t ldo, int64_t rows, int64_t cols,
+                     hipStream_t st);
+// out[i*ldo + j] = in[i*ldi + j] for j < cols (bf16 bit patterns)
+hipError_t copy_rows_u16(const uint16_t* in, int64_t ldi, uint16_t* out, int64_t ldo, int64_t rows, int64_t cols,
+                         hipStream_t st);
 // Three-term splits that carry all 24 bits of a float32: hi = bf16(x), lo = bf16(x - hi),
 // lo2 = bf16(x - hi - lo), so hi + lo + lo2 equals x to float32 precision (x = float(in) for the
 // float64 input).
@@ -102,11 +106,11 @@ int64_t dot_f64_partials();
 // out[i] = double(in[i]) / float(in[i])
 hipError_t widen_f32(const float* in, double* out, int64_t count, hipStream_t st);
 hipError_t narrow_f64(const double* in, float* out, int64_t count, hipStream_t st);
-// hi/lo[i] = split(bf16(a[i]) - bf16(b[i]))
-hipError_t split_diff_bf16(const uint16_t* a, const uint16_t* b, uint16_t* hi, uint16_t* lo, int64_t count,
-                           hipStream_t st);
-// hi/lo[i*m + k] = split(alpha (M ? M : I)[i][k] + (1 - alpha) (P ? P[i][k] : 0)), m x m float32 inputs
-hipError_t blend_split(const float* M, const float* P, float alpha, int64_t m, uint16_t* hi, uint16_t* lo,
+// hi/lo[i*ldo + j] = split(bf16(a[i*cols + j]) - bf16(b[i*cols + j]))
+hipError_t split_diff_bf16(const uint16_t* a, const uint16_t* b, uint16_t* hi, uint16_t* lo, int64_t ldo, int64_t rows,
+                           int64_t cols, hipStream_t st);
+// hi/lo[i*ldo + k] = split(alpha (M ? M : I)[i][k] + (1 - alpha) (P ? P[i][k] : 0)), m x m float32 inputs
+hipError_t blend_split(const float* M, const float* P, float alpha, int64_t m, uint16_t* hi, uint16_t* lo, int64_t ldo,
                        hipStream_t st);
 // out = sum of partials (fixed order) * scale, written to *out (device)
 hipError_t reduce_partials(const double* partials, int64_t count, double scale, double* out, hipStream_t st);
@@ -121,11 +125,12 @@ struct AdamArgs {
     uint16_t* Dhi;
     uint16_t* Dlo;
     int64_t m, n, c1;
+    int64_t ldd = 0;  // row stride of Dhi, Dlo and Dinc
     const float* Gp;  // [splits][m][n - c1]
     int64_t splits;
     float gscale, lr, beta1, beta2, eps, bc1, bc2;  // bc1 = 1/(1-beta1^t), bc2 = 1/(1-beta2^t)
     float* Dacc = nullptr;     // [m, n]
-    uint16_t* Dinc = nullptr;  // [m, n]
+    uint16_t* Dinc = nullptr;  // [m, ldd]
     int inc_reset = 0;
     // the block's first gradient, [m][n - c1], unscaled: g0_mode 1 stores sum_z Gp there,
     // 2 adds it to sum_z Gp (later steps, whose Gp holds the change only)
@@ -263,8 +268,9 @@ struct QuantArgs {
     int64_t ngroups;
     double* E;  // [m][bs]
     const float* W0;  // may be NULL (no split written)
-    uint16_t* Dhi;
+    uint16_t* Dhi;    // [m][ldd]
     uint16_t* Dlo;
+    int64_t ldd;
 };
 hipError_t quantize_block(const QuantArgs& q, hipStream_t st);
 // W[i][j] -= sum_k E[i][k] U[k][j] in float64 (M x N, K <= block width); when Dhi != NULL

@@ -410,8 +410,8 @@ __global__ __launch_bounds__(WAVES * 64) void quantize_block_kernel(QuantArgs q)
         if (q.Dhi) {
             uint16_t h, l;
             split_bf16((float)(w0 - (double)q.W0[i * n + c]), h, l);
-            q.Dhi[i * n + c] = h;
-            q.Dlo[i * n + c] = l;
+            q.Dhi[i * q.ldd + c] = h;
+            q.Dlo[i * q.ldd + c] = l;
         }
     }
     if (in1) {
@@ -422,8 +422,8 @@ __global__ __launch_bounds__(WAVES * 64) void quantize_block_kernel(QuantArgs q)
         if (q.Dhi) {
             uint16_t h, l;
             split_bf16((float)(w1 - (double)q.W0[i * n + c]), h, l);
-            q.Dhi[i * n + c] = h;
-            q.Dlo[i * n + c] = l;
+            q.Dhi[i * q.ldd + c] = h;
+            q.Dlo[i * q.ldd + c] = l;
         }
     }
 }
