@@ -226,41 +226,53 @@ int realq_ctx_reset_timing(realq_ctx* ctx) {
 
 }  // extern "C"
 
-// H += the sum of count products A_p B_p^T (n x n, K = g[p].K tokens each, Alo optional) in float64:
-// each product in float32 slices over token ranges (split-K fills the chip whatever n is; a slice's
-// float32 sums run over fewer tokens), the slices summed into H in float64 in a fixed order.
-// symmetric: the sum of products is a symmetric matrix; only its lower tiles are formed.  max_k > 0
-// bounds the tokens of a float32 sum of the hi/lo products (with weights of several orders of
-// magnitude a few tokens carry H, and what later tokens' additions to them round away shows in the
-// last codes of a sweep: 1024 tokens a sum leave 2e-7 of H where 8192 left 6e-7).
-static int acc_products(realq_ctx* ctx, realq::GemmArgs* g, int count, int64_t n, bool symmetric, int64_t max_k,
-                        double* H) {
-    const int64_t nt = (n + realq::plan::kLargeBM - 1) / realq::plan::kLargeBM;
-    const int64_t tiles = symmetric ? nt * (nt + 1) / 2 : nt * nt;
-    int64_t total = 0;
+static hipError_t acc_direct(const realq::GemmArgs& g, double* C, int64_t ldc, bool, hipStream_t st) {
+    return realq::gemm_acc_f64(g, C, ldc, st);
+}
+static hipError_t acc_direct(const realq::GemmArgs& g, float* C, int64_t ldc, bool store, hipStream_t st) {
+    return store ? realq::gemm_store_f32(g, C, ldc, 0, 1.f, st) : realq::gemm_acc_f32(g, C, ldc, 1.f, st);
+}
+
+// C (+)= the sum of count products A_p B_p^T (M x N, g[p].K wide each, Alo optional) in float64:
+// each product in float32 slices over ranges of K (split-K fills the chip whatever M and N are; a
+// slice's float32 sums are shorter), the slices summed into C in float64 in a fixed order.
+// symmetric: the sum of products is a symmetric matrix; only its lower tiles are formed.  flag
+// (device, may be NULL): the products from `always` on are only formed when it reads nonzero.
+// max_k > 0 bounds the terms of a float32 sum of the hi/lo products (with weights of several orders
+// of magnitude a few tokens carry H, and what later tokens' additions to them round away shows in
+// the last codes of a sweep: 1024 tokens a sum leave 2e-7 of H where 8192 left 6e-7).
+template <class Out>
+static int sum_products(realq_ctx* ctx, realq::GemmArgs* g, int count, int always, const int* flag, bool symmetric,
+                        int64_t max_k, bool accumulate, Out* C, int64_t ldc) {
+    const int64_t M = g[0].M, N = g[0].N;
+    const int64_t nt = (M + realq::plan::kLargeBM - 1) / realq::plan::kLargeBM;
+    const int64_t tiles = symmetric ? nt * (nt + 1) / 2 : realq::plan::tiles(M, N, true);
+    int64_t total = 0, first = 0;
     for (int p = 0; p < count; ++p) {
-        g[p].M = g[p].N = n;
         g[p].tri = symmetric;
+        g[p].run_if = p >= always ? flag : nullptr;
         g[p].splits = realq::plan::choose_acc_splits(tiles, g[p].K, g[p].Alo ? 2 : 1, ctx->cus, g[p].Alo ? max_k : 0);
         total += realq::gemm_effective_splits(g[p].K, g[p].splits);
+        if (p + 1 == always) first = total;
     }
     void* S;
-    const int rc = get_ws(ctx, "h_slices", (size_t)total * n * n * 4, &S);
-    if (rc == REALQ_ERR_OOM) {  // no room for the slices: straight into H, both triangles
+    const int rc = get_ws(ctx, "h_slices", (size_t)total * M * N * 4, &S);
+    if (rc == REALQ_ERR_OOM) {  // no room for the slices: straight into C, both triangles
         for (int p = 0; p < count; ++p) {
             g[p].tri = 0;
             g[p].splits = 1;
-            RQ_HIP(ctx, realq::gemm_acc_f64(g[p], H, n, ctx->stream));
+            RQ_HIP(ctx, acc_direct(g[p], C, ldc, p == 0 && !accumulate, ctx->stream));
         }
         return REALQ_OK;
     }
     if (rc) return rc;
     float* out = (float*)S;
     for (int p = 0; p < count; ++p) {
-        RQ_HIP(ctx, realq::gemm_grad(g[p], out, n, n * n, ctx->stream));
-        out += realq::gemm_effective_splits(g[p].K, g[p].splits) * n * n;
+        RQ_HIP(ctx, realq::gemm_grad(g[p], out, N, M * N, ctx->stream));
+        out += realq::gemm_effective_splits(g[p].K, g[p].splits) * M * N;
     }
-    RQ_HIP(ctx, realq::add_slices((const float*)S, total, n, symmetric, H, ctx->stream));
+    RQ_HIP(ctx, realq::add_slices((const float*)S, first, total, flag, M, N, symmetric, accumulate, C, ldc,
+                                  ctx->stream));
     return REALQ_OK;
 }
 
@@ -284,7 +296,7 @@ int realq::hessian_accum_chunks(realq_ctx* ctx, const uint16_t* Xhat, const floa
                                 {lo2, nullptr, tc, xt, tc, n, n, cur, 1}};
         const int count = s ? 2 : 1;
         if (alloc) {
-            const int rc = acc_products(ctx, g, count, n, true, s ? 1024 : 0, H_acc);
+            const int rc = sum_products(ctx, g, count, count, nullptr, true, s ? 1024 : 0, true, H_acc, n);
             if (rc) return rc;
         } else {
             for (int p = 0; p < count; ++p) RQ_HIP(ctx, realq::gemm_acc_f64(g[p], H_acc, n, ctx->stream));
@@ -478,11 +490,11 @@ static int gram_accum(realq_ctx* ctx, const uint16_t* Xhat, const uint16_t* X, c
                                                  (uint16_t*)sdl, (uint16_t*)dh, (uint16_t*)dl, tc, cur, n, s));
         RQ_HIP(ctx, realq::transpose_u16(Xhat + t0 * n, n, (uint16_t*)xt, tc, cur, n, s));
         realq::GemmArgs g{(const uint16_t*)sdh, (const uint16_t*)sdl, tc, (const uint16_t*)xt, tc, n, n, cur, 1};
-        if ((rc = acc_products(ctx, &g, 1, n, false, 0, Gdh))) return rc;
+        if ((rc = sum_products(ctx, &g, 1, 1, nullptr, false, 0, true, Gdh, n))) return rc;
         realq::GemmArgs gd[2] = {g, g};
         gd[0].B = (const uint16_t*)dh;
         gd[1].B = (const uint16_t*)dl;
-        if ((rc = acc_products(ctx, gd, 2, n, true, 0, Gdd))) return rc;
+        if ((rc = sum_products(ctx, gd, 2, 2, nullptr, true, 0, true, Gdd, n))) return rc;
     }
     return REALQ_OK;
 }
@@ -1175,42 +1187,49 @@ int realq_pullback_metric(realq_ctx* ctx, const float* W_next, const float* M_ne
     if (m_next <= 0 || m <= 0) return set_error(ctx, REALQ_ERR_SHAPE, "pullback_metric: need m_next, m > 0");
     if (!W_next || !P) return set_error(ctx, REALQ_ERR_INVALID_ARG, "pullback_metric: NULL W_next or P");
     hipStream_t s = ctx->stream;
-    void *WT, *T1 = nullptr;
+    // Float32 operands as three bf16 terms (all 24 bits), the product from the six term pairs above
+    // its own float32 rounding.  A bf16 checkpoint's weights are exact in the first term: the
+    // launches of the other pairs then find the flag down and return (the flag stays on the device,
+    // the call asynchronous).  M = NULL: W^T W is symmetric, one triangle is formed.
+    // 14336 x 4096 bf16-exact weights: 8.7 ms as a float32 vector GEMM (55 TFLOP/s), now 0.40 ms;
+    // error against float64 1.7e-6 -> 2.7e-7 (shorter float32 sums).
+    const int64_t kp = (m_next + 7) / 8 * 8;
+    struct Terms {
+        uint16_t *hi, *lo, *lo2;
+    };
     int rc;
-    if ((rc = get_ws(ctx, "p_WT", (size_t)m * m_next * 4, &WT))) return rc;
-    RQ_HIP(ctx, realq::transpose_f32(W_next, m, (float*)WT, m_next, m_next, m, s));  // WT = W_next^T [m, m_next]
-    const float* right = W_next;
-    if (M_next) {  // T1 = M_next W_next  [m_next, m]
-        if ((rc = get_ws(ctx, "p_T1", (size_t)m_next * m * 4, &T1))) return rc;
-        realq::SgemmArgs a{};
-        a.A = M_next;
-        a.lda = m_next;
-        a.B = W_next;
-        a.ldb = m;
-        a.C = (float*)T1;
-        a.ldc = m;
-        a.M = m_next;
-        a.N = m;
-        a.K = m_next;
-        a.alpha = 1.f;
-        a.beta = 0.f;
-        RQ_HIP(ctx, realq::sgemm(a, s));
-        right = (const float*)T1;
-    }
-    realq::SgemmArgs a{};
-    a.A = (const float*)WT;
-    a.lda = m_next;
-    a.B = right;
-    a.ldb = m;
-    a.C = P;
-    a.ldc = m;
-    a.M = m;
-    a.N = m;
-    a.K = m_next;
-    a.alpha = 1.f;
-    a.beta = accumulate ? 1.f : 0.f;
-    RQ_HIP(ctx, realq::sgemm(a, s));
-    return REALQ_OK;
+    auto terms = [&](const char* slot, int64_t rows, Terms& t) -> int {
+        void* p;
+        if ((rc = get_ws(ctx, slot, (size_t)3 * rows * kp * 2, &p))) return rc;
+        t.hi = (uint16_t*)p;
+        t.lo = t.hi + rows * kp;
+        t.lo2 = t.lo + rows * kp;
+        return REALQ_OK;
+    };
+    void* flag;
+    if ((rc = get_ws(ctx, "p_flag", 8, &flag))) return rc;
+    RQ_HIP(ctx, realq::fill_f64((double*)flag, 0.0, 1, s));
+    Terms w, r;
+    if ((rc = terms("p_W", m, w))) return rc;
+    RQ_HIP(ctx, realq::transpose_split3_f32(W_next, m, w.hi, w.lo, w.lo2, kp, m_next, m, (int*)flag, s));
+    auto product = [&](const Terms& a, const Terms& b, int64_t N, const int* f, bool sym, bool acc, float* C,
+                       int64_t ldc) -> int {
+        realq::GemmArgs g[4] = {{a.hi, nullptr, kp, b.hi, kp, m, N, m_next, 1},
+                                {a.hi, nullptr, kp, b.lo2, kp, m, N, m_next, 1},
+                                {a.hi, a.lo, kp, b.lo, kp, m, N, m_next, 1},
+                                {a.lo, a.lo2, kp, b.hi, kp, m, N, m_next, 1}};
+        return sum_products(ctx, g, 4, f ? 1 : 4, f, sym, 0, acc, C, ldc);
+    };
+    if (!M_next) return product(w, w, m, (const int*)flag, true, accumulate != 0, P, m);
+    // (M W)^T = W^T M^T [m, m_next], K-contiguous for the second product
+    void* T1;
+    if ((rc = terms("p_M", m_next, r))) return rc;
+    RQ_HIP(ctx, realq::split3_f32(M_next, m_next, r.hi, r.lo, r.lo2, kp, m_next, m_next, nullptr, s));
+    if ((rc = get_ws(ctx, "p_T1", (size_t)m * kp * 4, &T1))) return rc;
+    if ((rc = product(w, r, m_next, nullptr, false, false, (float*)T1, kp))) return rc;
+    if ((rc = terms("p_R", m, r))) return rc;
+    RQ_HIP(ctx, realq::split3_f32((const float*)T1, kp, r.hi, r.lo, r.lo2, kp, m, m_next, nullptr, s));
+    return product(w, r, m, nullptr, false, accumulate != 0, P, m);
 }
 
 int realq_handoff(realq_ctx* ctx, const float* Wa, const float* Wb, const uint16_t* X, int64_t T, int64_t n,

@@ -267,31 +267,9 @@ hipError_t swiglu_bwd(const float* dz, const float* a, const float* b, int which
 }
 
 // hi/lo[c * ldo + r] = split(in[r * ldi + c]) for r < rows, c < cols (float32 in, transposed out).
-__global__ __launch_bounds__(256) void transpose_split_f32_kernel(const float* __restrict__ in, int64_t ldi,
-                                                                  uint16_t* __restrict__ hi, uint16_t* __restrict__ lo,
-                                                                  int64_t ldo, int64_t rows, int64_t cols,
-                                                                  int64_t tiles_c) {
-    __shared__ float tile[64][65];
-    const int64_t tr = blockIdx.x / tiles_c, tc = blockIdx.x % tiles_c;
-    const int64_t r0 = tr * 64, c0 = tc * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int rr = ty; rr < 64; rr += 4) {
-        const int64_t r = r0 + rr, c = c0 + tx;
-        tile[rr][tx] = (r < rows && c < cols) ? in[r * ldi + c] : 0.f;
-    }
-    __syncthreads();
-    for (int cc = ty; cc < 64; cc += 4) {
-        const int64_t c = c0 + cc, r = r0 + tx;
-        if (r < rows && c < cols) split_bf16(tile[tx][cc], hi[c * ldo + r], lo[c * ldo + r]);
-    }
-}
 hipError_t transpose_split_f32(const float* in, int64_t ldi, uint16_t* hi, uint16_t* lo, int64_t ldo, int64_t rows,
                                int64_t cols, hipStream_t st) {
-    if (rows <= 0 || cols <= 0) return hipSuccess;
-    const int64_t tr = (rows + 63) / 64, tc = (cols + 63) / 64;
-    hipLaunchKernelGGL(transpose_split_f32_kernel, dim3((unsigned)(tr * tc)), dim3(TB), 0, st, in, ldi, hi, lo, ldo,
-                       rows, cols, tc);
-    return hipGetLastError();
+    return transpose_split3_f32(in, ldi, hi, lo, nullptr, ldo, rows, cols, nullptr, st);
 }
 
 // The next block's input gradient blended into the current one, per token:

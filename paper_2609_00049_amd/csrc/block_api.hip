@@ -129,9 +129,9 @@ int split_block(realq_ctx* ctx, const char* tag, const realq_mlp_block& b, int64
     if ((rc = ws_split3(ctx, t + "g", f * d, w.g)) || (rc = ws_split3(ctx, t + "u", f * d, w.u)) ||
         (rc = ws_split3(ctx, t + "d", d * f, w.d)) || (rc = ws_split(ctx, t + "dT", f * d, w.dT)))
         return rc;
-    RQ_HIP(ctx, realq::split3_f32(b.Wg, d, w.g.hi, w.g.lo, w.g.lo2, d, f, d, s));
-    RQ_HIP(ctx, realq::split3_f32(b.Wu, d, w.u.hi, w.u.lo, w.u.lo2, d, f, d, s));
-    RQ_HIP(ctx, realq::split3_f32(b.Wd, f, w.d.hi, w.d.lo, w.d.lo2, f, d, f, s));
+    RQ_HIP(ctx, realq::split3_f32(b.Wg, d, w.g.hi, w.g.lo, w.g.lo2, d, f, d, nullptr, s));
+    RQ_HIP(ctx, realq::split3_f32(b.Wu, d, w.u.hi, w.u.lo, w.u.lo2, d, f, d, nullptr, s));
+    RQ_HIP(ctx, realq::split3_f32(b.Wd, f, w.d.hi, w.d.lo, w.d.lo2, f, d, f, nullptr, s));
     RQ_HIP(ctx, realq::transpose_split_f32(b.Wd, f, w.dT.hi, w.dT.lo, d, d, f, s));
     if (backward) {
         if ((rc = ws_split(ctx, t + "gT", d * f, w.gT)) || (rc = ws_split(ctx, t + "uT", d * f, w.uT))) return rc;
@@ -437,7 +437,7 @@ extern "C" int realq_mlp_block_sweep(realq_ctx* ctx, const realq_mlp_desc* D, re
         // the quantized path with this module's final weights
         Split q;
         if ((rc = ws_split3(ctx, "m_sq", m * n, q))) return rc;
-        RQ_HIP(ctx, realq::split3_f32(Wq[mod], n, q.hi, q.lo, q.lo2, n, m, n, s));
+        RQ_HIP(ctx, realq::split3_f32(Wq[mod], n, q.hi, q.lo, q.lo2, n, m, n, nullptr, s));
         if (mod == 0 && (rc = lin_f32(ctx, q, f, d, fq.u, T, fq.a))) return rc;
         if (mod == 1 && (rc = lin_f32(ctx, q, f, d, fq.u, T, fq.b))) return rc;
         if (mod < 2) RQ_HIP(ctx, realq::swiglu_fwd(fq.a, fq.b, fq.z, T * f, s));
@@ -476,10 +476,10 @@ int split_dec(realq_ctx* ctx, const char* tag, const realq_decoder_block& b, int
         (rc = ws_split3(ctx, t + "v", Hk * d, w.v)) || (rc = ws_split3(ctx, t + "o", d * Hq, w.o)) ||
         (rc = ws_split(ctx, t + "oT", Hq * d, w.oT)))
         return rc;
-    RQ_HIP(ctx, realq::split3_f32(b.Wq, d, w.q.hi, w.q.lo, w.q.lo2, d, Hq, d, s));
-    RQ_HIP(ctx, realq::split3_f32(b.Wk, d, w.k.hi, w.k.lo, w.k.lo2, d, Hk, d, s));
-    RQ_HIP(ctx, realq::split3_f32(b.Wv, d, w.v.hi, w.v.lo, w.v.lo2, d, Hk, d, s));
-    RQ_HIP(ctx, realq::split3_f32(b.Wo, Hq, w.o.hi, w.o.lo, w.o.lo2, Hq, d, Hq, s));
+    RQ_HIP(ctx, realq::split3_f32(b.Wq, d, w.q.hi, w.q.lo, w.q.lo2, d, Hq, d, nullptr, s));
+    RQ_HIP(ctx, realq::split3_f32(b.Wk, d, w.k.hi, w.k.lo, w.k.lo2, d, Hk, d, nullptr, s));
+    RQ_HIP(ctx, realq::split3_f32(b.Wv, d, w.v.hi, w.v.lo, w.v.lo2, d, Hk, d, nullptr, s));
+    RQ_HIP(ctx, realq::split3_f32(b.Wo, Hq, w.o.hi, w.o.lo, w.o.lo2, Hq, d, Hq, nullptr, s));
     RQ_HIP(ctx, realq::transpose_split_f32(b.Wo, Hq, w.oT.hi, w.oT.lo, d, d, Hq, s));
     if (input_grad) {
         if ((rc = ws_split(ctx, t + "qT", d * Hq, w.qT)) || (rc = ws_split(ctx, t + "kT", d * Hk, w.kT)) ||
@@ -988,7 +988,7 @@ extern "C" int realq_decoder_block_sweep(realq_ctx* ctx, const realq_decoder_des
         }
         fwd_slot[mod]->lo_zero = false;
         RQ_HIP(ctx, realq::split3_f32(out->W_hat[mod], n, fwd_slot[mod]->hi, fwd_slot[mod]->lo, fwd_slot[mod]->lo2, n,
-                                      m, n, s));
+                                      m, n, nullptr, s));
         if ((rc = refresh(mod, 0, T))) return rc;
     }
     if ((rc = surrogate(1.0, 0, T))) return rc;

@@ -143,14 +143,17 @@ hipError_t transpose_scale_split(const uint16_t* in, int64_t ldi, const float* s
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- float32 product slices into a float64 sum
-// H[i][j] += sum_z S[z][i][j] in float64, z in order; SYM: only the slices' lower tiles exist (a
-// symmetric product), and the values below the diagonal are added on both sides of it, so the sum
+// ---------------------------------------------------------------- sum of float32 product slices
+// C[i][j] (+)= sum_z S[z][i][j] in float64, z in order; SYM: only the slices' lower tiles exist (a
+// symmetric product), and the values below the diagonal go to both sides of it, so the sum
 // stays exactly symmetric.  One 32 x 32 tile per block (lower tiles only with SYM); bound by HBM.
-template <bool SYM>
-__global__ __launch_bounds__(256) void add_slices_kernel(const float* __restrict__ S, int64_t slices, int64_t n,
-                                                         double* __restrict__ H, int64_t tiles) {
+template <bool SYM, class Out>
+__global__ __launch_bounds__(256) void add_slices_kernel(const float* __restrict__ S, int64_t always, int64_t slices,
+                                                         const int* __restrict__ flag, int64_t M, int64_t N,
+                                                         int accumulate, Out* __restrict__ C, int64_t ldc,
+                                                         int64_t tiles) {
     __shared__ double tile[32][33];
+    if (flag && *flag == 0) slices = always;
     int64_t ti, tj;
     if constexpr (SYM) {
         const int64_t b = blockIdx.x;
@@ -165,12 +168,12 @@ __global__ __launch_bounds__(256) void add_slices_kernel(const float* __restrict
     const int rr = threadIdx.x >> 3, cc = (threadIdx.x & 7) * 4;
     const int64_t i = ti * 32 + rr, j = tj * 32 + cc;
     double v[4] = {0.0, 0.0, 0.0, 0.0};
-    if (i < n) {
-        const float* p = S + i * n + j;
-        if (n % 4 == 0 && j < n) {
+    if (i < M) {
+        const float* p = S + i * N + j;
+        if (N % 4 == 0 && j < N) {
 #pragma unroll 4
             for (int64_t z = 0; z < slices; ++z) {
-                const f32x4 x = *reinterpret_cast<const f32x4*>(p + z * n * n);
+                const f32x4 x = *reinterpret_cast<const f32x4*>(p + z * M * N);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] += (double)x[e];
             }
@@ -178,9 +181,13 @@ __global__ __launch_bounds__(256) void add_slices_kernel(const float* __restrict
             for (int64_t z = 0; z < slices; ++z)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (j + e < n) v[e] += (double)p[z * n * n + e];
+                    if (j + e < N) v[e] += (double)p[z * M * N + e];
         }
     }
+    auto add = [&](int64_t r, int64_t c, double x) {
+        Out* p = C + r * ldc + c;
+        *p = (Out)(accumulate ? (double)*p + x : x);
+    };
     if constexpr (SYM) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) tile[rr][cc + e] = v[e];
@@ -194,22 +201,34 @@ __global__ __launch_bounds__(256) void add_slices_kernel(const float* __restrict
             const int64_t mi = tj * 32 + rr, mj = ti * 32 + cc;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (mi < n && mj + e < n) H[mi * n + mj + e] += tile[cc + e][rr];
+                if (mi < N && mj + e < M) add(mi, mj + e, tile[cc + e][rr]);
         }
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-        if (i < n && j + e < n) H[i * n + j + e] += v[e];
+        if (i < M && j + e < N) add(i, j + e, v[e]);
 }
 
-hipError_t add_slices(const float* S, int64_t slices, int64_t n, bool symmetric, double* H, hipStream_t st) {
-    if (n <= 0 || slices <= 0) return hipSuccess;
-    const int64_t t = (n + 31) / 32;
+template <class Out>
+static hipError_t add_slices_t(const float* S, int64_t always, int64_t slices, const int* flag, int64_t M, int64_t N,
+                               bool symmetric, bool accumulate, Out* C, int64_t ldc, hipStream_t st) {
+    if (M <= 0 || N <= 0) return hipSuccess;
+    const int64_t tm = (M + 31) / 32, tn = (N + 31) / 32;
     if (symmetric)
-        hipLaunchKernelGGL(add_slices_kernel<true>, dim3((unsigned)(t * (t + 1) / 2)), dim3(256), 0, st, S, slices, n, H, t);
+        hipLaunchKernelGGL((add_slices_kernel<true, Out>), dim3((unsigned)(tm * (tm + 1) / 2)), dim3(256), 0, st, S,
+                           always, slices, flag, M, N, (int)accumulate, C, ldc, tn);
     else
-        hipLaunchKernelGGL(add_slices_kernel<false>, dim3((unsigned)(t * t)), dim3(256), 0, st, S, slices, n, H, t);
+        hipLaunchKernelGGL((add_slices_kernel<false, Out>), dim3((unsigned)(tm * tn)), dim3(256), 0, st, S, always,
+                           slices, flag, M, N, (int)accumulate, C, ldc, tn);
     return hipGetLastError();
+}
+hipError_t add_slices(const float* S, int64_t always, int64_t slices, const int* flag, int64_t M, int64_t N,
+                      bool symmetric, bool accumulate, double* C, int64_t ldc, hipStream_t st) {
+    return add_slices_t(S, always, slices, flag, M, N, symmetric, accumulate, C, ldc, st);
+}
+hipError_t add_slices(const float* S, int64_t always, int64_t slices, const int* flag, int64_t M, int64_t N,
+                      bool symmetric, bool accumulate, float* C, int64_t ldc, hipStream_t st) {
+    return add_slices_t(S, always, slices, flag, M, N, symmetric, accumulate, C, ldc, st);
 }
 
 // Input perturbation of one token chunk, transposed: delta = Xhat - X (rows = tokens), and
@@ -316,22 +335,128 @@ hipError_t split3_f64(const double* in, uint16_t* hi, uint16_t* lo, uint16_t* lo
     return hipGetLastError();
 }
 
-__global__ void split3_f32_kernel(const float* __restrict__ A, int64_t lda, uint16_t* __restrict__ hi,
-                                  uint16_t* __restrict__ lo, uint16_t* __restrict__ lo2, int64_t ld, int64_t cols,
-                                  int64_t total) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = e / cols, j = e % cols;
-        const int64_t o = i * ld + j;
-        split3(A[i * lda + j], hi[o], lo[o], lo2[o]);
+// One wave's verdict on its lower terms: a plain store of 1, skipped once the flag is up (every
+// writer stores the same value).
+__device__ __forceinline__ void raise_flag(int* flag, bool any) {
+    if (flag && __ballot(any) != 0 && (threadIdx.x & 63) == 0 && *(volatile int*)flag == 0) *(volatile int*)flag = 1;
+}
+
+// One row and 1024 columns per block, 4 columns per thread (16-byte loads, 8-byte stores where the
+// rows allow them): bound by HBM (14 weight matrices of an 8B-shaped block: 77 -> 58 us on average
+// against one element per thread and a 64-bit division each).
+__global__ __launch_bounds__(256) void split3_f32_kernel(const float* __restrict__ A, int64_t lda,
+                                                         uint16_t* __restrict__ hi, uint16_t* __restrict__ lo,
+                                                         uint16_t* __restrict__ lo2, int64_t ld, int64_t cols,
+                                                         int* __restrict__ flag, int vec) {
+    typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
+    const int64_t c = ((int64_t)blockIdx.y * 256 + threadIdx.x) * 4;
+    const float* a = A + (int64_t)blockIdx.x * lda + c;
+    const int64_t o = (int64_t)blockIdx.x * ld + c;
+    uint32_t any = 0;
+    if (vec && c + 4 <= cols) {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(a);
+        u16x4 h, l, l2;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            uint16_t t0, t1, t2;
+            split3(x[e], t0, t1, t2);
+            h[e] = t0;
+            l[e] = t1;
+            l2[e] = t2;
+            any |= (uint32_t)(t1 | t2) & 0x7FFFu;
+        }
+        *reinterpret_cast<u16x4*>(hi + o) = h;
+        *reinterpret_cast<u16x4*>(lo + o) = l;
+        *reinterpret_cast<u16x4*>(lo2 + o) = l2;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (c + e < cols) {
+                split3(a[e], hi[o + e], lo[o + e], lo2[o + e]);
+                any |= (uint32_t)(lo[o + e] | lo2[o + e]) & 0x7FFFu;
+            }
     }
+    raise_flag(flag, any != 0);
 }
 
 hipError_t split3_f32(const float* A, int64_t lda, uint16_t* hi, uint16_t* lo, uint16_t* lo2, int64_t ld,
-                      int64_t rows, int64_t cols, hipStream_t st) {
-    const int64_t total = rows * cols;
-    if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(split3_f32_kernel, dim3(grid_for(total, 4)), dim3(TB), 0, st, A, lda, hi, lo, lo2, ld, cols,
-                       total);
+                      int64_t rows, int64_t cols, int* flag, hipStream_t st) {
+    if (rows <= 0 || cols <= 0) return hipSuccess;
+    auto al = [](const void* p, uintptr_t b) { return ((uintptr_t)p & (b - 1)) == 0; };
+    const int vec = al(A, 16) && lda % 4 == 0 && al(hi, 8) && al(lo, 8) && al(lo2, 8) && ld % 4 == 0;
+    hipLaunchKernelGGL(split3_f32_kernel, dim3((unsigned)rows, (unsigned)((cols + 1023) / 1024)), dim3(256), 0, st, A,
+                       lda, hi, lo, lo2, ld, cols, flag, vec);
+    return hipGetLastError();
+}
+
+// Transposed terms of a float32 matrix through a 64 x 64 LDS tile: 16-byte loads along a row and
+// 16-byte stores along a column where the arrays allow them; bound by HBM.
+__global__ __launch_bounds__(256) void transpose_split3_f32_kernel(const float* __restrict__ in, int64_t ldi,
+                                                                   uint16_t* __restrict__ hi, uint16_t* __restrict__ lo,
+                                                                   uint16_t* __restrict__ lo2, int64_t ldo,
+                                                                   int64_t rows, int64_t cols, int64_t tiles_c,
+                                                                   int* __restrict__ flag, int vec_in, int vec_out) {
+    __shared__ float tile[64][65];
+    const int64_t r0 = (blockIdx.x / tiles_c) * 64, c0 = (blockIdx.x % tiles_c) * 64;
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const int rr = (t >> 4) + 16 * p, cc = (t & 15) * 4;
+        const int64_t r = r0 + rr, c = c0 + cc;
+        f32x4 x = {0.f, 0.f, 0.f, 0.f};
+        if (r < rows) {
+            const float* q = in + r * ldi + c;
+            if (vec_in && c + 4 <= cols) x = *reinterpret_cast<const f32x4*>(q);
+            else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (c + e < cols) x[e] = q[e];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) tile[rr][cc + e] = x[e];
+    }
+    __syncthreads();
+    uint32_t any = 0;
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        const int cc = (t >> 3) + 32 * p, rr = (t & 7) * 8;
+        const int64_t c = c0 + cc, r = r0 + rr;
+        if (c >= cols || r >= rows) continue;
+        const int64_t o = c * ldo + r;
+        u16x8 h, l, l2;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            uint16_t t0, t1, t2;
+            split3(tile[rr + e][cc], t0, t1, t2);
+            h[e] = t0;
+            l[e] = t1;
+            l2[e] = t2;
+            any |= (uint32_t)(t1 | t2) & 0x7FFFu;  // rows past the end hold zeros
+        }
+        auto put = [&](uint16_t* out, u16x8 v) {
+            if (vec_out && r + 8 <= rows) *reinterpret_cast<u16x8*>(out + o) = v;
+            else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (r + e < rows) out[o + e] = v[e];
+            }
+        };
+        put(hi, h);
+        put(lo, l);
+        if (lo2) put(lo2, l2);
+    }
+    raise_flag(flag, any != 0);
+}
+
+hipError_t transpose_split3_f32(const float* in, int64_t ldi, uint16_t* hi, uint16_t* lo, uint16_t* lo2, int64_t ldo,
+                                int64_t rows, int64_t cols, int* flag, hipStream_t st) {
+    if (rows <= 0 || cols <= 0) return hipSuccess;
+    const int64_t tr = (rows + 63) / 64, tc = (cols + 63) / 64;
+    const int vec_in = ((uintptr_t)in & 15) == 0 && ldi % 4 == 0;
+    const int vec_out = rows16(hi, ldo) && rows16(lo, ldo) && rows16(lo2, ldo);
+    hipLaunchKernelGGL(transpose_split3_f32_kernel, dim3((unsigned)(tr * tc)), dim3(256), 0, st, in, ldi, hi, lo, lo2,
+                       ldo, rows, cols, tc, flag, vec_in, vec_out);
     return hipGetLastError();
 }
 
@@ -425,33 +550,6 @@ hipError_t dot_f64(const double* X, const double* Y, int64_t count, double* part
     return hipGetLastError();
 }
 int64_t dot_f64_partials() { return DOT_BLOCKS; }
-
-__global__ __launch_bounds__(256) void transpose_f32_kernel(const float* __restrict__ in, int64_t ldi,
-                                                            float* __restrict__ out, int64_t ldo, int64_t rows,
-                                                            int64_t cols, int64_t tiles_c) {
-    __shared__ float tile[64][65];
-    const int64_t tr = blockIdx.x / tiles_c, tc = blockIdx.x % tiles_c;
-    const int64_t r0 = tr * 64, c0 = tc * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int rr = ty; rr < 64; rr += 4) {
-        const int64_t r = r0 + rr, c = c0 + tx;
-        tile[rr][tx] = (r < rows && c < cols) ? in[r * ldi + c] : 0.f;
-    }
-    __syncthreads();
-    for (int cc = ty; cc < 64; cc += 4) {
-        const int64_t c = c0 + cc, r = r0 + tx;
-        if (r < rows && c < cols) out[c * ldo + r] = tile[tx][cc];
-    }
-}
-
-hipError_t transpose_f32(const float* in, int64_t ldi, float* out, int64_t ldo, int64_t rows, int64_t cols,
-                         hipStream_t st) {
-    if (rows <= 0 || cols <= 0) return hipSuccess;
-    const int64_t tr = (rows + 63) / 64, tc = (cols + 63) / 64;
-    hipLaunchKernelGGL(transpose_f32_kernel, dim3((unsigned)(tr * tc)), dim3(256), 0, st, in, ldi, out, ldo, rows,
-                       cols, tc);
-    return hipGetLastError();
-}
 
 // ---------------------------------------------------------------- splits
 __global__ void split_diff_f32_kernel(const float* __restrict__ A, int64_t lda, const float* __restrict__ Bm,

@@ -153,7 +153,8 @@ __global__ __launch_bounds__(C::NT) void gemm_nt_kernel(const uint16_t* __restri
                                                         const uint16_t* __restrict__ B, int64_t ldb, int64_t M,
                                                         int64_t N, int64_t K, int64_t k_per_split, int vec_ok,
                                                         int64_t tiles_m, int64_t tiles_n, int64_t group_m, int a_blk,
-                                                        Epi epi) {
+                                                        const int* __restrict__ run_if, Epi epi) {
+    if (run_if && *run_if == 0) return;
     constexpr int A_ROWS = C::BM * (HAS_LO ? 2 : 1);
     constexpr int STAGE = (A_ROWS + C::BN) * LDS_STRIDE;  // bf16 elements per stage
     // Three LDS stages as separate arrays (the compiler can tell a stage being filled by the
@@ -977,10 +978,10 @@ static hipError_t launch_cfg(const GemmArgs& g, const Epi& epi, hipStream_t stre
     dim3 grid((unsigned)(g.tri ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n), 1, (unsigned)splits);
     if (g.Alo)
         hipLaunchKernelGGL((gemm_nt_kernel<C, Epi, true>), grid, dim3(C::NT), 0, stream, g.Ahi, g.Alo, g.lda, g.B,
-                           g.ldb, g.M, g.N, g.K, kps, (int)vec, tiles_m, tiles_n, group_m, g.a_blocked, epi);
+                           g.ldb, g.M, g.N, g.K, kps, (int)vec, tiles_m, tiles_n, group_m, g.a_blocked, g.run_if, epi);
     else
         hipLaunchKernelGGL((gemm_nt_kernel<C, Epi, false>), grid, dim3(C::NT), 0, stream, g.Ahi, g.Alo, g.lda, g.B,
-                           g.ldb, g.M, g.N, g.K, kps, (int)vec, tiles_m, tiles_n, group_m, g.a_blocked, epi);
+                           g.ldb, g.M, g.N, g.K, kps, (int)vec, tiles_m, tiles_n, group_m, g.a_blocked, g.run_if, epi);
     return hipGetLastError();
 }
 

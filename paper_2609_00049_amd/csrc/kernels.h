@@ -21,6 +21,7 @@ struct GemmArgs {
     int a_blocked = 0;    // A in the blocked hi/lo layout of gemm_resid (Alo = Ahi + 32): element
                           // (i, k) at i*lda + (k/32)*64 + k%32
     int tri = 0;          // M == N: only the 256x256 tiles on and below the diagonal (gemm_grad)
+    const int* run_if = nullptr;  // device flag; when it reads 0 the launch does nothing
 };
 int64_t gemm_effective_splits(int64_t K, int64_t splits);
 int64_t gemm_num_blocks(int64_t M, int64_t N, int tile = 0);
@@ -48,9 +49,6 @@ hipError_t gemm_loss(const GemmArgs& g, const float* B0, int64_t ldb0, const flo
 hipError_t gemm_store_bf16_t(const GemmArgs& g, uint16_t* out, int64_t ld, hipStream_t st, const float* add = nullptr);
 hipError_t gemm_store_f32_t(const GemmArgs& g, float* out, int64_t ld, hipStream_t st, const float* add = nullptr);
 hipError_t gemm_swiglu_t(const GemmArgs& g, const float* G, int64_t ldg, uint16_t* out, int64_t ld, hipStream_t st);
-// out[c*ldo + r] = in[r*ldi + c] (float32)
-hipError_t transpose_f32(const float* in, int64_t ldi, float* out, int64_t ldo, int64_t rows, int64_t cols,
-                         hipStream_t st);
 
 // ---------------------------------------------------------------- elementwise / layout
 hipError_t fill_f32(float* p, float v, int64_t count, hipStream_t st);
@@ -64,9 +62,14 @@ hipError_t transpose_u16(const uint16_t* in, int64_t ldi, uint16_t* out, int64_t
 // receives the unweighted transpose from the same pass.
 hipError_t transpose_scale_split(const uint16_t* in, int64_t ldi, const float* s, uint16_t* plain, uint16_t* hi,
                                  uint16_t* lo, uint16_t* lo2, int64_t ldo, int64_t rows, int64_t cols, hipStream_t st);
-// H[i][j] += sum_z S[z][i][j] (n x n slices, float64 sum, z in order); symmetric: S holds the tiles
-// on and below the diagonal only and both triangles of H receive them.
-hipError_t add_slices(const float* S, int64_t slices, int64_t n, bool symmetric, double* H, hipStream_t st);
+// C[i*ldc + j] = (accumulate ? C : 0) + sum_z S[z][i][j] (M x N slices, float64 sum, z in order);
+// symmetric (M == N): S holds the tiles on and below the diagonal only and both triangles of C
+// receive them.  flag (device, may be NULL): the slices from `always` on are only read when it is
+// nonzero.
+hipError_t add_slices(const float* S, int64_t always, int64_t slices, const int* flag, int64_t M, int64_t N,
+                      bool symmetric, bool accumulate, double* C, int64_t ldc, hipStream_t st);
+hipError_t add_slices(const float* S, int64_t always, int64_t slices, const int* flag, int64_t M, int64_t N,
+                      bool symmetric, bool accumulate, float* C, int64_t ldc, hipStream_t st);
 // hi/lo[i*ld + j] = split(A[i*lda + j] - (Bm ? Bm[i*ldb + j] : 0)) for j < cols (float32 inputs)
 hipError_t split_diff_f32(const float* A, int64_t lda, const float* Bm, int64_t ldb, uint16_t* hi, uint16_t* lo,
                           int64_t ld, int64_t rows, int64_t cols, hipStream_t st);
@@ -88,8 +91,13 @@ hipError_t copy_rows_u16(const uint16_t* in, int64_t ldi, uint16_t* out, int64_t
 // lo2 = bf16(x - hi - lo), so hi + lo + lo2 equals x to float32 precision (x = float(in) for the
 // float64 input).
 hipError_t split3_f64(const double* in, uint16_t* hi, uint16_t* lo, uint16_t* lo2, int64_t count, hipStream_t st);
+// flag (may be NULL): *flag = 1 when any lower term is nonzero, i.e. A is not bf16-exact (the caller
+// clears it).
 hipError_t split3_f32(const float* A, int64_t lda, uint16_t* hi, uint16_t* lo, uint16_t* lo2, int64_t ld,
-                      int64_t rows, int64_t cols, hipStream_t st);
+                      int64_t rows, int64_t cols, int* flag, hipStream_t st);
+// Transposed: hi/lo[/lo2][c*ldo + r] = the terms of in[r*ldi + c] (lo2 may be NULL: two terms)
+hipError_t transpose_split3_f32(const float* in, int64_t ldi, uint16_t* hi, uint16_t* lo, uint16_t* lo2, int64_t ldo,
+                                int64_t rows, int64_t cols, int* flag, hipStream_t st);
 // *flag |= 1 when any of p[0 .. count) is a nonzero bf16 value (the caller clears *flag)
 hipError_t any_nonzero_u16(const uint16_t* p, int64_t count, int* flag, hipStream_t st);
 // G[i][j] = C0[i][c1+j] + P[i][c1+j], i < m, j < w
@@ -151,20 +159,7 @@ hipError_t reduce_splits(const float* Gp, int64_t splits, int64_t m, int64_t w, 
 // Adam with a ready gradient G (m x (n-c1)).
 hipError_t adam_update_dense(const AdamArgs& a, const float* G, hipStream_t st);
 
-// ---------------------------------------------------------------- fp32 GEMM (VALU): C = beta*C + alpha*A*B
-// A [M,K] lda, B [K,N] ldb, C [M,N] ldc, all float32 row-major.
-struct SgemmArgs {
-    const float* A;
-    int64_t lda;
-    const float* B;
-    int64_t ldb;
-    float* C;
-    int64_t ldc;
-    int64_t M, N, K;
-    float alpha, beta;
-};
-hipError_t sgemm(const SgemmArgs& a, hipStream_t st);
-// float64 VALU GEMM: C = A B (accumulate = false) or C += A B; A [M,K] lda, B [K,N] ldb,
+// float64 GEMM on the matrix cores: C = A B (accumulate = false) or C += A B; A [M,K] lda, B [K,N] ldb,
 // C [M,N] ldc, all float64 row-major.
 hipError_t dgemm(const double* A, int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc, int64_t M,
                  int64_t N, int64_t K, bool accumulate, hipStream_t st);

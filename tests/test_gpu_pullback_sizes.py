@@ -1,0 +1,35 @@
+"""The pulled-back metric P = W^T M W at tile edges and odd sizes, for bf16-exact and full float32
+weights (the lower terms of an exact weight are skipped), with and without a (non-symmetric) M,
+stored and accumulated, against float64.  Three bf16 terms carry all 24 bits and the dropped term
+pairs are below 2^-25 of the product; sums of K float32 products round by at most K 2^-24 of the sum
+of absolute values (twice, with M, whose inner product is rounded to float32 once more)."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("exact", [True, False])
+@pytest.mark.parametrize("m_next,m,dense", [(1, 1, False), (37, 65, False), (300, 257, False), (1023, 520, False),
+                                            (65, 37, True), (264, 300, True)])
+def test_pullback_at_tile_edges(rq, ctx, m_next, m, dense, exact, accumulate):
+    import torch
+    print(f"[gpu-case] pullback {m_next}x{m} dense={dense} exact={exact} accumulate={accumulate}", flush=True)
+    g = torch.Generator().manual_seed(m_next + 3 * m)
+    W = torch.randn((m_next, m), generator=g)
+    if exact:
+        W = W.to(torch.bfloat16).float()
+    M = torch.randn((m_next, m_next), generator=g) if dense else None
+    P0 = torch.randn((m, m), generator=g)
+    P = P0.cuda()
+    rq.pullback_metric(ctx, W.cuda(), P, None if M is None else M.cuda(), accumulate=accumulate)
+    torch.cuda.synchronize()
+    W64 = W.double()
+    R = W64 if M is None else M.double() @ W64
+    Ra = W64.abs() if M is None else M.double().abs() @ W64.abs()
+    ref = W64.T @ R + (P0.double() if accumulate else 0.0)
+    bound = (2 * m_next + 6) * 2.0 ** -24 * (W64.abs().T @ Ra) + 2.0 ** -23 * (ref.abs() + P0.double().abs())
+    assert bool(((P.cpu().double() - ref).abs() <= bound).all())
+    if not dense and not accumulate:
+        assert torch.equal(P, P.T)
