@@ -86,13 +86,14 @@ struct realq_bgd_state {
     int64_t locked = 0;  // columns [0, locked) are folded into the residual base
     bool owns = true;
     // Rows of every GEMM operand start on 16 bytes whatever n and T are (the direct-to-LDS loads need
-    // it; the checked register path is about 6x slower): columns padded to ldn, tokens to Tp.  When
-    // the steps' token chunks do not start on multiples of 8 tokens each chunk starts on a multiple of
-    // 64 in the token-minor arrays instead (chunk_pos), and Xg / sg are padded copies where the
-    // caller's rows or chunk starts are not aligned.
-    int64_t ldn = 0, Tp = 0;
+    // it; the checked register path is about 6x slower) and are an odd number of 128-byte lines
+    // apart (plan::operand_stride): columns padded to ldn, tokens to Tp.  When the steps' token chunks
+    // do not start on multiples of 8 tokens each chunk starts on a multiple of 64 in the token-minor
+    // arrays instead (chunk_pos).  Xg / sg are padded copies of the caller's activations and token
+    // weights.
+    int64_t ldn = 0, ldx = 0, Tp = 0;
     bool chunked = false;
-    const uint16_t* Xg = nullptr;  // [T,ldn] Xhat as the GEMMs read it
+    const uint16_t* Xg = nullptr;  // [T,ldx] Xhat as the GEMMs read it (ldx = n: the caller's own)
     const float* sg = nullptr;     // [Tp] token weights at their chunk positions, or NULL
     float* B = nullptr;  // [m,Tp] residual base
     float* mA = nullptr;
@@ -124,7 +125,7 @@ struct realq_bgd_state {
     float* C0 = nullptr;      // [m,n] W0 Delta^T S Xhat
     float* Pm = nullptr;      // [m,n] D Xhat^T S Xhat (per step)
     double* cconst = nullptr; // <W0 Delta^T S Delta, W0> (device scalar)
-    // blended metric alpha M + (1 - alpha) P as a bf16 pair [m, pad8(m)], formed once per alpha
+    // blended metric alpha M + (1 - alpha) P as a bf16 pair [m, operand_stride(m)], formed once per alpha
     uint16_t* Mah = nullptr;
     uint16_t* Mal = nullptr;
     float Ma_alpha = -1.f;
@@ -276,24 +277,24 @@ static int sum_products(realq_ctx* ctx, realq::GemmArgs* g, int count, int alway
     return REALQ_OK;
 }
 
-// Token chunks of tc tokens staged in caller-provided bf16 buffers of n * tc elements each (xt, and
-// hi, lo, lo2 when s is given): the chunk transposed (and, with weights, s_t xhat_t split into three
+// Token chunks of tc tokens staged in caller-provided bf16 buffers of n rows of ld >= tc elements each
+// (xt, and hi, lo, lo2 when s is given): the chunk transposed (and, with weights, s_t xhat_t split into three
 // bf16 terms), then H_acc += chunk^T chunk on MFMA.  alloc = false (the allocation-free entry point)
 // adds the products straight into H_acc and skips the timing events.
 int realq::hessian_accum_chunks(realq_ctx* ctx, const uint16_t* Xhat, const float* s, int64_t T, int64_t n,
-                                double* H_acc, int64_t tc, uint16_t* xt, uint16_t* hi, uint16_t* lo, uint16_t* lo2,
-                                bool alloc) {
+                                double* H_acc, int64_t tc, int64_t ld, uint16_t* xt, uint16_t* hi, uint16_t* lo,
+                                uint16_t* lo2, bool alloc) {
     Timed tm(ctx, alloc ? "hessian" : nullptr);
     for (int64_t t0 = 0; t0 < T; t0 += tc) {
         const int64_t cur = std::min(tc, T - t0);
         // s_t xhat_t in three bf16 terms: with a heavy-tailed s a few tokens carry H, and the
         // 2^-17 remainder of a hi/lo pair would not average out over the tokens
         if (s)
-            RQ_HIP(ctx, realq::transpose_scale_split(Xhat + t0 * n, n, s + t0, xt, hi, lo, lo2, tc, cur, n, ctx->stream));
+            RQ_HIP(ctx, realq::transpose_scale_split(Xhat + t0 * n, n, s + t0, xt, hi, lo, lo2, ld, cur, n, ctx->stream));
         else
-            RQ_HIP(ctx, realq::transpose_u16(Xhat + t0 * n, n, xt, tc, cur, n, ctx->stream));
-        realq::GemmArgs g[2] = {{s ? hi : xt, s ? lo : nullptr, tc, xt, tc, n, n, cur, 1},
-                                {lo2, nullptr, tc, xt, tc, n, n, cur, 1}};
+            RQ_HIP(ctx, realq::transpose_u16(Xhat + t0 * n, n, xt, ld, cur, n, ctx->stream));
+        realq::GemmArgs g[2] = {{s ? hi : xt, s ? lo : nullptr, ld, xt, ld, n, n, cur, 1},
+                                {lo2, nullptr, ld, xt, ld, n, n, cur, 1}};
         const int count = s ? 2 : 1;
         if (alloc) {
             const int rc = sum_products(ctx, g, count, count, nullptr, true, s ? 1024 : 0, true, H_acc, n);
@@ -316,15 +317,16 @@ int realq_hessian_accum(realq_ctx* ctx, const uint16_t* Xhat, const float* s, in
     int64_t tc = (int64_t)(128ll << 20) / n;
     tc = tc < 256 ? 256 : (tc / 256) * 256;
     if (tc > T) tc = ((T + 7) / 8) * 8;
+    const int64_t ld = realq::plan::operand_stride(tc);
     void *xt = nullptr, *hi = nullptr, *lo = nullptr, *lo2 = nullptr;
-    int rc = get_ws(ctx, "h_xt", (size_t)n * tc * 2, &xt);
+    int rc = get_ws(ctx, "h_xt", (size_t)n * ld * 2, &xt);
     if (rc) return rc;
     if (s) {
-        if ((rc = get_ws(ctx, "h_hi", (size_t)n * tc * 2, &hi))) return rc;
-        if ((rc = get_ws(ctx, "h_lo", (size_t)n * tc * 2, &lo))) return rc;
-        if ((rc = get_ws(ctx, "h_lo2", (size_t)n * tc * 2, &lo2))) return rc;
+        if ((rc = get_ws(ctx, "h_hi", (size_t)n * ld * 2, &hi))) return rc;
+        if ((rc = get_ws(ctx, "h_lo", (size_t)n * ld * 2, &lo))) return rc;
+        if ((rc = get_ws(ctx, "h_lo2", (size_t)n * ld * 2, &lo2))) return rc;
     }
-    return realq::hessian_accum_chunks(ctx, Xhat, s, T, n, H_acc, tc, (uint16_t*)xt, (uint16_t*)hi, (uint16_t*)lo,
+    return realq::hessian_accum_chunks(ctx, Xhat, s, T, n, H_acc, tc, ld, (uint16_t*)xt, (uint16_t*)hi, (uint16_t*)lo,
                                        (uint16_t*)lo2, true);
 }
 
@@ -415,12 +417,11 @@ int realq_chol_inverse(realq_ctx* ctx, const double* H_acc, int64_t n, int64_t T
 // ============================================================================ BGD state
 
 // Row stride (bf16 values) of split(R o s) in the blocked layout for `cur` tokens: hi and lo of
-// every 32 tokens, rounded up to whole blocks.
-static int64_t r_ld(int64_t cur) { return 2 * ((cur + 31) / 32) * 32; }
+// every 32 tokens, rounded up to an operand stride.
+static int64_t r_ld(int64_t cur) { return realq::plan::operand_stride(2 * ((cur + 31) / 32) * 32); }
 // row stride of bf16(acc o s) on a later step of a column block (row-major, in the same buffer)
-static int64_t q_ld(int64_t cur) { return ((cur + 31) / 32) * 32; }
+static int64_t q_ld(int64_t cur) { return realq::plan::operand_stride(cur); }
 
-static int64_t pad8(int64_t v) { return (v + 7) / 8 * 8; }
 // Position of the token chunk that starts at t0 in the token-minor arrays (B, XhT, sg).
 static int64_t chunk_pos(const realq_bgd_state* st, int64_t t0) {
     if (!st->chunked) return t0;
@@ -476,20 +477,21 @@ static int gram_accum(realq_ctx* ctx, const uint16_t* Xhat, const uint16_t* X, c
     int64_t tc = (int64_t)(128ll << 20) / n;
     tc = tc < 256 ? 256 : (tc / 256) * 256;
     if (tc > T) tc = ((T + 7) / 8) * 8;
-    if ((rc = get_ws(ctx, "g_sdh", (size_t)n * tc * 2, &sdh))) return rc;
-    if ((rc = get_ws(ctx, "g_sdl", (size_t)n * tc * 2, &sdl))) return rc;
-    if ((rc = get_ws(ctx, "g_dh16", (size_t)n * tc * 2, &dh))) return rc;
-    if ((rc = get_ws(ctx, "g_dl16", (size_t)n * tc * 2, &dl))) return rc;
-    if ((rc = get_ws(ctx, "g_xt", (size_t)n * tc * 2, &xt))) return rc;
+    const int64_t ld = realq::plan::operand_stride(tc);
+    if ((rc = get_ws(ctx, "g_sdh", (size_t)n * ld * 2, &sdh))) return rc;
+    if ((rc = get_ws(ctx, "g_sdl", (size_t)n * ld * 2, &sdl))) return rc;
+    if ((rc = get_ws(ctx, "g_dh16", (size_t)n * ld * 2, &dh))) return rc;
+    if ((rc = get_ws(ctx, "g_dl16", (size_t)n * ld * 2, &dl))) return rc;
+    if ((rc = get_ws(ctx, "g_xt", (size_t)n * ld * 2, &xt))) return rc;
     Timed tm(ctx, "gram");
     RQ_HIP(ctx, realq::fill_f64(Gdh, 0.0, n * n, s));
     RQ_HIP(ctx, realq::fill_f64(Gdd, 0.0, n * n, s));
     for (int64_t t0 = 0; t0 < T; t0 += tc) {
         const int64_t cur = std::min(tc, T - t0);
         RQ_HIP(ctx, realq::transpose_delta_split(Xhat + t0 * n, X + t0 * n, n, sw ? sw + t0 : nullptr, (uint16_t*)sdh,
-                                                 (uint16_t*)sdl, (uint16_t*)dh, (uint16_t*)dl, tc, cur, n, s));
-        RQ_HIP(ctx, realq::transpose_u16(Xhat + t0 * n, n, (uint16_t*)xt, tc, cur, n, s));
-        realq::GemmArgs g{(const uint16_t*)sdh, (const uint16_t*)sdl, tc, (const uint16_t*)xt, tc, n, n, cur, 1};
+                                                 (uint16_t*)sdl, (uint16_t*)dh, (uint16_t*)dl, ld, cur, n, s));
+        RQ_HIP(ctx, realq::transpose_u16(Xhat + t0 * n, n, (uint16_t*)xt, ld, cur, n, s));
+        realq::GemmArgs g{(const uint16_t*)sdh, (const uint16_t*)sdl, ld, (const uint16_t*)xt, ld, n, n, cur, 1};
         if ((rc = sum_products(ctx, &g, 1, 1, nullptr, false, 0, true, Gdh, n))) return rc;
         realq::GemmArgs gd[2] = {g, g};
         gd[0].B = (const uint16_t*)dh;
@@ -577,10 +579,11 @@ static int state_init(realq_bgd_state* st) {
     st->nbatch = (T + st->Tb - 1) / st->Tb;
     int64_t Tc = st->prm.tok_chunk > 0 ? std::min<int64_t>(st->prm.tok_chunk, st->Tb) : st->Tb;
     st->Tc = Tc;
-    const int64_t ldn = st->ldn = pad8(n);
+    const int64_t ldn = st->ldn = realq::plan::operand_stride(n);
     st->chunked = (Tc < T && Tc % 8) || (st->Tb < T && st->Tb % 8);
     const int64_t per_batch = (st->Tb + Tc - 1) / Tc;
-    const int64_t Tp = st->Tp = st->chunked ? st->nbatch * per_batch * ((Tc + 63) / 64 * 64) : pad8(T);
+    const int64_t Tp = st->Tp =
+        realq::plan::operand_stride(st->chunked ? st->nbatch * per_batch * ((Tc + 63) / 64 * 64) : T);
     int rc;
     void* p;
     if ((rc = state_alloc(st, &p, (size_t)m * Tp * 4, "s_B"))) return rc;
@@ -617,12 +620,20 @@ static int state_init(realq_bgd_state* st) {
     Timed tm(ctx, "init");
     RQ_HIP(ctx, realq::fill_f32(st->mA, 0.f, m * n, s));
     RQ_HIP(ctx, realq::fill_f32(st->vA, 0.f, m * n, s));
+    // The copy costs one read and write of Xhat against a residual product per Block-GD step; without
+    // steps, or without room for it, aligned rows stay where they are.
     st->Xg = st->Xhat;
-    if (ldn != n) {
-        if ((rc = state_alloc(st, &p, (size_t)T * ldn * 2, "s_Xg"))) return rc;
-        st->Xg = (const uint16_t*)p;
-        RQ_HIP(ctx, realq::copy_rows_u16(st->Xhat, n, (uint16_t*)p, ldn, T, n, s));
+    st->ldx = n;
+    if (ldn != n && (n % 8 || st->prm.steps > 0)) {
+        rc = state_alloc(st, &p, (size_t)T * ldn * 2, "s_Xg");
+        if (rc && (rc != REALQ_ERR_OOM || n % 8)) return rc;
+        if (!rc) {
+            st->Xg = (const uint16_t*)p;
+            st->ldx = ldn;
+            RQ_HIP(ctx, realq::copy_rows_u16(st->Xhat, n, (uint16_t*)p, ldn, T, n, s));
+        }
     }
+    const int64_t ldx = st->ldx;
     st->sg = st->s;
     if (st->s && st->chunked) {
         if ((rc = state_alloc(st, &p, (size_t)Tp * 4, "s_sg"))) return rc;
@@ -634,7 +645,7 @@ static int state_init(realq_bgd_state* st) {
             return rc;
     }
     if ((rc = each_range(st, [&](int64_t t0, int64_t len, int64_t pos) -> int {
-             RQ_HIP(ctx, realq::transpose_u16(st->Xg + t0 * ldn, ldn, st->XhT + pos, Tp, len, n, s));
+             RQ_HIP(ctx, realq::transpose_u16(st->Xg + t0 * ldx, ldx, st->XhT + pos, Tp, len, n, s));
              return REALQ_OK;
          })))
         return rc;
@@ -680,7 +691,7 @@ static int state_init_gram(realq_bgd_state* st) {
     st->Tc = T;
     st->Tb = T;
     st->nbatch = 1;
-    const int64_t ldn = st->ldn = pad8(n);
+    const int64_t ldn = st->ldn = realq::plan::operand_stride(n);
     int rc;
     void* p;
     if ((rc = state_alloc(st, &p, (size_t)m * n * 4, "s_m"))) return rc;
@@ -912,10 +923,10 @@ static int lock_block(realq_ctx* ctx, realq_bgd_state* st, int64_t c0, int64_t b
     st->inc_c1 = -1;  // the residual base moves: the next step starts a block
     st->inc_ready = false;
     if (!st->gram) {
-        const int64_t ldn = st->ldn;
+        const int64_t ldn = st->ldn, ldx = st->ldx;
         Timed tm(ctx, "lock");
         const int rc = each_range(st, [&](int64_t t0, int64_t len, int64_t pos) -> int {
-            realq::GemmArgs g{st->Dhi + c0, st->Dlo + c0, ldn, st->Xg + t0 * ldn + c0, ldn, st->m, len, bs, 1};
+            realq::GemmArgs g{st->Dhi + c0, st->Dlo + c0, ldn, st->Xg + t0 * ldx + c0, ldx, st->m, len, bs, 1};
             RQ_HIP(ctx, realq::gemm_acc_f32(g, st->B + pos, st->Tp, 1.f, ctx->stream));
             return REALQ_OK;
         });
@@ -955,7 +966,7 @@ int realq_bgd_step(realq_ctx* ctx, realq_bgd_state* st, double* W, int64_t c1, f
     if (c1 < 0 || c1 > st->n) return set_error(ctx, REALQ_ERR_SHAPE, "bgd_step: need 0 <= c1 <= n");
     if (!std::isfinite(alpha) || alpha < 0.f || alpha > 1.f)
         return set_error(ctx, REALQ_ERR_INVALID_ARG, "bgd_step: alpha must lie in [0, 1]");
-    const int64_t m = st->m, n = st->n, T = st->T, Tc = st->Tc, nJ = n - c1, ldn = st->ldn, Tp = st->Tp;
+    const int64_t m = st->m, n = st->n, T = st->T, Tc = st->Tc, nJ = n - c1, ldn = st->ldn, ldx = st->ldx, Tp = st->Tp;
     hipStream_t s = ctx->stream;
     if (nJ == 0) {
         if (loss_out) RQ_HIP(ctx, realq::fill_f64(loss_out, NAN, 1, s));
@@ -1009,9 +1020,9 @@ int realq_bgd_step(realq_ctx* ctx, realq_bgd_state* st, double* W, int64_t c1, f
             double* const pch = pbase + pl.chunks[ch].parts_off;
             const int64_t pos = chunk_pos(st, t0);
             const float* sc = chunk_s(st, t0);
-            realq::GemmArgs g{st->Dhi + c1, st->Dlo + c1, ldn, st->Xg + t0 * ldn + c1, ldn, m, cur, nJ, 1};
+            realq::GemmArgs g{st->Dhi + c1, st->Dlo + c1, ldn, st->Xg + t0 * ldx + c1, ldx, m, cur, nJ, 1};
             if (inc_step) {
-                realq::GemmArgs gi{st->Dinc + c1, nullptr, ldn, st->Xg + t0 * ldn + c1, ldn, m, cur, nJ, 1};
+                realq::GemmArgs gi{st->Dinc + c1, nullptr, ldn, st->Xg + t0 * ldx + c1, ldx, m, cur, nJ, 1};
                 Timed tm(ctx, "resid_inc");
                 RQ_HIP(ctx, realq::gemm_resid_inc(gi, sc, st->Rhi, q_ld(cur), pch, s));
             } else if (!clip) {
@@ -1111,22 +1122,23 @@ int realq_bgd_step(realq_ctx* ctx, realq_bgd_state* st, double* W, int64_t c1, f
         // (the lo*lo term is below float32 rounding of the product).
         if (!st->Mah) {
             void* p;
-            if ((rc = state_alloc(st, &p, (size_t)m * pad8(m) * 2, "s_Mah"))) return rc;
+            if ((rc = state_alloc(st, &p, (size_t)m * realq::plan::operand_stride(m) * 2, "s_Mah"))) return rc;
             st->Mah = (uint16_t*)p;
-            if ((rc = state_alloc(st, &p, (size_t)m * pad8(m) * 2, "s_Mal"))) return rc;
+            if ((rc = state_alloc(st, &p, (size_t)m * realq::plan::operand_stride(m) * 2, "s_Mal"))) return rc;
             st->Mal = (uint16_t*)p;
             st->Ma_alpha = -1.f;
         }
         if (st->Ma_alpha != alpha) {
-            RQ_HIP(ctx, realq::blend_split(st->M, alpha < 1.f ? st->P : nullptr, alpha, m, st->Mah, st->Mal, pad8(m), s));
+            RQ_HIP(ctx, realq::blend_split(st->M, alpha < 1.f ? st->P : nullptr, alpha, m, st->Mah, st->Mal,
+                                           realq::plan::operand_stride(m), s));
             st->Ma_alpha = alpha;
         }
         void *Gm, *gth, *gtl;
         if ((rc = get_ws(ctx, "b_Gm", (size_t)m * nJ * 4, &Gm))) return rc;
-        if ((rc = get_ws(ctx, "b_GTh", (size_t)pad8(m) * nJ * 2, &gth))) return rc;
-        if ((rc = get_ws(ctx, "b_GTl", (size_t)pad8(m) * nJ * 2, &gtl))) return rc;
+        if ((rc = get_ws(ctx, "b_GTh", (size_t)realq::plan::operand_stride(m) * nJ * 2, &gth))) return rc;
+        if ((rc = get_ws(ctx, "b_GTl", (size_t)realq::plan::operand_stride(m) * nJ * 2, &gtl))) return rc;
         const float invT = (float)(1.0 / (double)Tn);
-        const int64_t mp = pad8(m);
+        const int64_t mp = realq::plan::operand_stride(m);
         {
             Timed tm(ctx, "metric");
             RQ_HIP(ctx,
@@ -1152,7 +1164,7 @@ int realq_bgd_loss(realq_ctx* ctx, realq_bgd_state* st, const double* W, double*
         return gram_loss(ctx, st, W, loss_out);
     }
     // R = B + (W - W0)[:, J] Xhat[:, J]^T with J the columns not yet folded into B.
-    const int64_t m = st->m, T = st->T, Tc = st->Tc, n = st->n, c1 = st->locked, nJ = n - c1, ldn = st->ldn;
+    const int64_t m = st->m, T = st->T, Tc = st->Tc, n = st->n, c1 = st->locked, nJ = n - c1, ldn = st->ldn, ldx = st->ldx;
     int64_t nparts = 0;
     std::vector<realq::plan::Chunk> chunks;
     // all tokens in chunks; with chunked positions no chunk crosses a batch
@@ -1171,7 +1183,7 @@ int realq_bgd_loss(realq_ctx* ctx, realq_bgd_state* st, const double* W, double*
     if (nJ > 0) RQ_HIP(ctx, realq::split_diff_f64(W + c1, n, st->W0 + c1, n, st->Dhi + c1, st->Dlo + c1, ldn, m, nJ,
                                                   ctx->stream));
     for (const auto& c : chunks) {
-        realq::GemmArgs g{st->Dhi + c1, st->Dlo + c1, ldn, st->Xg + c.t0 * ldn + c1, ldn, m, c.len, nJ, 1};
+        realq::GemmArgs g{st->Dhi + c1, st->Dlo + c1, ldn, st->Xg + c.t0 * ldx + c1, ldx, m, c.len, nJ, 1};
         RQ_HIP(ctx, realq::gemm_loss(g, st->B + chunk_pos(st, c.t0), st->Tp, chunk_s(st, c.t0),
                                      (double*)parts + c.parts_off, ctx->stream));
     }
@@ -1193,7 +1205,7 @@ int realq_pullback_metric(realq_ctx* ctx, const float* W_next, const float* M_ne
     // the call asynchronous).  M = NULL: W^T W is symmetric, one triangle is formed.
     // 14336 x 4096 bf16-exact weights: 8.7 ms as a float32 vector GEMM (55 TFLOP/s), now 0.40 ms;
     // error against float64 1.7e-6 -> 2.7e-7 (shorter float32 sums).
-    const int64_t kp = (m_next + 7) / 8 * 8;
+    const int64_t kp = realq::plan::operand_stride(m_next);
     struct Terms {
         uint16_t *hi, *lo, *lo2;
     };
@@ -1241,7 +1253,7 @@ int realq_handoff(realq_ctx* ctx, const float* Wa, const float* Wb, const uint16
     hipStream_t s = ctx->stream;
     void *hi, *lo, *xg;
     int rc;
-    const int64_t ldn = pad8(n);  // 16-byte operand rows whatever n is
+    const int64_t ldn = (n + 7) / 8 * 8;  // 16-byte operand rows whatever n is
     if ((rc = get_ws(ctx, "h_wh", (size_t)m * ldn * 2, &hi))) return rc;
     if ((rc = get_ws(ctx, "h_wl", (size_t)m * ldn * 2, &lo))) return rc;
     const uint16_t* Xg = X;

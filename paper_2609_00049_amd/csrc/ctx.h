@@ -51,11 +51,11 @@ namespace realq {
 // Argument checks shared by the entry points (REALQ_OK or an error set on ctx).
 int validate_q(realq_ctx* ctx, const realq_qparams* qp);
 int validate_bgd(realq_ctx* ctx, const realq_bgd_params* p);
-// Token-chunked Hessian accumulation into H_acc with caller-provided staging buffers (n * tc bf16
-// each; hi, lo, lo2 only used when s is given).  alloc: the products may go through context
+// Token-chunked Hessian accumulation into H_acc with caller-provided staging buffers (n rows of
+// ld >= tc bf16 each; hi, lo, lo2 only used when s is given).  alloc: the products may go through context
 // workspaces (acc_products); false: straight into H_acc, no workspace and no timing events.
 int hessian_accum_chunks(realq_ctx* ctx, const uint16_t* Xhat, const float* s, int64_t T, int64_t n, double* H_acc,
-                         int64_t tc, uint16_t* xt, uint16_t* hi, uint16_t* lo, uint16_t* lo2, bool alloc);
+                         int64_t tc, int64_t ld, uint16_t* xt, uint16_t* hi, uint16_t* lo, uint16_t* lo2, bool alloc);
 
 // A roctx range over a host scope: the launches it encloses show under its name in a
 // `rocprofv3 --marker-trace` run (the push is a no-op call when no tool is attached).

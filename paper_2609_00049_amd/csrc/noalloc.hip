@@ -72,5 +72,5 @@ extern "C" int realq_hessian_accum_noalloc(realq_ctx* ctx, const uint16_t* Xhat,
     uint16_t* lo2 = reinterpret_cast<uint16_t*>(b + 3 * kStage);
     // every staged element the GEMMs read is written by the transposes of the same chunk, so
     // nothing left in the array by an earlier call needs clearing
-    return realq::hessian_accum_chunks(ctx, Xhat, s, T, n, H_acc, tc, xt, hi, lo, lo2, false);
+    return realq::hessian_accum_chunks(ctx, Xhat, s, T, n, H_acc, tc, tc, xt, hi, lo, lo2, false);
 }

@@ -50,6 +50,11 @@ int64_t choose_splits(int64_t M, int64_t N, int64_t K, int cus) {
     return best;
 }
 
+int64_t operand_stride(int64_t n) {
+    const int64_t lines = (n + 63) / 64;
+    return 64 * (lines | 1);
+}
+
 int64_t choose_acc_splits(int64_t tiles, int64_t K, int passes, int cus, int64_t max_k) {
     if (cus < 1) cus = 1;
     const int64_t smin = max_k > 0 ? (K + max_k - 1) / max_k : 1;

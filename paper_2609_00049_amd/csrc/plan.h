@@ -28,6 +28,12 @@ int64_t effective_splits(int64_t K, int64_t splits);
 // every split keeps at least 256 tokens.
 int64_t choose_splits(int64_t M, int64_t N, int64_t K, int cus);
 
+// Row stride (elements) of a bf16 GEMM operand laid out by the library: whole 128-byte lines, an odd
+// number of them.  A tile's loads walk 256 rows at one K offset; with a power-of-two stride those
+// lines fall on a few memory channels (gradient product of 2048 x 4096 over 65536 tokens: 1.11 to
+// 1.46 ms from run to run at a stride of 65536 elements, 0.93 ms at 65600).
+int64_t operand_stride(int64_t n);
+
 // Split-K factor of a product accumulated in float64 over `tiles` 256x256 tiles and K tokens with
 // `passes` MFMA passes per tile: the cheapest of 1 .. 256 by the time its rounds of `cus` tiles take
 // at the GEMM's rate (about 30 ns per token, tile and pass) plus the write and read of its float32
