@@ -95,22 +95,40 @@ int prod3(realq_ctx* ctx, const Split& X, int64_t rows, int64_t K, const Split& 
     return REALQ_OK;
 }
 
-// Sets w.lo_zero when the lower terms of a split are all zero (a bf16-exact matrix, such as a
-// weight of a bf16 checkpoint): its products then skip the passes of those terms, which would add
-// exact zeros.  One stream synchronisation; for the fixed operands set up once per call.
-int mark_exact(realq_ctx* ctx, Split& w, int64_t count) {
-    int* flag;
-    int rc;
-    if ((rc = ws(ctx, "nz_flag", 1, flag))) return rc;
-    RQ_HIP(ctx, realq::fill_f32(reinterpret_cast<float*>(flag), 0.f, 1, ctx->stream));
-    RQ_HIP(ctx, realq::any_nonzero_u16(w.lo, count, flag, ctx->stream));
-    if (w.lo2) RQ_HIP(ctx, realq::any_nonzero_u16(w.lo2, count, flag, ctx->stream));
-    int host = 1;
-    RQ_HIP(ctx, hipMemcpyAsync(&host, flag, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
-    RQ_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    w.lo_zero = host == 0;
-    return REALQ_OK;
-}
+// Which fixed operands are bf16-exact: their splits raise a device flag each when a lower term is
+// nonzero, and settle() reads all flags with one stream synchronisation and sets lo_zero of the
+// operands whose flag stayed down (a bf16 checkpoint's weights), whose products then skip the passes
+// of those terms, which would add exact zeros.  A transposed operand shares its matrix's flag.
+struct ExactFlags {
+    static constexpr int kMax = 16;
+    int* flags = nullptr;
+    int used = 0;
+    Split* who[3 * kMax];
+    int of[3 * kMax], n = 0;
+
+    int begin(realq_ctx* ctx) {
+        int rc;
+        if ((rc = ws(ctx, "nz_flags", kMax, flags))) return rc;
+        RQ_HIP(ctx, realq::fill_f32(reinterpret_cast<float*>(flags), 0.f, kMax, ctx->stream));
+        return REALQ_OK;
+    }
+    int* add(Split& a, Split* b = nullptr) {
+        who[n] = &a;
+        of[n++] = used;
+        if (b) {
+            who[n] = b;
+            of[n++] = used;
+        }
+        return flags + used++;
+    }
+    int settle(realq_ctx* ctx) {
+        int host[kMax];
+        RQ_HIP(ctx, hipMemcpyAsync(host, flags, sizeof(int) * used, hipMemcpyDeviceToHost, ctx->stream));
+        RQ_HIP(ctx, hipStreamSynchronize(ctx->stream));
+        for (int i = 0; i < n; ++i) who[i]->lo_zero = host[of[i]] == 0;
+        return REALQ_OK;
+    }
+};
 
 // Precomputed splits of one block's weights.
 struct BlockW {
@@ -120,20 +138,26 @@ struct BlockW {
     Split F;              // [d][d] or empty (identity)
 };
 
-int split_block(realq_ctx* ctx, const char* tag, const realq_mlp_block& b, int64_t d, int64_t f, bool backward,
-                BlockW& w) {
+// What a block's splits are for: the forward alone, the forward and the gradient of its own weights
+// (Wd^T), or its input gradient too (Wg^T, Wu^T).
+enum class Use { kForward, kOwnGrad, kInputGrad };
+
+int split_block(realq_ctx* ctx, const char* tag, const realq_mlp_block& b, int64_t d, int64_t f, Use use, BlockW& w,
+                ExactFlags& ex) {
     hipStream_t s = ctx->stream;
     const std::string t(tag);
     int rc;
     w.gamma = b.gamma;
     if ((rc = ws_split3(ctx, t + "g", f * d, w.g)) || (rc = ws_split3(ctx, t + "u", f * d, w.u)) ||
-        (rc = ws_split3(ctx, t + "d", d * f, w.d)) || (rc = ws_split(ctx, t + "dT", f * d, w.dT)))
+        (rc = ws_split3(ctx, t + "d", d * f, w.d)))
         return rc;
-    RQ_HIP(ctx, realq::split3_f32(b.Wg, d, w.g.hi, w.g.lo, w.g.lo2, d, f, d, nullptr, s));
-    RQ_HIP(ctx, realq::split3_f32(b.Wu, d, w.u.hi, w.u.lo, w.u.lo2, d, f, d, nullptr, s));
-    RQ_HIP(ctx, realq::split3_f32(b.Wd, f, w.d.hi, w.d.lo, w.d.lo2, f, d, f, nullptr, s));
+    RQ_HIP(ctx, realq::split3_f32(b.Wg, d, w.g.hi, w.g.lo, w.g.lo2, d, f, d, ex.add(w.g, &w.gT), s));
+    RQ_HIP(ctx, realq::split3_f32(b.Wu, d, w.u.hi, w.u.lo, w.u.lo2, d, f, d, ex.add(w.u, &w.uT), s));
+    RQ_HIP(ctx, realq::split3_f32(b.Wd, f, w.d.hi, w.d.lo, w.d.lo2, f, d, f, ex.add(w.d, &w.dT), s));
+    if (use == Use::kForward) return REALQ_OK;
+    if ((rc = ws_split(ctx, t + "dT", f * d, w.dT))) return rc;
     RQ_HIP(ctx, realq::transpose_split_f32(b.Wd, f, w.dT.hi, w.dT.lo, d, d, f, s));
-    if (backward) {
+    if (use == Use::kInputGrad) {
         if ((rc = ws_split(ctx, t + "gT", d * f, w.gT)) || (rc = ws_split(ctx, t + "uT", d * f, w.uT))) return rc;
         RQ_HIP(ctx, realq::transpose_split_f32(b.Wg, d, w.gT.hi, w.gT.lo, f, f, d, s));
         RQ_HIP(ctx, realq::transpose_split_f32(b.Wu, d, w.uT.hi, w.uT.lo, f, f, d, s));
@@ -141,12 +165,8 @@ int split_block(realq_ctx* ctx, const char* tag, const realq_mlp_block& b, int64
     if (b.F) {
         if ((rc = ws_split(ctx, t + "F", d * d, w.F))) return rc;
         RQ_HIP(ctx, realq::split_diff_f32(b.F, d, nullptr, 0, w.F.hi, w.F.lo, d, d, d, s));
-        if ((rc = mark_exact(ctx, w.F, d * d))) return rc;
+        RQ_HIP(ctx, realq::any_nonzero_u16(w.F.lo, d * d, ex.add(w.F), s));
     }
-    if ((rc = mark_exact(ctx, w.g, f * d)) || (rc = mark_exact(ctx, w.u, f * d)) || (rc = mark_exact(ctx, w.d, d * f)) ||
-        (rc = mark_exact(ctx, w.dT, f * d)))
-        return rc;
-    if (backward && ((rc = mark_exact(ctx, w.gT, d * f)) || (rc = mark_exact(ctx, w.uT, d * f)))) return rc;
     return REALQ_OK;
 }
 
@@ -251,8 +271,10 @@ extern "C" int realq_mlp_block_sweep(realq_ctx* ctx, const realq_mlp_desc* D, re
 
     // ---- fixed operands: weight splits, normalised inputs, full-precision outputs
     BlockW w0, w2;
-    if ((rc = split_block(ctx, "m0", B0, d, f, false, w0))) return rc;
-    if (window && (rc = split_block(ctx, "m2", D->next, d, f, true, w2))) return rc;
+    ExactFlags ex;
+    if ((rc = ex.begin(ctx)) || (rc = split_block(ctx, "m0", B0, d, f, Use::kOwnGrad, w0, ex))) return rc;
+    if (window && (rc = split_block(ctx, "m2", D->next, d, f, Use::kInputGrad, w2, ex))) return rc;
+    if ((rc = ex.settle(ctx))) return rc;
     Fwd fs, fq, fn;  // full-precision path, quantized path, next block
     if ((rc = alloc_fwd(ctx, "mfs", T, d, f, fs)) || (rc = alloc_fwd(ctx, "mfq", T, d, f, fq))) return rc;
     if (window && (rc = alloc_fwd(ctx, "mfn", T, d, f, fn))) return rc;
@@ -467,35 +489,35 @@ struct DecW {  // one decoder block's weights as the GEMMs consume them
 };
 
 int split_dec(realq_ctx* ctx, const char* tag, const realq_decoder_block& b, int64_t d, int64_t f, int64_t Hq,
-              int64_t Hk, bool input_grad, DecW& w) {
+              int64_t Hk, Use use, DecW& w) {
     hipStream_t s = ctx->stream;
     const std::string t(tag);
     int rc;
+    ExactFlags ex;
     w.gamma1 = b.gamma1;
-    if ((rc = ws_split3(ctx, t + "q", Hq * d, w.q)) || (rc = ws_split3(ctx, t + "k", Hk * d, w.k)) ||
-        (rc = ws_split3(ctx, t + "v", Hk * d, w.v)) || (rc = ws_split3(ctx, t + "o", d * Hq, w.o)) ||
-        (rc = ws_split(ctx, t + "oT", Hq * d, w.oT)))
+    if ((rc = ex.begin(ctx)) || (rc = ws_split3(ctx, t + "q", Hq * d, w.q)) || (rc = ws_split3(ctx, t + "k", Hk * d, w.k)) ||
+        (rc = ws_split3(ctx, t + "v", Hk * d, w.v)) || (rc = ws_split3(ctx, t + "o", d * Hq, w.o)))
         return rc;
-    RQ_HIP(ctx, realq::split3_f32(b.Wq, d, w.q.hi, w.q.lo, w.q.lo2, d, Hq, d, nullptr, s));
-    RQ_HIP(ctx, realq::split3_f32(b.Wk, d, w.k.hi, w.k.lo, w.k.lo2, d, Hk, d, nullptr, s));
-    RQ_HIP(ctx, realq::split3_f32(b.Wv, d, w.v.hi, w.v.lo, w.v.lo2, d, Hk, d, nullptr, s));
-    RQ_HIP(ctx, realq::split3_f32(b.Wo, Hq, w.o.hi, w.o.lo, w.o.lo2, Hq, d, Hq, nullptr, s));
-    RQ_HIP(ctx, realq::transpose_split_f32(b.Wo, Hq, w.oT.hi, w.oT.lo, d, d, Hq, s));
-    if (input_grad) {
+    RQ_HIP(ctx, realq::split3_f32(b.Wq, d, w.q.hi, w.q.lo, w.q.lo2, d, Hq, d, ex.add(w.q, &w.qT), s));
+    RQ_HIP(ctx, realq::split3_f32(b.Wk, d, w.k.hi, w.k.lo, w.k.lo2, d, Hk, d, ex.add(w.k, &w.kT), s));
+    RQ_HIP(ctx, realq::split3_f32(b.Wv, d, w.v.hi, w.v.lo, w.v.lo2, d, Hk, d, ex.add(w.v, &w.vT), s));
+    RQ_HIP(ctx, realq::split3_f32(b.Wo, Hq, w.o.hi, w.o.lo, w.o.lo2, Hq, d, Hq, ex.add(w.o, &w.oT), s));
+    if (use != Use::kForward) {
+        if ((rc = ws_split(ctx, t + "oT", Hq * d, w.oT))) return rc;
+        RQ_HIP(ctx, realq::transpose_split_f32(b.Wo, Hq, w.oT.hi, w.oT.lo, d, d, Hq, s));
+    }
+    if (use == Use::kInputGrad) {
         if ((rc = ws_split(ctx, t + "qT", d * Hq, w.qT)) || (rc = ws_split(ctx, t + "kT", d * Hk, w.kT)) ||
             (rc = ws_split(ctx, t + "vT", d * Hk, w.vT)))
             return rc;
         RQ_HIP(ctx, realq::transpose_split_f32(b.Wq, d, w.qT.hi, w.qT.lo, Hq, Hq, d, s));
         RQ_HIP(ctx, realq::transpose_split_f32(b.Wk, d, w.kT.hi, w.kT.lo, Hk, Hk, d, s));
         RQ_HIP(ctx, realq::transpose_split_f32(b.Wv, d, w.vT.hi, w.vT.lo, Hk, Hk, d, s));
-        if ((rc = mark_exact(ctx, w.qT, d * Hq)) || (rc = mark_exact(ctx, w.kT, d * Hk)) ||
-            (rc = mark_exact(ctx, w.vT, d * Hk)))
-            return rc;
     }
-    if ((rc = mark_exact(ctx, w.q, Hq * d)) || (rc = mark_exact(ctx, w.k, Hk * d)) || (rc = mark_exact(ctx, w.v, Hk * d)) ||
-        (rc = mark_exact(ctx, w.o, d * Hq)) || (rc = mark_exact(ctx, w.oT, Hq * d)))
+    // the attention gradients enter the MLP half of every block with its input gradient
+    if ((rc = split_block(ctx, (t + "m").c_str(), b.mlp, d, f, use == Use::kForward ? use : Use::kInputGrad, w.mlp, ex)))
         return rc;
-    return split_block(ctx, (t + "m").c_str(), b.mlp, d, f, true, w.mlp);
+    return ex.settle(ctx);
 }
 
 struct DecDims {
@@ -698,7 +720,7 @@ extern "C" int realq_decoder_forward(realq_ctx* ctx, const realq_decoder_desc* D
     hipStream_t s = ctx->stream;
     DecW w;
     DecF F;
-    if ((rc = split_dec(ctx, "df", Dd->blk, D.d, D.f, D.Hq, D.Hk, false, w)) || (rc = alloc_decf(ctx, "dff", D, F)) ||
+    if ((rc = split_dec(ctx, "df", Dd->blk, D.d, D.f, D.Hq, D.Hk, Use::kForward, w)) || (rc = alloc_decf(ctx, "dff", D, F)) ||
         (rc = dec_forward(ctx, w, Dd->X, nullptr, D, F)))
         return rc;
     const int64_t T = D.T;
@@ -765,8 +787,8 @@ extern "C" int realq_decoder_block_sweep(realq_ctx* ctx, const realq_decoder_des
     if (out->loss_trace && steps > 0) RQ_HIP(ctx, realq::fill_f64(out->loss_trace, NAN, B_total * steps, s));
 
     DecW wq, wn;  // the quantized path's current weights; the next block's
-    if ((rc = split_dec(ctx, "d0", B0, d, f, D.Hq, D.Hk, false, wq))) return rc;
-    if (window && (rc = split_dec(ctx, "d2", N0, d, f, D.Hq, D.Hk, true, wn))) return rc;
+    if ((rc = split_dec(ctx, "d0", B0, d, f, D.Hq, D.Hk, Use::kOwnGrad, wq))) return rc;
+    if (window && (rc = split_dec(ctx, "d2", N0, d, f, D.Hq, D.Hk, Use::kInputGrad, wn))) return rc;
     DecF Fs, Fq, Fn;
     if ((rc = alloc_decf(ctx, "dfs", D, Fs)) || (rc = alloc_decf(ctx, "dfq", D, Fq))) return rc;
     if (window && (rc = alloc_decf(ctx, "dfn", D, Fn))) return rc;
