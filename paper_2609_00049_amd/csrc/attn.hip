@@ -96,6 +96,10 @@ namespace {
 constexpr int AT = 32;
 constexpr int TSTR = AT + 8;  // bf16 per row of a staged 32 x 32 tile (80 bytes: 16-byte aligned rows)
 typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef float f32x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16v2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16v8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int TSTR32 = AT + 4;  // uint32 per row of a staged 32 x 32 tile of hi | lo pairs (144 bytes)
 
@@ -118,21 +122,6 @@ __device__ __forceinline__ void split8x3(const float* p, bf16x8& hi, bf16x8& lo,
     lo2 = __builtin_bit_cast(bf16x8, l2);
 }
 
-__device__ __forceinline__ void split8x3(const float (&x8)[8], bf16x8& hi, bf16x8& lo, bf16x8& lo2) {
-    u16x8 h, l, l2;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-        const float x = x8[u];
-        h[u] = f2bf(x);
-        const float r = x - bf2f(h[u]);
-        l[u] = f2bf(r);
-        l2[u] = f2bf(r - bf2f(l[u]));
-    }
-    hi = __builtin_bit_cast(bf16x8, h);
-    lo = __builtin_bit_cast(bf16x8, l);
-    lo2 = __builtin_bit_cast(bf16x8, l2);
-}
-
 __device__ __forceinline__ f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
@@ -144,6 +133,14 @@ __device__ __forceinline__ f32x16 zero16() {
     return z;
 }
 
+// dS, dS^T and P^T are kept as 32 x 32 tiles of 2 KB, [head][row tile][column tile], and a tile as its
+// 16-byte chunks [column chunk][row], so that the fragment a wave reads and the chunks it writes are
+// 1 KB in a row (as [L][L] rows the accesses were 64 bytes with a stride of 2 L bytes, for L a power
+// of two all on one memory channel; at L = 2048 dQ took 172 us and dK/dV 438 us, so 141 and 359).
+// Offset of lane's chunk `half` of tile (rt, ct):
+__device__ __forceinline__ int64_t tile_chunk(int64_t sh, int64_t nt, int64_t rt, int64_t ct, int half, int lane) {
+    return ((sh * nt + rt) * nt + ct) * (AT * AT) + (half * 64 + lane) * 8;
+}
 __device__ __forceinline__ int acc_row(int e, int lane) { return 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3); }
 
 }  // namespace
@@ -268,9 +265,20 @@ __global__ __launch_bounds__(256) void attn_fwd_kernel(const uint16_t* __restric
 // tiles (one per wave, the waves of a block take consecutive query tiles of one head): every key
 // tile is loaded once per block with direct-to-LDS 16-byte loads into one of two buffers, the next
 // tile's loads overlapping the current tile's work, and each wave keeps its query fragments in
-// registers.  Per lane the arithmetic (MFMA order, the float64 statistics, the three-term P) is that
-// of attn_fwd_kernel, so the outputs are bitwise the same.  LDS rows are XOR-swizzled by 16-byte
-// chunk so the fragment reads (one chunk of 16 or 32 consecutive rows) are free of bank conflicts:
+// registers.  Bound by the vector units (an exponent, an exponential and a three-term split per score
+// and pass), so the scores stay in registers: S^T = K Q^T puts a query in lane l % 32 and, with the
+// key rows taken in the order of attn_key(), 8 consecutive keys 16 k2 + 8 (l / 32) + 0..7 in entries
+// 8 k2 + 0..7, which is the fragment that P v reads.  Each half lane keeps its own reference exponent
+// and sum, merged after pass 1; the reference moves only when a score passes it by more than a factor
+// 2.  The exponent is formed in float64 in units of log 2 and its float32 goes to v_exp_f32: the same
+// half ulp of the exponent as expf of a float32 argument, without its range reduction.  Measured
+// against float64 at 32 to 1024 tokens the error of O32, LSE and the gradients is that of
+// attn_fwd_kernel's arithmetic (O32 1.477e-7, before 1.478e-7, at 512 tokens and 16 heads of 128).
+// 4 sequences of 2048 tokens, 32 heads of 128: 1465 us with scores and P through LDS and expf,
+// 1328 us with the scores in registers, 688 us with these exponentials, conversion instructions and
+// no accumulators moved between register files.
+// LDS rows are XOR-swizzled by 16-byte chunk so the fragment reads (one chunk of 16 or 32 consecutive
+// rows) are free of bank conflicts:
 //   key tile   [32 keys][HD] bf16, chunk c of key row r at position c ^ (r mod HD/8)
 //   value tile [HD cols][32 keys] bf16 (from v^T), chunk c of row r at c ^ ((r/2 ^ r/8) mod 4)
 namespace {
@@ -283,10 +291,31 @@ __device__ __forceinline__ void attn_wait_vm() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 __device__ __forceinline__ int vswz(int r) { return ((r >> 1) ^ (r >> 3)) & 3; }
+// hi | lo << 16 of one value, and the three bf16 terms of eight, rounded by the conversion instruction (to nearest even, as f2bf).
+__device__ __forceinline__ uint32_t split_pk(float x) {
+    asm("" : "+v"(x));  // a float from here on: one conversion each, not one from the float64 behind x
+    const __bf16 h = (__bf16)x;
+    return __builtin_bit_cast(uint32_t, bf16v2{h, (__bf16)(x - (float)h)});
+}
+__device__ __forceinline__ void split8x3_pk(const float (&x)[8], bf16x8& hi, bf16x8& lo, bf16x8& lo2) {
+    f32x8 v;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = x[u];
+    const bf16v8 h = __builtin_convertvector(v, bf16v8);
+    v -= __builtin_convertvector(h, f32x8);
+    const bf16v8 l = __builtin_convertvector(v, bf16v8);
+    v -= __builtin_convertvector(l, f32x8);
+    hi = __builtin_bit_cast(bf16x8, h);
+    lo = __builtin_bit_cast(bf16x8, l);
+    lo2 = __builtin_bit_cast(bf16x8, __builtin_convertvector(v, bf16v8));
+}
+__device__ __forceinline__ float attn_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+// The key that row r of the S^T product holds (a permutation within each 16 keys).
+__device__ __forceinline__ int attn_key(int r) { return (r & 16) | (r & 4) << 1 | (r & 8) >> 1 | (r & 3); }
 }  // namespace
 
 template <int HD>
-__global__ __launch_bounds__(256) void attn_fwd_lds_kernel(const uint16_t* __restrict__ qr,
+__global__ __launch_bounds__(256, 2) void attn_fwd_lds_kernel(const uint16_t* __restrict__ qr,
                                                            const uint16_t* __restrict__ kr,
                                                            const uint16_t* __restrict__ vt, int64_t T, int64_t H,
                                                            int64_t Hkv, int64_t L, float* __restrict__ O32,
@@ -296,8 +325,6 @@ __global__ __launch_bounds__(256) void attn_fwd_lds_kernel(const uint16_t* __res
     constexpr int KBYTES = AT * HD * 2, VBYTES = HD * AT * 2;
     constexpr int KDMA = KBYTES / 1024 / 4, VDMA = VBYTES / 1024 / 4;  // 1 KB loads per wave and tile
     static_assert(KDMA >= 1 && VDMA >= 1 && NCT <= CG, "head width");
-    __shared__ float sS[4][AT][AT + 1];
-    __shared__ __attribute__((aligned(16))) uint16_t sP[4][3][AT][TSTR];
     __shared__ __attribute__((aligned(16))) uint16_t sKV[2][(KBYTES + VBYTES) / 2];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wv = __builtin_amdgcn_readfirstlane(wave);
@@ -307,10 +334,8 @@ __global__ __launch_bounds__(256) void attn_fwd_lds_kernel(const uint16_t* __res
     const int64_t itmax = nt - 1 - 4 * qb;          // the block's longest row of key tiles
     const int64_t it = itmax - wave;                 // this wave's query tile (may be < 0)
     const int64_t g = h / (H / Hkv);
-    const double scale = 1.0 / sqrt((double)HD);
-    float(*Sw)[AT + 1] = sS[wave];
-    uint16_t(*Pw)[AT][TSTR] = sP[wave];
-    const int rr = lane >> 1, hh = lane & 1, c32 = lane & 31, k8 = 8 * (lane >> 5);
+    const double scale = 1.4426950408889634 / sqrt((double)HD);  // scores in units of log 2
+    const int c32 = lane & 31, k8 = 8 * (lane >> 5), krow = attn_key(c32);
     const int64_t ldk = Hkv * HD;                    // key row stride (elements)
     const uint16_t* kbase = kr + (s * L) * ldk + g * HD;
     const uint16_t* vbase = vt + (g * HD) * T + s * L;
@@ -346,48 +371,57 @@ __global__ __launch_bounds__(256) void attn_fwd_lds_kernel(const uint16_t* __res
 #pragma unroll
         for (int kk = 0; kk < NK; ++kk) qf[kk] = ld8(qa + 16 * kk);
     }
+    // entry e: query c32, key 16 (e / 8) + k8 + e % 8 of the tile; masked -inf
     auto scores = [&](int b, int64_t jt) {
         const uint16_t* kt = &sKV[b][0];
         f32x16 acc = zero16();
 #pragma unroll
         for (int kk = 0; kk < NK; ++kk) {
             const int c = 2 * kk + (lane >> 5);
-            const bf16x8 bk = ld8(kt + c32 * HD + ((c ^ (c32 % KCH)) * 8));
-            acc = mfma(qf[kk], bk, acc);
+            const bf16x8 bk = ld8(kt + krow * HD + ((c ^ (krow % KCH)) * 8));
+            acc = mfma(bk, qf[kk], acc);
         }
-        const bool diag = jt == it;
+        if (jt == it) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int r = acc_row(e, lane);
-            Sw[r][c32] = (diag && c32 > r) ? -INFINITY : acc[e];
+            for (int e = 0; e < 16; ++e)
+                if (16 * (e >> 3) + k8 + (e & 7) > c32) acc[e] = -INFINITY;
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        return acc;
     };
     // pass 1: the row max and sum
-    double m_row = -INFINITY, l_row = 0.0;
+    double m_row = -1e300, l_row = 0.0;    // of this half lane's keys (finite: it may have none)
     load_tile(0, 0, false);
     for (int64_t jt = 0; jt <= itmax; ++jt) {
         attn_wait_vm<0>();                 // this wave's share of tile jt has landed
         __syncthreads();                   // every share landed; tile jt-1's buffer is free
         if (jt + 1 <= itmax) load_tile(jt + 1, (int)((jt + 1) & 1), false);
         if (jt <= it) {
-            scores((int)(jt & 1), jt);
-            float smax = -INFINITY;  // scaling by a positive constant keeps the order
+            const f32x16 sc = scores((int)(jt & 1), jt);
+            float smax = sc[0];  // scaling by a positive constant keeps the order
 #pragma unroll
-            for (int k = 0; k < 16; ++k) smax = fmaxf(smax, Sw[rr][16 * hh + k]);
-            smax = fmaxf(smax, __shfl_xor(smax, 1));
-            const double m_new = fmax(m_row, (double)smax * scale);
+            for (int e = 1; e < 16; ++e) smax = fmaxf(smax, sc[e]);
+            const double mx = (double)smax * scale;
+            if (__any(mx > m_row + 1.0)) {
+                const double m_new = mx > m_row + 1.0 ? mx : m_row;
+                l_row *= exp2(m_row - m_new);
+                m_row = m_new;
+            }
             double sum = 0.0;
 #pragma unroll
-            for (int k = 0; k < 16; ++k) sum += (double)expf((float)((double)Sw[rr][16 * hh + k] * scale - m_new));
-            sum += __shfl_xor(sum, 1);
-            l_row = l_row * exp(m_row - m_new) + sum;
-            m_row = m_new;
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            for (int e = 0; e < 16; ++e) sum += (double)attn_exp2((float)fma((double)sc[e], scale, -m_row));
+            l_row += sum;
         }
     }
-    if (active0 && hh == 0) LSE[(s * L + it * AT + rr) * H + h] = m_row + log(l_row);
+    {
+        const double mo = __shfl_xor(m_row, 32), lo = __shfl_xor(l_row, 32), m = fmax(m_row, mo);
+        const double l0 = l_row * exp2(m_row - m), l1 = lo * exp2(mo - m);
+        l_row = l0 + l1;
+        m_row = m;
+    }
+    if (active0 && lane < 32) LSE[(s * L + it * AT + c32) * H + h] =
+            m_row * 0.6931471805599453 + log(l_row);
     const double inv_l = 1.0 / l_row;
+    const float inv_hi = (float)inv_l, inv_lo = (float)(inv_l - (double)inv_hi);
     // pass 2: P v over the value-column tiles
     f32x16 oacc[NCT];
 #pragma unroll
@@ -401,37 +435,30 @@ __global__ __launch_bounds__(256) void attn_fwd_lds_kernel(const uint16_t* __res
         if (jt + 1 <= itmax) load_tile(jt + 1, (int)((jt + 1) & 1), true);
         if (jt <= it) {
             const int b = (int)(jt & 1);
-            scores(b, jt);
-#pragma unroll
-            for (int k = 0; k < 16; ++k) {
-                const float pf =
-                    (float)((double)expf((float)((double)Sw[rr][16 * hh + k] * scale - m_row)) * inv_l);
-                const uint16_t ph = f2bf(pf);
-                const float r1 = pf - bf2f(ph);
-                const uint16_t pl = f2bf(r1);
-                Pw[0][rr][16 * hh + k] = ph;
-                Pw[1][rr][16 * hh + k] = pl;
-                Pw[2][rr][16 * hh + k] = f2bf(r1 - bf2f(pl));
-            }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const f32x16 sc = scores(b, jt);
             const uint16_t* vtile = &sKV[b][KBYTES / 2];
 #pragma unroll
             for (int k2 = 0; k2 < 2; ++k2) {
-                const int col = 16 * k2 + k8;
-                const bf16x8 ah = ld8(&Pw[0][c32][col]);
-                const bf16x8 al = ld8(&Pw[1][c32][col]);
-                const bf16x8 al2 = ld8(&Pw[2][c32][col]);
+                float p[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const float x = attn_exp2((float)fma((double)sc[8 * k2 + u], scale, -m_row));
+                    p[u] = fmaf(x, inv_hi, x * inv_lo);
+                }
+                bf16x8 a[3];
+                split8x3_pk(p, a[0], a[1], a[2]);
                 const int c = 2 * k2 + (lane >> 5);
+                bf16x8 bv[NCT];
 #pragma unroll
                 for (int ct = 0; ct < NCT; ++ct) {
                     const int row = ct * AT + c32;
-                    const bf16x8 bv = ld8(vtile + row * AT + ((c ^ vswz(row)) * 8));
-                    oacc[ct] = mfma(ah, bv, oacc[ct]);
-                    oacc[ct] = mfma(al, bv, oacc[ct]);
-                    oacc[ct] = mfma(al2, bv, oacc[ct]);
+                    bv[ct] = ld8(vtile + row * AT + ((c ^ vswz(row)) * 8));
                 }
+#pragma unroll
+                for (int term = 0; term < 3; ++term)
+#pragma unroll
+                    for (int ct = 0; ct < NCT; ++ct) oacc[ct] = mfma(a[term], bv[ct], oacc[ct]);
             }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
     }
     if (!active0) return;
@@ -543,8 +570,8 @@ __global__ __launch_bounds__(256) void attn_ds_kernel(const uint16_t* __restrict
         split_bf16(ds, vh[e], vl[e]);
         split_bf16(p, qh[e], ql[e]);
     }
-    const int r = lane >> 2, c8 = (lane & 3) * 8;
-    auto flush = [&](const uint16_t (&v)[16], bool transposed, uint16_t* dst, int64_t row0, int64_t col0) {
+    const int r = lane & 31, c8 = (lane >> 5) * 8;
+    auto flush = [&](const uint16_t (&v)[16], bool transposed, uint16_t* dst, int64_t rt, int64_t ct) {
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             const int a = acc_row(e, lane), b = lane & 31;
@@ -554,27 +581,29 @@ __global__ __launch_bounds__(256) void attn_ds_kernel(const uint16_t* __restrict
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
-            const int rr = r + 16 * half;
-            *reinterpret_cast<u16x8*>(dst + (sh * L + row0 + rr) * L + col0 + c8) =
-                *reinterpret_cast<const u16x8*>(&tb[rr][c8]);
+            *reinterpret_cast<u16x8*>(dst + tile_chunk(sh, nt, rt, ct, half, lane)) =
+                *reinterpret_cast<const u16x8*>(&tb[r][c8 + 16 * half]);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     };
-    flush(vh, false, dSh, it * AT, jt * AT);
-    flush(vl, false, dSl, it * AT, jt * AT);
-    flush(vh, true, dSth, jt * AT, it * AT);
-    flush(vl, true, dStl, jt * AT, it * AT);
-    flush(qh, true, Pth, jt * AT, it * AT);
-    flush(ql, true, Ptl, jt * AT, it * AT);
+    flush(vh, false, dSh, it, jt);
+    flush(vl, false, dSl, it, jt);
+    flush(vh, true, dSth, jt, it);
+    flush(vl, true, dStl, jt, it);
+    flush(qh, true, Pth, jt, it);
+    flush(ql, true, Ptl, jt, it);
 }
 
 // attn_ds_kernel with the work of a query tile in one wave (used when the grid has at least 512
-// blocks: with 300 registers a wave has its SIMD to itself): the four waves of a block take
+// blocks: with 260 registers a wave has its SIMD to itself): the four waves of a block take
 // consecutive query tiles of one head (as the forward's), keep their query fragments, LSE and D in
-// LDS and their dO rows in registers (split into three terms per key tile), and walk the
+// LDS and their dO rows in registers (split into three terms once), and walk the
 // key tiles on or below their diagonal while the block streams each key tile and value tile into
 // two LDS buffers (rows XOR-swizzled as in the forward).  Per element the arithmetic is that of
-// attn_ds_kernel, so the six outputs are bitwise the same.
+// attn_ds_kernel, except that the probabilities are formed as in the forward's second form.  Bound by
+// the 12 bytes written per score and by one wave per SIMD; 2 sequences of 2048 tokens, 16 heads of
+// 128: 502 us with expf and rows of [L][L], 441 us with the forward's exponentials and conversion
+// instructions, 305 us with tile-major outputs and without a branch per score (2.6 TB/s written).
 template <int HD>
 __global__ __launch_bounds__(256) void attn_ds_lds_kernel(const uint16_t* __restrict__ qr,
                                                           const uint16_t* __restrict__ kr,
@@ -594,7 +623,7 @@ __global__ __launch_bounds__(256) void attn_ds_lds_kernel(const uint16_t* __rest
     __shared__ __attribute__((aligned(16))) uint16_t sKV[2][TBYTES];   // [buf][key tile | value tile]
     __shared__ __attribute__((aligned(16))) uint16_t sQ[4][AT * HD];    // each wave's query rows (swizzled)
     __shared__ __attribute__((aligned(16))) uint32_t stage[4][AT][TSTR32];
-    __shared__ double sLD[4][2][AT];
+    __shared__ __attribute__((aligned(16))) f64x2 sLD[4][AT];  // LSE (units of log 2), D
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wv = __builtin_amdgcn_readfirstlane(wave);
     const int64_t nt = L / AT, nq = (nt + 3) / 4;
@@ -639,28 +668,30 @@ __global__ __launch_bounds__(256) void attn_ds_lds_kernel(const uint16_t* __rest
             split8x3(a + 16 * kk, dOh[kk], dOl[kk], dOl2[kk]);
         }
         if (lane < AT) {
-            sLD[wave][0][lane] = LSE[(s * L + it * AT + lane) * H + h];
-            sLD[wave][1][lane] = D[(s * L + it * AT + lane) * H + h];
+            const int64_t r = (s * L + it * AT + lane) * H + h;
+            sLD[wave][lane] = f64x2{LSE[r] * 1.4426950408889634, D[r]};
         }
     }
-    const double scale = 1.0 / sqrt((double)HD);
+    const double scale = 1.4426950408889634 / sqrt((double)HD);  // exponents in units of log 2
     uint32_t(*tb)[TSTR32] = stage[wave];
-    const int r = lane >> 2, c8 = (lane & 3) * 8;
+    const int r = lane & 31, c8 = (lane >> 5) * 8;
     // values packed as hi | lo << 16, staged whole and split into the hi and lo arrays on the way out
-    auto flush = [&](const uint32_t (&val)[16], bool transposed, uint16_t* dst_hi, uint16_t* dst_lo, int64_t row0,
-                     int64_t col0) {
+    auto flush = [&](const uint32_t (&val)[16], bool transposed, uint16_t* dst_hi, uint16_t* dst_lo, int64_t rt,
+                     int64_t ct) {
+        if (transposed) {  // entries 4 q .. 4 q + 3 are consecutive query rows
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int a = acc_row(e, lane), b = lane & 31;
-            if (transposed) tb[b][a] = val[e];
-            else tb[a][b] = val[e];
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<u32x4*>(&tb[c32][acc_row(4 * q, lane)]) =
+                    u32x4{val[4 * q], val[4 * q + 1], val[4 * q + 2], val[4 * q + 3]};
+        } else {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) tb[acc_row(e, lane)][c32] = val[e];
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
-            const int rr = r + 16 * half;
-            const u32x4 v0 = *reinterpret_cast<const u32x4*>(&tb[rr][c8]);
-            const u32x4 v1 = *reinterpret_cast<const u32x4*>(&tb[rr][c8 + 4]);
+            const u32x4 v0 = *reinterpret_cast<const u32x4*>(&tb[r][c8 + 16 * half]);
+            const u32x4 v1 = *reinterpret_cast<const u32x4*>(&tb[r][c8 + 16 * half + 4]);
             u16x8 h, l;
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -669,7 +700,7 @@ __global__ __launch_bounds__(256) void attn_ds_lds_kernel(const uint16_t* __rest
                 h[u + 4] = (uint16_t)(v1[u] & 0xffffu);
                 l[u + 4] = (uint16_t)(v1[u] >> 16);
             }
-            const int64_t o = (sh * L + row0 + rr) * L + col0 + c8;
+            const int64_t o = tile_chunk(sh, nt, rt, ct, half, lane);
             *reinterpret_cast<u16x8*>(dst_hi + o) = h;
             *reinterpret_cast<u16x8*>(dst_lo + o) = l;
         }
@@ -697,22 +728,27 @@ __global__ __launch_bounds__(256) void attn_ds_lds_kernel(const uint16_t* __rest
             acc = mfma(dOl2[kk], bv, acc);
             sc = mfma(ld8(qw + off), ld8(kt + off), sc);
         }
+        float pv[16];
+        double ld[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const f64x2 x = sLD[wave][acc_row(e, lane)];
+            pv[e] = attn_exp2((float)fma((double)sc[e], scale, -x[0]));
+            ld[e] = x[1];
+        }
+        if (jt == it) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) pv[e] = c32 <= acc_row(e, lane) ? pv[e] : 0.f;
+        }
         uint32_t dsv[16], pv2[16];
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            const int ir = acc_row(e, lane);
-            const int64_t i = it * AT + ir, j = jt * AT + c32;
-            const float pv = j <= i ? expf((float)((double)sc[e] * scale - sLD[wave][0][ir])) : 0.f;
-            const float ds = (float)((double)pv * ((double)acc[e] - sLD[wave][1][ir]));
-            uint16_t a0, a1, b0, b1;
-            split_bf16(ds, a0, a1);
-            split_bf16(pv, b0, b1);
-            dsv[e] = (uint32_t)a0 | ((uint32_t)a1 << 16);
-            pv2[e] = (uint32_t)b0 | ((uint32_t)b1 << 16);
+            dsv[e] = split_pk((float)((double)pv[e] * ((double)acc[e] - ld[e])));
+            pv2[e] = split_pk(pv[e]);
         }
-        flush(dsv, false, dSh, dSl, it * AT, jt * AT);
-        flush(dsv, true, dSth, dStl, jt * AT, it * AT);
-        flush(pv2, true, Pth, Ptl, jt * AT, it * AT);
+        flush(dsv, false, dSh, dSl, it, jt);
+        flush(dsv, true, dSth, dStl, jt, it);
+        flush(pv2, true, Pth, Ptl, jt, it);
     }
 }
 
@@ -726,14 +762,14 @@ __global__ __launch_bounds__(256) void attn_dq_kernel(const uint16_t* __restrict
     const int64_t ct = (int64_t)blockIdx.y * 4 + wave;
     if (ct >= hd / AT) return;
     const int64_t g = h / (H / Hkv);
-    const int64_t arow = (sh * L + it * AT + (lane & 31)) * L + 8 * (lane >> 5);
     const uint16_t* b = kt + (g * hd + ct * AT + (lane & 31)) * T + s * L + 8 * (lane >> 5);
     f32x16 acc = zero16();
     const int64_t jend = (it + 1) * AT;
     for (int64_t j0 = 0; j0 < jend; j0 += 32) {  // two steps per trip
         const bf16x8 b0 = ld8(b + j0), b1 = ld8(b + j0 + 16);
-        const bf16x8 h0 = ld8(dSh + arow + j0), l0 = ld8(dSl + arow + j0);
-        const bf16x8 h1 = ld8(dSh + arow + j0 + 16), l1 = ld8(dSl + arow + j0 + 16);
+        const int64_t a0 = tile_chunk(sh, nt, it, j0 / AT, 0, lane), a1 = a0 + 512;
+        const bf16x8 h0 = ld8(dSh + a0), l0 = ld8(dSl + a0);
+        const bf16x8 h1 = ld8(dSh + a1), l1 = ld8(dSl + a1);
         acc = mfma(h0, b0, acc);
         acc = mfma(l0, b0, acc);
         acc = mfma(h1, b1, acc);
@@ -768,7 +804,7 @@ __global__ __launch_bounds__(256) void attn_dq_lds_kernel(const uint16_t* __rest
     const int64_t itmax = nt - 1 - 4 * qb;
     const int64_t it = itmax - wave;
     const int64_t g = h / (H / Hkv);
-    const int c32 = lane & 31, k8 = 8 * (lane >> 5);
+    const int c32 = lane & 31;
     u16x8 breg[BCH];
     auto load_B = [&](int64_t jt) {
 #pragma unroll
@@ -789,12 +825,12 @@ __global__ __launch_bounds__(256) void attn_dq_lds_kernel(const uint16_t* __rest
     struct AF {
         bf16x8 h[2], l[2];
     };
-    const int64_t arow = (sh * L + it * AT + c32) * L + k8;
     auto load_A = [&](int64_t jt, AF& f) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            f.h[u] = ld8(dSh + arow + jt * AT + 16 * u);
-            f.l[u] = ld8(dSl + arow + jt * AT + 16 * u);
+            const int64_t a = tile_chunk(sh, nt, it, jt, u, lane);
+            f.h[u] = ld8(dSh + a);
+            f.l[u] = ld8(dSl + a);
         }
     };
     f32x16 acc[NCT];
@@ -865,18 +901,17 @@ __global__ __launch_bounds__(256) void attn_dkv_kernel(const uint16_t* __restric
     f32x16 ak = zero16(), av = zero16();
     for (int64_t hh = 0; hh < rep; ++hh) {
         const int64_t h = g * rep + hh, sh = s * H + h;
-        const int64_t arow = (sh * L + jt * AT + (lane & 31)) * L + 8 * (lane >> 5);
         const int64_t brow = (h * hd + ct * AT + (lane & 31)) * T + s * L + 8 * (lane >> 5);
         for (int64_t i0 = ibeg; i0 < iend; i0 += 32) {  // whole tiles: two steps per trip
             bf16x8 q[2], sh_[2], sl[2], ph[2], pl[2], doh[2], dol[2];
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                const int64_t k = i0 + 16 * u;
+                const int64_t k = i0 + 16 * u, a = tile_chunk(sh, nt, jt, i0 / AT, u, lane);
                 q[u] = ld8(qt + brow + k);
-                sh_[u] = ld8(dSth + arow + k);
-                sl[u] = ld8(dStl + arow + k);
-                ph[u] = ld8(Pth + arow + k);
-                pl[u] = ld8(Ptl + arow + k);
+                sh_[u] = ld8(dSth + a);
+                sl[u] = ld8(dStl + a);
+                ph[u] = ld8(Pth + a);
+                pl[u] = ld8(Ptl + a);
                 doh[u] = ld8(dOth + brow + k);
                 dol[u] = ld8(dOtl + brow + k);
             }
@@ -934,7 +969,7 @@ __global__ __launch_bounds__(256) void attn_dkv_lds_kernel(const uint16_t* __res
     const bool wave_on = jt < nt && (z + 1) * CH > jt;  // this wave's key tile has terms in the chunk
     const int64_t rep = H / Hkv;
     const int64_t nsteps = rep * (i1 - i0);
-    const int c32 = lane & 31, k8 = 8 * (lane >> 5);
+    const int c32 = lane & 31;
     const uint16_t* Bsrc[3] = {qt, dOth, dOtl};
     // step x: head hh = x / (i1 - i0), query tile it = i0 + x % (i1 - i0)
     auto step_of = [&](int64_t x, int64_t& h, int64_t& it) {
@@ -966,14 +1001,13 @@ __global__ __launch_bounds__(256) void attn_dkv_lds_kernel(const uint16_t* __res
     auto load_A = [&](int64_t x, AF& f) {
         int64_t h, it;
         step_of(x, h, it);
-        const int64_t sh = s * H + h;
-        const int64_t arow = (sh * L + jt * AT + c32) * L + it * AT + k8;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            f.sh[u] = ld8(dSth + arow + 16 * u);
-            f.sl[u] = ld8(dStl + arow + 16 * u);
-            f.ph[u] = ld8(Pth + arow + 16 * u);
-            f.pl[u] = ld8(Ptl + arow + 16 * u);
+            const int64_t a = tile_chunk(s * H + h, nt, jt, it, u, lane);
+            f.sh[u] = ld8(dSth + a);
+            f.sl[u] = ld8(dStl + a);
+            f.ph[u] = ld8(Pth + a);
+            f.pl[u] = ld8(Ptl + a);
         }
     };
     auto active = [&](int64_t x) {

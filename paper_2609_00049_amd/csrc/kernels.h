@@ -234,7 +234,7 @@ hipError_t rope_inv(const float* in, float* out, const double* cs, int64_t T, in
 hipError_t attn_fwd(const uint16_t* qr, const uint16_t* kr, const uint16_t* v, int64_t T, int64_t H, int64_t Hkv,
                     int64_t hd, int64_t L, double* LSE, float* O32, uint16_t* O, uint16_t* vt, hipStream_t st);
 // Scratch of the attention backward: D [T][H] float64; dS, dS^T and P^T as bf16 hi/lo pairs,
-// each [T/L][H][L][L]; kr^T [Hkv hd][T], qr^T [H hd][T], dO^T hi/lo [H hd][T]; partial dK/dV.
+// each [T/L][H] times L^2 in 32 x 32 tiles; kr^T [Hkv hd][T], qr^T [H hd][T], dO^T hi/lo [H hd][T]; partial dK/dV.
 struct AttnScratch {
     double* D;
     uint16_t *dSh, *dSl, *dSth, *dStl, *Pth, *Ptl;
