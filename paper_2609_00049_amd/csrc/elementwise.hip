@@ -2,8 +2,6 @@
 // reductions and the fused split-K reduction + Adam update (Appendix D.1 constants
 // arrive as arguments).  Every kernel here is HBM-bound; loops are grid-strided
 // with coalesced rows.
-#include <algorithm>
-
 #include "common.h"
 #include "kernels.h"
 
@@ -43,10 +41,8 @@ hipError_t fill_u16(uint16_t* p, uint16_t v, int64_t count, hipStream_t st) {
 
 // ---------------------------------------------------------------- tiled transposes (64 x 64 tiles via LDS)
 // out[c][r] of a token-major bf16 array.  Bound by HBM: 16-byte loads along a row and 16-byte stores
-// along a column where the arrays allow them (2-byte accesses per lane moved 2.4 TB/s), the 16-bit
-// tile in LDS with rows 33 banks apart so that the eight values of a column chunk and the eight chunks
-// of a wave fall on different banks.  1024 columns x 131072 tokens with the weighted terms: 622 us
-// as two passes of 2-byte accesses, 245 us here.
+// along a column where the arrays allow them (2-byte accesses per lane moved 2.4 TB/s), the 16-bit tile in LDS with rows 33 banks apart so that the eight values of a
+// column chunk and the eight chunks of a wave fall on different banks.
 // SCALE: also the three bf16 terms of s[r] * x (hi + lo + lo2 holds all 24 bits of the float32
 // product), in the same pass over the input; o0 (the plain transpose) may then be NULL.
 namespace {
@@ -717,35 +713,25 @@ __device__ __forceinline__ void adam_elem(const AdamArgs& a, int64_t i, int64_t 
     a.Dlo[di] = l;
 }
 
-// One row per blockIdx.y step and 256 columns per blockIdx.x: no division per element (the 64-bit one
-// of a flat index was most of the work: 131072 weights in 16 slices 20 us, 5 us now).  The slices are summed in
-// order, eight loads in flight.
-__global__ __launch_bounds__(256) void adam_kernel(AdamArgs a) {
-    const int64_t w = a.n - a.c1, zstride = a.m * w;
-    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (j >= w) return;
-    for (int64_t i = blockIdx.y; i < a.m; i += gridDim.y) {
-        const int64_t e = i * w + j;
+__global__ void adam_kernel(AdamArgs a) {
+    const int64_t w = a.n - a.c1;
+    const int64_t total = a.m * w;
+    const int64_t zstride = a.m * w;
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
         float g = 0.f;
-#pragma unroll 8
         for (int64_t z = 0; z < a.splits; ++z) g += a.Gp[z * zstride + e];
         if (a.g0_mode == 2) g += a.G0[e];
         else if (a.g0_mode == 1) a.G0[e] = g;
         g *= a.gscale;
-        adam_elem(a, i, a.c1 + j, g);
+        int64_t i = e / w, j = a.c1 + e % w;
+        adam_elem(a, i, j, g);
     }
 }
 
-// Columns in blocks of 256, and as many row steps as make about 32768 blocks (16 per compute unit and
-// round; below that one row per block).
-static dim3 row_grid(int64_t rows, int64_t cols) {
-    const int64_t x = (cols + 255) / 256, y = std::max<int64_t>(1, std::min<int64_t>(rows, 32768 / x));
-    return dim3((unsigned)x, (unsigned)y);
-}
-
 hipError_t adam_update(const AdamArgs& a, hipStream_t st) {
-    if (a.m <= 0 || a.n <= a.c1) return hipSuccess;
-    hipLaunchKernelGGL(adam_kernel, row_grid(a.m, a.n - a.c1), dim3(256), 0, st, a);
+    const int64_t total = a.m * (a.n - a.c1);
+    if (total <= 0) return hipSuccess;
+    hipLaunchKernelGGL(adam_kernel, dim3(grid_for(total, 4)), dim3(TB), 0, st, a);
     return hipGetLastError();
 }
 
@@ -799,16 +785,19 @@ hipError_t inc_loss(const double* L0, const float* G0, const uint16_t* Dinc, int
     return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void adam_dense_kernel(AdamArgs a, const float* __restrict__ G) {
+__global__ void adam_dense_kernel(AdamArgs a, const float* __restrict__ G) {
     const int64_t w = a.n - a.c1;
-    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (j >= w) return;
-    for (int64_t i = blockIdx.y; i < a.m; i += gridDim.y) adam_elem(a, i, a.c1 + j, G[i * w + j]);
+    const int64_t total = a.m * w;
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
+        int64_t i = e / w, j = a.c1 + e % w;
+        adam_elem(a, i, j, G[e]);
+    }
 }
 
 hipError_t adam_update_dense(const AdamArgs& a, const float* G, hipStream_t st) {
-    if (a.m <= 0 || a.n <= a.c1) return hipSuccess;
-    hipLaunchKernelGGL(adam_dense_kernel, row_grid(a.m, a.n - a.c1), dim3(256), 0, st, a, G);
+    const int64_t total = a.m * (a.n - a.c1);
+    if (total <= 0) return hipSuccess;
+    hipLaunchKernelGGL(adam_dense_kernel, dim3(grid_for(total, 4)), dim3(TB), 0, st, a, G);
     return hipGetLastError();
 }
 
@@ -816,7 +805,6 @@ __global__ void reduce_splits_kernel(const float* __restrict__ Gp, int64_t split
                                      float* __restrict__ G, int accumulate) {
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
         float g = 0.f;
-#pragma unroll 8
         for (int64_t z = 0; z < splits; ++z) g += Gp[z * total + e];
         g *= gscale;
         G[e] = accumulate ? G[e] + g : g;
