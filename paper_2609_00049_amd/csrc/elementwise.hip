@@ -2,6 +2,8 @@
 // reductions and the fused split-K reduction + Adam update (Appendix D.1 constants
 // arrive as arguments).  Every kernel here is HBM-bound; loops are grid-strided
 // with coalesced rows.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -303,18 +305,23 @@ hipError_t split_f64(const double* in, uint16_t* hi, uint16_t* lo, int64_t ldo, 
 }
 
 // Rows of `cols` bf16 values copied to stride ldo: activations whose rows are not a multiple of 16
-// bytes, laid out once for the GEMMs' direct-to-LDS loads.  One row per blockIdx.x.
+// bytes, laid out once for the GEMMs' direct-to-LDS loads.  A block takes every gridDim.x-th row.
 __global__ __launch_bounds__(256) void copy_rows_kernel(const uint16_t* __restrict__ in, int64_t ldi,
-                                                        uint16_t* __restrict__ out, int64_t ldo, int64_t cols) {
-    const uint16_t* p = in + (int64_t)blockIdx.x * ldi;
-    uint16_t* q = out + (int64_t)blockIdx.x * ldo;
-    for (int64_t c = threadIdx.x; c < cols; c += 256) q[c] = p[c];
+                                                        uint16_t* __restrict__ out, int64_t ldo, int64_t rows,
+                                                        int64_t cols) {
+    for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
+        const uint16_t* p = in + r * ldi;
+        uint16_t* q = out + r * ldo;
+        for (int64_t c = threadIdx.x; c < cols; c += 256) q[c] = p[c];
+    }
 }
 
 hipError_t copy_rows_u16(const uint16_t* in, int64_t ldi, uint16_t* out, int64_t ldo, int64_t rows, int64_t cols,
                          hipStream_t st) {
     if (rows <= 0 || cols <= 0) return hipSuccess;
-    hipLaunchKernelGGL(copy_rows_kernel, dim3((unsigned)rows), dim3(256), 0, st, in, ldi, out, ldo, cols);
+    // a launch holds less than 2^32 threads: 2^20 blocks at most, whatever the token count
+    const int64_t grid = std::min<int64_t>(rows, 1 << 20);
+    hipLaunchKernelGGL(copy_rows_kernel, dim3((unsigned)grid), dim3(256), 0, st, in, ldi, out, ldo, rows, cols);
     return hipGetLastError();
 }
 

@@ -1,0 +1,76 @@
+"""Checks of the library's host logic (launch limits, launch counts, memory held) on the HIP runtime of
+fake_hip.cpp, which books allocations and launches and computes nothing.  Run by tests/test_host_logic.py
+as a program of its own, one check per process:  host_logic.py <fake runtime> <library> <check>."""
+import ctypes
+import sys
+
+VP, I64 = ctypes.c_void_p, ctypes.c_int64
+
+
+class BgdParams(ctypes.Structure):
+    _fields_ = [("steps", ctypes.c_int32), ("lr", ctypes.c_float), ("beta1", ctypes.c_float), ("beta2", ctypes.c_float),
+                ("eps", ctypes.c_float), ("tok_chunk", I64), ("form", ctypes.c_int32), ("loss_clip", ctypes.c_float),
+                ("batch", I64), ("resid_increment", ctypes.c_int32)]
+
+
+def buf(k):
+    """A device address of the caller's; nothing reads it."""
+    return VP((1 << 36) + (k << 34))
+
+
+class Library:
+    def __init__(self, fake, lib):
+        self.fake = ctypes.CDLL(fake, mode=ctypes.RTLD_GLOBAL)  # first: the library's HIP calls bind to it
+        for f in ("fake_held", "fake_peak", "fake_launches", "fake_bad_launches", "fake_copies", "fake_mallocs"):
+            getattr(self.fake, f).restype = I64
+        self.fake.fake_set_limit.argtypes = [I64]
+        self.fake.fake_set_host_value.argtypes = [ctypes.c_double]
+        self.c = ctypes.CDLL(lib)
+        self.c.realq_last_error.restype = ctypes.c_char_p
+        self.c.realq_last_error.argtypes = [VP]
+        self.ctx = VP()
+        assert self.c.realq_ctx_create(ctypes.byref(self.ctx), None) == 0
+
+    def call(self, name, *args):
+        """A call of the ABI on this context; ints go as int64, floats as float."""
+        conv = {int: I64, float: ctypes.c_float}
+        rc = getattr(self.c, name)(self.ctx, *[conv.get(type(a), lambda x: x)(a) for a in args])
+        return rc, "" if rc == 0 else self.c.realq_last_error(self.ctx).decode()
+
+    def ok(self, name, *args):
+        rc, msg = self.call(name, *args)
+        assert rc == 0, (name, rc, msg)
+        assert self.fake.fake_bad_launches() == 0
+
+    def state(self, m, n, T, s=buf(4), M=None, P=None, same=False, **params):
+        b = BgdParams()
+        self.c.realq_bgd_params_default(ctypes.byref(b))
+        b.steps = 2
+        for k, v in params.items():
+            setattr(b, k, v)
+        st = VP()
+        self.ok("realq_bgd_state_create", ctypes.byref(st), buf(1), buf(2), buf(2) if same else buf(3), s, M, P, m, n, T,
+                ctypes.byref(b))
+        return st
+
+    def held(self):
+        return self.fake.fake_held()
+
+    def launches(self):
+        return self.fake.fake_launches(b"") + self.fake.fake_copies()
+
+
+def many_tokens(L):
+    """Rows that need a padded copy, 2^24 of them: no launch past the grid limit."""
+    T = 1 << 24
+    for n in (133, 136):
+        st = L.state(64, n, T)
+        L.ok("realq_bgd_lock_block", st, 0, 128)
+        L.ok("realq_bgd_loss", st, buf(5), buf(6))
+        L.c.realq_bgd_state_destroy(st)
+    L.ok("realq_handoff", buf(1), None, buf(2), T, 133, 64, buf(3))
+
+
+if __name__ == "__main__":
+    globals()[sys.argv[3]](Library(sys.argv[1], sys.argv[2]))
+    print("passed")
