@@ -87,14 +87,13 @@ struct realq_bgd_state {
     bool owns = true;
     // Rows of every GEMM operand start on 16 bytes whatever n and T are (the direct-to-LDS loads need
     // it; the checked register path is about 6x slower) and are an odd number of 128-byte lines
-    // apart (plan::operand_stride): columns padded to ldn, tokens to Tp.  When the steps' token chunks
-    // do not start on multiples of 8 tokens each chunk starts on a multiple of 64 in the token-minor
-    // arrays instead (chunk_pos).  Xg / sg are padded copies of the caller's activations and token
-    // weights.
+    // apart (plan::operand_stride): columns padded to ldn, tokens to Tp.  `at` gives each token's place
+    // in the token-minor arrays (plan::Places).  Xg / sg are padded copies of the caller's activations
+    // and token weights in the order of the places.
     int64_t ldn = 0, ldx = 0, Tp = 0;
-    bool chunked = false;
-    const uint16_t* Xg = nullptr;  // [T,ldx] Xhat as the GEMMs read it (ldx = n: the caller's own)
-    const float* sg = nullptr;     // [Tp] token weights at their chunk positions, or NULL
+    realq::plan::Places at;
+    const uint16_t* Xg = nullptr;  // [at.count,ldx] Xhat as the GEMMs read it (ldx = n: the caller's own)
+    const float* sg = nullptr;     // [at.count] token weights, or NULL
     float* B = nullptr;  // [m,Tp] residual base
     float* mA = nullptr;
     float* vA = nullptr;  // [m,n]
@@ -422,30 +421,6 @@ static int64_t r_ld(int64_t cur) { return realq::plan::operand_stride(2 * ((cur 
 // row stride of bf16(acc o s) on a later step of a column block (row-major, in the same buffer)
 static int64_t q_ld(int64_t cur) { return realq::plan::operand_stride(cur); }
 
-// Position of the token chunk that starts at t0 in the token-minor arrays (B, XhT, sg).
-static int64_t chunk_pos(const realq_bgd_state* st, int64_t t0) {
-    if (!st->chunked) return t0;
-    const int64_t cs = (st->Tc + 63) / 64 * 64, per_batch = (st->Tb + st->Tc - 1) / st->Tc;
-    return (t0 / st->Tb * per_batch + t0 % st->Tb / st->Tc) * cs;
-}
-// Calls f(t0, len, pos) for token ranges that are contiguous in the token-minor arrays: all tokens,
-// or with chunked positions every chunk.
-extern "C++" {
-template <class F>
-static int each_range(const realq_bgd_state* st, F f) {
-    if (!st->chunked) return f((int64_t)0, st->T, (int64_t)0);
-    for (int64_t b0 = 0; b0 < st->T; b0 += st->Tb) {
-        const int64_t b1 = std::min(st->T, b0 + st->Tb);
-        for (int64_t t0 = b0; t0 < b1; t0 += st->Tc)
-            if (int rc = f(t0, std::min(st->Tc, b1 - t0), chunk_pos(st, t0))) return rc;
-    }
-    return REALQ_OK;
-}
-}  // extern "C++"
-static const float* chunk_s(const realq_bgd_state* st, int64_t t0) {
-    return st->sg ? st->sg + chunk_pos(st, t0) : nullptr;
-}
-
 static int state_alloc(realq_bgd_state* st, void** p, size_t bytes, const char* slot) {
     realq_ctx* ctx = st->ctx;
     if (!st->owns) return get_ws(ctx, slot, bytes, p);
@@ -580,12 +555,26 @@ static int state_init(realq_bgd_state* st) {
     int64_t Tc = st->prm.tok_chunk > 0 ? std::min<int64_t>(st->prm.tok_chunk, st->Tb) : st->Tb;
     st->Tc = Tc;
     const int64_t ldn = st->ldn = realq::plan::operand_stride(n);
-    st->chunked = (Tc < T && Tc % 8) || (st->Tb < T && st->Tb % 8);
-    const int64_t per_batch = (st->Tb + Tc - 1) / Tc;
-    const int64_t Tp = st->Tp =
-        realq::plan::operand_stride(st->chunked ? st->nbatch * per_batch * ((Tc + 63) / 64 * 64) : T);
     int rc;
     void* p;
+    st->at = realq::plan::place_tokens(T, st->Tb, Tc);
+    // The activations are copied where their rows or places differ from the caller's.  The copy costs one
+    // read and write of Xhat against a residual product per Block-GD step; without steps, or without
+    // room for it, aligned rows stay where they are.  Without room, tokens keep their order.
+    st->Xg = st->Xhat;
+    st->ldx = n;
+    if (st->at.apart || (ldn != n && (n % 8 || st->prm.steps > 0))) {
+        rc = state_alloc(st, &p, (size_t)st->at.count * ldn * 2, "s_Xg");
+        if (rc && (rc != REALQ_ERR_OOM || n % 8)) return rc;
+        if (rc) {
+            st->at = realq::plan::place_tokens(T, st->Tb, Tc, false);
+        } else {
+            st->Xg = (const uint16_t*)p;
+            st->ldx = ldn;
+        }
+    }
+    const realq::plan::Places& at = st->at;
+    const int64_t Tp = st->Tp = realq::plan::operand_stride(at.count);
     if ((rc = state_alloc(st, &p, (size_t)m * Tp * 4, "s_B"))) return rc;
     st->B = (float*)p;
     if ((rc = state_alloc(st, &p, (size_t)m * n * 4, "s_m"))) return rc;
@@ -620,35 +609,14 @@ static int state_init(realq_bgd_state* st) {
     Timed tm(ctx, "init");
     RQ_HIP(ctx, realq::fill_f32(st->mA, 0.f, m * n, s));
     RQ_HIP(ctx, realq::fill_f32(st->vA, 0.f, m * n, s));
-    // The copy costs one read and write of Xhat against a residual product per Block-GD step; without
-    // steps, or without room for it, aligned rows stay where they are.
-    st->Xg = st->Xhat;
-    st->ldx = n;
-    if (ldn != n && (n % 8 || st->prm.steps > 0)) {
-        rc = state_alloc(st, &p, (size_t)T * ldn * 2, "s_Xg");
-        if (rc && (rc != REALQ_ERR_OOM || n % 8)) return rc;
-        if (!rc) {
-            st->Xg = (const uint16_t*)p;
-            st->ldx = ldn;
-            RQ_HIP(ctx, realq::copy_rows_u16(st->Xhat, n, (uint16_t*)p, ldn, T, n, s));
-        }
-    }
-    const int64_t ldx = st->ldx;
+    if (st->Xg != st->Xhat) RQ_HIP(ctx, realq::place_rows_u16(st->Xhat, n, const_cast<uint16_t*>(st->Xg), ldn, n, at, s));
     st->sg = st->s;
-    if (st->s && st->chunked) {
-        if ((rc = state_alloc(st, &p, (size_t)Tp * 4, "s_sg"))) return rc;
+    if (st->s && at.apart) {
+        if ((rc = state_alloc(st, &p, (size_t)at.count * 4, "s_sg"))) return rc;
         st->sg = (const float*)p;
-        if ((rc = each_range(st, [&](int64_t t0, int64_t len, int64_t pos) -> int {
-                 RQ_HIP(ctx, hipMemcpyAsync((float*)p + pos, st->s + t0, (size_t)len * 4, hipMemcpyDeviceToDevice, s));
-                 return REALQ_OK;
-             })))
-            return rc;
+        RQ_HIP(ctx, realq::place_f32(st->s, (float*)p, at, s));
     }
-    if ((rc = each_range(st, [&](int64_t t0, int64_t len, int64_t pos) -> int {
-             RQ_HIP(ctx, realq::transpose_u16(st->Xg + t0 * ldx, ldx, st->XhT + pos, Tp, len, n, s));
-             return REALQ_OK;
-         })))
-        return rc;
+    RQ_HIP(ctx, realq::transpose_u16(st->Xg, st->ldx, st->XhT, Tp, at.count, n, s));
     // Residual base before any block is locked: B = W0 (Xhat - X)^T.
     if (st->X == st->Xhat) {
         RQ_HIP(ctx, realq::fill_f32(st->B, 0.f, m * Tp, s));
@@ -656,23 +624,18 @@ static int state_init(realq_bgd_state* st) {
         // W0 = W0hi + W0lo (in the D buffers for now), Xhat - X = Dxh + Dxl (bf16 pairs, exact
         // difference in float32 first): B = W0 Dxh^T (both halves of W0) + W0hi Dxl^T.
         RQ_HIP(ctx, realq::split_diff_f32(st->W0, n, nullptr, 0, st->Dhi, st->Dlo, ldn, m, n, s));
-        const int64_t tcx = std::max<int64_t>(8, std::min<int64_t>(T, ((int64_t)(256ll << 20) / (2 * ldn) / 8) * 8));
+        const int64_t tcx = std::max<int64_t>(8, std::min(at.count, ((int64_t)(256ll << 20) / (2 * ldn) / 8) * 8));
         void *xh, *xl;
         if ((rc = get_ws(ctx, "i_xh", (size_t)tcx * ldn * 2, &xh))) return rc;
         if ((rc = get_ws(ctx, "i_xl", (size_t)tcx * ldn * 2, &xl))) return rc;
-        if ((rc = each_range(st, [&](int64_t r0, int64_t len, int64_t pos) -> int {
-                 for (int64_t t0 = 0; t0 < len; t0 += tcx) {
-                     const int64_t cur = std::min(tcx, len - t0);
-                     RQ_HIP(ctx, realq::split_diff_bf16(st->Xhat + (r0 + t0) * n, st->X + (r0 + t0) * n, (uint16_t*)xh,
-                                                        (uint16_t*)xl, ldn, cur, n, s));
-                     realq::GemmArgs g{st->Dhi, st->Dlo, ldn, (const uint16_t*)xh, ldn, m, cur, n, 1};
-                     RQ_HIP(ctx, realq::gemm_store_f32(g, st->B + pos + t0, Tp, 0, 1.f, s));
-                     realq::GemmArgs g2{st->Dhi, nullptr, ldn, (const uint16_t*)xl, ldn, m, cur, n, 1};
-                     RQ_HIP(ctx, realq::gemm_acc_f32(g2, st->B + pos + t0, Tp, 1.f, s));
-                 }
-                 return REALQ_OK;
-             })))
-            return rc;
+        for (int64_t p0 = 0; p0 < at.count; p0 += tcx) {
+            const int64_t cur = std::min(tcx, at.count - p0);
+            RQ_HIP(ctx, realq::split_diff_bf16(st->Xhat, st->X, (uint16_t*)xh, (uint16_t*)xl, ldn, cur, n, at, p0, s));
+            realq::GemmArgs g{st->Dhi, st->Dlo, ldn, (const uint16_t*)xh, ldn, m, cur, n, 1};
+            RQ_HIP(ctx, realq::gemm_store_f32(g, st->B + p0, Tp, 0, 1.f, s));
+            realq::GemmArgs g2{st->Dhi, nullptr, ldn, (const uint16_t*)xl, ldn, m, cur, n, 1};
+            RQ_HIP(ctx, realq::gemm_acc_f32(g2, st->B + p0, Tp, 1.f, s));
+        }
     }
     RQ_HIP(ctx, realq::fill_u16(st->Dhi, 0, m * ldn, s));
     RQ_HIP(ctx, realq::fill_u16(st->Dlo, 0, m * ldn, s));
@@ -923,14 +886,9 @@ static int lock_block(realq_ctx* ctx, realq_bgd_state* st, int64_t c0, int64_t b
     st->inc_c1 = -1;  // the residual base moves: the next step starts a block
     st->inc_ready = false;
     if (!st->gram) {
-        const int64_t ldn = st->ldn, ldx = st->ldx;
+        realq::GemmArgs g{st->Dhi + c0, st->Dlo + c0, st->ldn, st->Xg + c0, st->ldx, st->m, st->at.count, bs, 1};
         Timed tm(ctx, "lock");
-        const int rc = each_range(st, [&](int64_t t0, int64_t len, int64_t pos) -> int {
-            realq::GemmArgs g{st->Dhi + c0, st->Dlo + c0, ldn, st->Xg + t0 * ldx + c0, ldx, st->m, len, bs, 1};
-            RQ_HIP(ctx, realq::gemm_acc_f32(g, st->B + pos, st->Tp, 1.f, ctx->stream));
-            return REALQ_OK;
-        });
-        if (rc) return rc;
+        RQ_HIP(ctx, realq::gemm_acc_f32(g, st->B, st->Tp, 1.f, ctx->stream));
     }
     st->locked = c0 + bs;
     return REALQ_OK;
@@ -1018,11 +976,11 @@ int realq_bgd_step(realq_ctx* ctx, realq_bgd_state* st, double* W, int64_t c1, f
         for (int64_t ch = 0; ch < nchunks; ++ch) {
             const int64_t t0 = pl.chunks[ch].t0, cur = pl.chunks[ch].len;
             double* const pch = pbase + pl.chunks[ch].parts_off;
-            const int64_t pos = chunk_pos(st, t0);
-            const float* sc = chunk_s(st, t0);
-            realq::GemmArgs g{st->Dhi + c1, st->Dlo + c1, ldn, st->Xg + t0 * ldx + c1, ldx, m, cur, nJ, 1};
+            const int64_t pos = realq::plan::place_of(st->at, t0);
+            const float* sc = st->sg ? st->sg + pos : nullptr;
+            realq::GemmArgs g{st->Dhi + c1, st->Dlo + c1, ldn, st->Xg + pos * ldx + c1, ldx, m, cur, nJ, 1};
             if (inc_step) {
-                realq::GemmArgs gi{st->Dinc + c1, nullptr, ldn, st->Xg + t0 * ldx + c1, ldx, m, cur, nJ, 1};
+                realq::GemmArgs gi{st->Dinc + c1, nullptr, ldn, st->Xg + pos * ldx + c1, ldx, m, cur, nJ, 1};
                 Timed tm(ctx, "resid_inc");
                 RQ_HIP(ctx, realq::gemm_resid_inc(gi, sc, st->Rhi, q_ld(cur), pch, s));
             } else if (!clip) {
@@ -1164,19 +1122,11 @@ int realq_bgd_loss(realq_ctx* ctx, realq_bgd_state* st, const double* W, double*
         return gram_loss(ctx, st, W, loss_out);
     }
     // R = B + (W - W0)[:, J] Xhat[:, J]^T with J the columns not yet folded into B.
-    const int64_t m = st->m, T = st->T, Tc = st->Tc, n = st->n, c1 = st->locked, nJ = n - c1, ldn = st->ldn, ldx = st->ldx;
+    // Places without a token hold zero inputs and a zero base: R is zero there.
+    const int64_t m = st->m, T = st->T, n = st->n, c1 = st->locked, nJ = n - c1, ldn = st->ldn, ldx = st->ldx;
     int64_t nparts = 0;
-    std::vector<realq::plan::Chunk> chunks;
-    // all tokens in chunks; with chunked positions no chunk crosses a batch
-    for (int64_t b0 = 0, Tl = st->chunked ? st->Tb : T; b0 < T; b0 += Tl) {
-        int64_t np = 0;
-        for (realq::plan::Chunk c : realq::plan::plan_loss(m, std::min(Tl, T - b0), Tc, &np)) {
-            c.t0 += b0;
-            c.parts_off += nparts;
-            chunks.push_back(c);
-        }
-        nparts += np;
-    }
+    const std::vector<realq::plan::Chunk> chunks =
+        realq::plan::plan_loss(m, st->at.count, st->at.apart ? st->at.chunk : st->Tc, &nparts);
     void* parts;
     int rc;
     if ((rc = get_ws(ctx, "b_parts", (size_t)nparts * 8, &parts))) return rc;
@@ -1184,7 +1134,7 @@ int realq_bgd_loss(realq_ctx* ctx, realq_bgd_state* st, const double* W, double*
                                                   ctx->stream));
     for (const auto& c : chunks) {
         realq::GemmArgs g{st->Dhi + c1, st->Dlo + c1, ldn, st->Xg + c.t0 * ldx + c1, ldx, m, c.len, nJ, 1};
-        RQ_HIP(ctx, realq::gemm_loss(g, st->B + chunk_pos(st, c.t0), st->Tp, chunk_s(st, c.t0),
+        RQ_HIP(ctx, realq::gemm_loss(g, st->B + c.t0, st->Tp, st->sg ? st->sg + c.t0 : nullptr,
                                      (double*)parts + c.parts_off, ctx->stream));
     }
     RQ_HIP(ctx, realq::reduce_partials((const double*)parts, nparts, 0.5 / (double)T, loss_out, ctx->stream));

@@ -305,23 +305,43 @@ hipError_t split_f64(const double* in, uint16_t* hi, uint16_t* lo, int64_t ldo, 
 }
 
 // Rows of `cols` bf16 values copied to stride ldo: activations whose rows are not a multiple of 16
-// bytes, laid out once for the GEMMs' direct-to-LDS loads.  A block takes every gridDim.x-th row.
-__global__ __launch_bounds__(256) void copy_rows_kernel(const uint16_t* __restrict__ in, int64_t ldi,
-                                                        uint16_t* __restrict__ out, int64_t ldo, int64_t rows,
-                                                        int64_t cols) {
-    for (int64_t r = blockIdx.x; r < rows; r += gridDim.x) {
-        const uint16_t* p = in + r * ldi;
+// bytes, or whose tokens have places of their own, laid out once for the GEMMs' direct-to-LDS loads.
+// A block takes every gridDim.x-th row.
+__global__ __launch_bounds__(256) void place_rows_kernel(const uint16_t* __restrict__ in, int64_t ldi,
+                                                         uint16_t* __restrict__ out, int64_t ldo, int64_t cols,
+                                                         plan::Places L) {
+    for (int64_t r = blockIdx.x; r < L.count; r += gridDim.x) {
+        const int64_t t = plan::token_at(L, r);
+        const uint16_t* p = in + t * ldi;
         uint16_t* q = out + r * ldo;
-        for (int64_t c = threadIdx.x; c < cols; c += 256) q[c] = p[c];
+        for (int64_t c = threadIdx.x; c < cols; c += 256) q[c] = t >= 0 ? p[c] : 0;
     }
+}
+
+hipError_t place_rows_u16(const uint16_t* in, int64_t ldi, uint16_t* out, int64_t ldo, int64_t cols,
+                          const plan::Places& L, hipStream_t st) {
+    if (L.count <= 0 || cols <= 0) return hipSuccess;
+    // a launch holds less than 2^32 threads: 2^20 blocks at most, whatever the token count
+    const int64_t grid = std::min<int64_t>(L.count, 1 << 20);
+    hipLaunchKernelGGL(place_rows_kernel, dim3((unsigned)grid), dim3(256), 0, st, in, ldi, out, ldo, cols, L);
+    return hipGetLastError();
 }
 
 hipError_t copy_rows_u16(const uint16_t* in, int64_t ldi, uint16_t* out, int64_t ldo, int64_t rows, int64_t cols,
                          hipStream_t st) {
-    if (rows <= 0 || cols <= 0) return hipSuccess;
-    // a launch holds less than 2^32 threads: 2^20 blocks at most, whatever the token count
-    const int64_t grid = std::min<int64_t>(rows, 1 << 20);
-    hipLaunchKernelGGL(copy_rows_kernel, dim3((unsigned)grid), dim3(256), 0, st, in, ldi, out, ldo, rows, cols);
+    return place_rows_u16(in, ldi, out, ldo, cols, plan::place_tokens(rows, rows, rows), st);
+}
+
+__global__ void place_f32_kernel(const float* __restrict__ in, float* __restrict__ out, plan::Places L) {
+    for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < L.count; p += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t t = plan::token_at(L, p);
+        out[p] = t >= 0 ? in[t] : 0.f;
+    }
+}
+
+hipError_t place_f32(const float* in, float* out, const plan::Places& L, hipStream_t st) {
+    if (L.count <= 0) return hipSuccess;
+    hipLaunchKernelGGL(place_f32_kernel, dim3(grid_for(L.count, 1)), dim3(TB), 0, st, in, out, L);
     return hipGetLastError();
 }
 
@@ -654,10 +674,11 @@ hipError_t blend_split(const float* M, const float* P, float alpha, int64_t m, u
 
 __global__ void split_diff_bf16_kernel(const uint16_t* __restrict__ a, const uint16_t* __restrict__ b,
                                        uint16_t* __restrict__ hi, uint16_t* __restrict__ lo, int64_t cols, int64_t ldo,
-                                       int64_t total) {
+                                       int64_t total, plan::Places L, int64_t p0) {
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-        const float v = bf2f(a[e]) - bf2f(b[e]);  // exact in float32 for bf16 inputs of similar magnitude
-        const int64_t o = ldo == cols ? e : (e / cols) * ldo + e % cols;
+        const int64_t i = e / cols, j = e % cols, t = plan::token_at(L, p0 + i), o = i * ldo + j;
+        // exact in float32 for bf16 inputs of similar magnitude
+        const float v = t >= 0 ? bf2f(a[t * cols + j]) - bf2f(b[t * cols + j]) : 0.f;
         uint16_t h, l;
         split_bf16(v, h, l);
         hi[o] = h;
@@ -666,11 +687,11 @@ __global__ void split_diff_bf16_kernel(const uint16_t* __restrict__ a, const uin
 }
 
 hipError_t split_diff_bf16(const uint16_t* a, const uint16_t* b, uint16_t* hi, uint16_t* lo, int64_t ldo, int64_t rows,
-                           int64_t cols, hipStream_t st) {
+                           int64_t cols, const plan::Places& L, int64_t p0, hipStream_t st) {
     const int64_t total = rows * cols;
     if (total <= 0) return hipSuccess;
     hipLaunchKernelGGL(split_diff_bf16_kernel, dim3(grid_for(total, 4)), dim3(TB), 0, st, a, b, hi, lo, cols, ldo,
-                       total);
+                       total, L, p0);
     return hipGetLastError();
 }
 

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "plan.h"
+
 namespace realq {
 
 // ---------------------------------------------------------------- bf16 MFMA NT GEMM
@@ -114,9 +116,15 @@ int64_t dot_f64_partials();
 // out[i] = double(in[i]) / float(in[i])
 hipError_t widen_f32(const float* in, double* out, int64_t count, hipStream_t st);
 hipError_t narrow_f64(const double* in, float* out, int64_t count, hipStream_t st);
-// hi/lo[i*ldo + j] = split(bf16(a[i*cols + j]) - bf16(b[i*cols + j]))
+// hi/lo[i*ldo + j] = split(bf16(a[t*cols + j]) - bf16(b[t*cols + j])) with t the token at place p0 + i
+// (zeros where there is none)
 hipError_t split_diff_bf16(const uint16_t* a, const uint16_t* b, uint16_t* hi, uint16_t* lo, int64_t ldo, int64_t rows,
-                           int64_t cols, hipStream_t st);
+                           int64_t cols, const plan::Places& L, int64_t p0, hipStream_t st);
+// out[p*ldo + j] = in[t*ldi + j], j < cols, t the token at place p (zeros where there is none)
+hipError_t place_rows_u16(const uint16_t* in, int64_t ldi, uint16_t* out, int64_t ldo, int64_t cols,
+                          const plan::Places& L, hipStream_t st);
+// out[p] = in[t] (float32), likewise
+hipError_t place_f32(const float* in, float* out, const plan::Places& L, hipStream_t st);
 // hi/lo[i*ldo + k] = split(alpha (M ? M : I)[i][k] + (1 - alpha) (P ? P[i][k] : 0)), m x m float32 inputs
 hipError_t blend_split(const float* M, const float* P, float alpha, int64_t m, uint16_t* hi, uint16_t* lo, int64_t ldo,
                        hipStream_t st);

@@ -55,6 +55,22 @@ int64_t operand_stride(int64_t n) {
     return 64 * (lines | 1);
 }
 
+Places place_tokens(int64_t T, int64_t Tb, int64_t Tc, bool may_part) {
+    Places L;
+    L.T = T;
+    L.Tb = L.batch = Tb;
+    L.Tc = L.chunk = Tc;
+    L.count = T;
+    if (!may_part || ((Tc >= T || Tc % 8 == 0) && (Tb >= T || Tb % 8 == 0))) return L;
+    auto round8 = [](int64_t v) { return (v + 7) / 8 * 8; };
+    Places P = L;
+    P.apart = true;
+    P.chunk = round8(Tc);
+    P.batch = Tb / Tc * P.chunk + round8(Tb % Tc);
+    P.count = place_of(P, T - 1) + 1;
+    return P.count <= T + T / 16 ? P : L;
+}
+
 int64_t choose_acc_splits(int64_t tiles, int64_t K, int passes, int cus, int64_t max_k) {
     if (cus < 1) cus = 1;
     const int64_t smin = max_k > 0 ? (K + max_k - 1) / max_k : 1;

@@ -71,6 +71,29 @@ def many_tokens(L):
     L.ok("realq_handoff", buf(1), None, buf(2), T, 133, 64, buf(3))
 
 
+def short_chunks(L):
+    """Batches and token chunks that are not multiples of 8: the state's arrays grow by a sixteenth at most
+    over the aligned case's (besides the inputs' copy, which that case has too), and its set-up and
+    lock take as many launches as that case's."""
+    m, n, T = 1024, 4096, 262144
+    for clip in (0.0, 0.95):
+        for case in (dict(batch=9), dict(batch=100), dict(batch=1001), dict(batch=1), dict(tok_chunk=4),
+                     dict(tok_chunk=1003), dict(batch=65535, tok_chunk=33)):
+            got = []
+            for params in ({k: (v + 7) // 8 * 8 for k, v in case.items()}, case):
+                h0 = L.held()
+                L.fake.fake_reset()
+                st = L.state(m, n, T, loss_clip=clip, **params)
+                made = L.launches()
+                L.fake.fake_reset()
+                L.ok("realq_bgd_lock_block", st, 0, 128)
+                got.append((L.held() - h0, made, L.launches()))
+                L.c.realq_bgd_state_destroy(st)
+            (h_al, made_al, lock_al), (h, made, lock) = got
+            assert h <= 1.07 * h_al, (case, h, h_al)
+            assert made <= made_al + 1 and lock == lock_al == 1, (case, got)  # one more: the token weights
+
+
 if __name__ == "__main__":
     globals()[sys.argv[3]](Library(sys.argv[1], sys.argv[2]))
     print("passed")

@@ -2,6 +2,7 @@
 // AddressSanitizer and UndefinedBehaviorSanitizer by tests/test_host_plan.py.  It checks that the
 // split-K and loss-partial workspaces a Block-GD step allocates hold everything its launches write,
 // for every chunk of every step, including a short last mini-batch and a short last token chunk.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <random>
@@ -90,6 +91,49 @@ int main() {
             const int64_t se = effective_splits(K, s);
             for (int64_t k2 = 1; k2 <= K; k2 += 97) CHECK(effective_splits(k2, se) <= se);
         }
+    // operand rows: enough, whole 128-byte lines, an odd number of them, never shorter for more columns
+    for (int64_t n = 1; n <= 20000; n += n < 300 ? 1 : 61) {
+        const int64_t ld = operand_stride(n);
+        CHECK(ld >= n && ld % 64 == 0 && ld / 64 % 2 == 1 && ld < n + 128);
+        CHECK(operand_stride(n + 1) >= ld);
+    }
+    // Places: every token has one of its own, in order, that leads back to it; every chunk of a step
+    // is contiguous and, where tokens are apart, starts on a multiple of 8; the places without a
+    // token say so and are few.
+    {
+        int parted = 0;
+        auto check = [&](int64_t T, int64_t Tb, int64_t Tc) {
+            for (bool may : {true, false}) {
+                const Places L = place_tokens(T, Tb, Tc, may);
+                parted += L.apart;
+                CHECK(may || !L.apart);
+                CHECK(L.count >= T && L.count <= T + T / 16);
+                std::vector<int64_t> at((size_t)L.count, -1);
+                for (int64_t t = 0; t < T; ++t) at.at((size_t)place_of(L, t)) = t;
+                int64_t held = 0;
+                for (int64_t p = 0; p < L.count; ++p) {
+                    CHECK(token_at(L, p) == at[(size_t)p]);
+                    held += at[(size_t)p] >= 0;
+                }
+                CHECK(held == T);
+                const bool aligned = (Tb >= T || Tb % 8 == 0) && (Tc >= T || Tc % 8 == 0);
+                CHECK(!(aligned && L.apart));
+                for (int64_t t = 0; t < (T + Tb - 1) / Tb; ++t)
+                    for (const Chunk& c : plan_step(7, 5, T, Tb, Tc, t, 256, 0).chunks) {
+                        CHECK(place_of(L, c.t0 + c.len - 1) == place_of(L, c.t0) + c.len - 1);
+                        CHECK(!(L.apart || aligned) || place_of(L, c.t0) % 8 == 0);
+                    }
+            }
+        };
+        for (int64_t T : {1, 7, 8, 9, 1003, 4096, 4099})
+            for (int64_t Tb : {1, 8, 9, 100, 333, 336, 1001, 1002, 4099})
+                for (int64_t Tc : {1, 4, 8, 63, 96, 97, 100, 101, 500, 1001, 4099}) {
+                    const int64_t b = std::min(Tb, T);
+                    check(T, b, std::min(Tc, b));
+                }
+        CHECK(parted > 20);
+        CHECK(!place_tokens(262144, 9, 9).apart && place_tokens(262144, 100, 100).apart);
+    }
     // randomised shapes, batches, chunks and CU counts
     std::mt19937_64 rng(1234);
     auto pick = [&](int64_t lo, int64_t hi) { return lo + (int64_t)(rng() % (uint64_t)(hi - lo + 1)); };
