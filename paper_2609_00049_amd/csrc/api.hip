@@ -23,6 +23,21 @@ int set_error(realq_ctx* ctx, int code, const std::string& msg) {
     return code;
 }
 
+// Device memory for `slot` (NULL: none of the context's).  The slices of finished products are given
+// back before the memory is said to be out: nothing is kept in them between calls.
+static bool device_alloc(realq_ctx* ctx, const char* slot, size_t bytes, void** p) {
+    for (;;) {
+        if (hipMalloc(p, bytes) == hipSuccess && *p) return true;
+        (void)hipGetLastError();
+        *p = nullptr;
+        realq_ctx::Buf& slices = ctx->ws[kSliceSlot];
+        if (!slices.p || (slot && std::strcmp(slot, kSliceSlot) == 0)) return false;
+        if (hipStreamSynchronize(ctx->stream) != hipSuccess) return false;
+        (void)hipFree(slices.p);
+        slices = realq_ctx::Buf();
+    }
+}
+
 int get_ws(realq_ctx* ctx, const char* slot, size_t bytes, void** out) {
     auto& b = ctx->ws[slot];
     if (bytes == 0) bytes = 16;
@@ -35,11 +50,9 @@ int get_ws(realq_ctx* ctx, const char* slot, size_t bytes, void** out) {
             b.bytes = 0;
         }
         void* p = nullptr;
-        if (hipMalloc(&p, bytes) != hipSuccess || !p) {
-            (void)hipGetLastError();
+        if (!device_alloc(ctx, slot, bytes, &p))
             return set_error(ctx, REALQ_ERR_OOM,
                              std::string("device allocation of ") + std::to_string(bytes) + " bytes for " + slot);
-        }
         b.p = p;
         b.bytes = bytes;
     }
@@ -233,6 +246,22 @@ static hipError_t acc_direct(const realq::GemmArgs& g, float* C, int64_t ldc, bo
     return store ? realq::gemm_store_f32(g, C, ldc, 0, 1.f, st) : realq::gemm_acc_f32(g, C, ldc, 1.f, st);
 }
 
+// Most bytes the slices of sum_products hold; larger products are formed in panels of rows.
+static constexpr int64_t kSliceBytes = (int64_t)3 << 30;
+
+// Room for product slices: `want` bytes, or what the context holds when that is at least 7/8 of it
+// (fewer tokens can take up to 1.13 times the slices, and a call takes no new memory after a larger
+// one), or as much as there is, down to `least`; 0 when there is not that.
+static int64_t slice_room(realq_ctx* ctx, int64_t want, int64_t least, void** S, int* rc) {
+    const int64_t held = (int64_t)ctx->ws[realq::kSliceSlot].bytes;
+    if (held >= least && held >= want / 8 * 7) want = held;
+    for (;; want = std::max(least, want / 2)) {
+        *rc = get_ws(ctx, realq::kSliceSlot, (size_t)want, S);
+        if (*rc == REALQ_OK) return want;
+        if (*rc != REALQ_ERR_OOM || want == least) return 0;
+    }
+}
+
 // C (+)= the sum of count products A_p B_p^T (M x N, g[p].K wide each, Alo optional) in float64:
 // each product in float32 slices over ranges of K (split-K fills the chip whatever M and N are; a
 // slice's float32 sums are shorter), the slices summed into C in float64 in a fixed order.
@@ -241,38 +270,67 @@ static hipError_t acc_direct(const realq::GemmArgs& g, float* C, int64_t ldc, bo
 // max_k > 0 bounds the terms of a float32 sum of the hi/lo products (with weights of several orders
 // of magnitude a few tokens carry H, and what later tokens' additions to them round away shows in
 // the last codes of a sweep: 1024 tokens a sum leave 2e-7 of H where 8192 left 6e-7).
+// The slices are held for one panel of rows at a time; how many panels changes no sum.
 template <class Out>
 static int sum_products(realq_ctx* ctx, realq::GemmArgs* g, int count, int always, const int* flag, bool symmetric,
                         int64_t max_k, bool accumulate, Out* C, int64_t ldc) {
     const int64_t M = g[0].M, N = g[0].N;
     const int64_t nt = (M + realq::plan::kLargeBM - 1) / realq::plan::kLargeBM;
     const int64_t tiles = symmetric ? nt * (nt + 1) / 2 : realq::plan::tiles(M, N, true);
+    hipStream_t s = ctx->stream;
     int64_t total = 0, first = 0;
     for (int p = 0; p < count; ++p) {
-        g[p].tri = symmetric;
         g[p].run_if = p >= always ? flag : nullptr;
         g[p].splits = realq::plan::choose_acc_splits(tiles, g[p].K, g[p].Alo ? 2 : 1, ctx->cus, g[p].Alo ? max_k : 0);
         total += realq::gemm_effective_splits(g[p].K, g[p].splits);
         if (p + 1 == always) first = total;
     }
+    // one row of tiles over all columns; never more than the whole
+    const int64_t least = realq::plan::panel_bytes(N, false, total, 0, std::min(M, realq::plan::kLargeBM));
+    const int64_t all = realq::plan::panel_bytes(N, symmetric, total, 0, M);
     void* S;
-    const int rc = get_ws(ctx, "h_slices", (size_t)total * M * N * 4, &S);
-    if (rc == REALQ_ERR_OOM) {  // no room for the slices: straight into C, both triangles
+    int rc;
+    const int64_t room = slice_room(ctx, std::max(least, std::min(all, kSliceBytes)), least, &S, &rc);
+    if (rc == REALQ_ERR_OOM) {  // not even one row of tiles: straight into C, both triangles
         for (int p = 0; p < count; ++p) {
-            g[p].tri = 0;
-            g[p].splits = 1;
-            RQ_HIP(ctx, acc_direct(g[p], C, ldc, p == 0 && !accumulate, ctx->stream));
+            const int64_t step = g[p].Alo && max_k > 0 ? max_k : g[p].K;
+            for (int64_t k0 = 0; k0 < g[p].K; k0 += step) {
+                realq::GemmArgs q = g[p];
+                q.Ahi += k0;
+                if (q.Alo) q.Alo += k0;
+                q.B += k0;
+                q.K = std::min(step, g[p].K - k0);
+                q.splits = 1;
+                RQ_HIP(ctx, acc_direct(q, C, ldc, p == 0 && k0 == 0 && !accumulate, s));
+            }
         }
         return REALQ_OK;
     }
     if (rc) return rc;
-    float* out = (float*)S;
-    for (int p = 0; p < count; ++p) {
-        RQ_HIP(ctx, realq::gemm_grad(g[p], out, N, M * N, ctx->stream));
-        out += realq::gemm_effective_splits(g[p].K, g[p].splits) * M * N;
+    const int64_t budget = realq::plan::even_budget(M, N, symmetric, total, room);
+    for (int64_t r0 = 0; r0 < M;) {
+        const int64_t rows = realq::plan::panel_rows(M, N, symmetric, total, r0, budget);
+        const int64_t cols = symmetric ? r0 + rows : N;
+        float* out = (float*)S;
+        for (int p = 0; p < count; ++p) {
+            realq::GemmArgs q = g[p];
+            q.Ahi += r0 * q.lda;
+            if (q.Alo) q.Alo += r0 * q.lda;
+            q.M = rows;
+            q.N = symmetric ? r0 : N;  // symmetric: the columns left of the panel's own square, if any
+            RQ_HIP(ctx, realq::gemm_grad(q, out, cols, rows * cols, s));
+            if (symmetric) {
+                q.B += r0 * q.ldb;
+                q.N = rows;
+                q.tri = 1;
+                RQ_HIP(ctx, realq::gemm_grad(q, out + r0, cols, rows * cols, s));
+            }
+            out += realq::gemm_effective_splits(q.K, q.splits) * rows * cols;
+        }
+        RQ_HIP(ctx, realq::add_slices((const float*)S, first, total, flag, r0, r0 + rows, N, symmetric, accumulate, C,
+                                      ldc, s));
+        r0 += rows;
     }
-    RQ_HIP(ctx, realq::add_slices((const float*)S, first, total, flag, M, N, symmetric, accumulate, C, ldc,
-                                  ctx->stream));
     return REALQ_OK;
 }
 
@@ -425,10 +483,8 @@ static int state_alloc(realq_bgd_state* st, void** p, size_t bytes, const char* 
     realq_ctx* ctx = st->ctx;
     if (!st->owns) return get_ws(ctx, slot, bytes, p);
     *p = nullptr;
-    if (hipMalloc(p, bytes ? bytes : 16) != hipSuccess || !*p) {
-        (void)hipGetLastError();
+    if (!realq::device_alloc(ctx, nullptr, bytes ? bytes : 16, p))
         return set_error(ctx, REALQ_ERR_OOM, std::string("device allocation of ") + std::to_string(bytes) + " bytes");
-    }
     st->allocations.push_back(*p);
     return REALQ_OK;
 }

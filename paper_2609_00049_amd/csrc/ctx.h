@@ -37,6 +37,9 @@ struct realq_ctx {
 
 namespace realq {
 
+// Slot of the float32 slices of products summed in float64 (api.hip), whose buffer other
+// allocations may take back.
+constexpr const char* kSliceSlot = "h_slices";
 // Device buffer of at least `bytes` for `slot` (grown by synchronising the stream and
 // reallocating; contents are not kept across growth).
 int get_ws(realq_ctx* ctx, const char* slot, size_t bytes, void** out);

@@ -148,36 +148,37 @@ hipError_t transpose_scale_split(const uint16_t* in, int64_t ldi, const float* s
 }
 
 // ---------------------------------------------------------------- sum of float32 product slices
-// C[i][j] (+)= sum_z S[z][i][j] in float64, z in order; SYM: only the slices' lower tiles exist (a
-// symmetric product), and the values below the diagonal go to both sides of it, so the sum
-// stays exactly symmetric.  One 32 x 32 tile per block (lower tiles only with SYM); bound by HBM.
+// C[i][j] (+)= sum_z S[z][i - r0][j] in float64, z in order, for the rows [r0, r1); SYM: only the slices'
+// lower tiles exist (a symmetric product; ncols = r1), and the values below the diagonal go to both
+// sides of it, so the sum stays exactly symmetric.  One 32 x 32 tile per block (lower tiles only with
+// SYM); bound by HBM.
 template <bool SYM, class Out>
 __global__ __launch_bounds__(256) void add_slices_kernel(const float* __restrict__ S, int64_t always, int64_t slices,
-                                                         const int* __restrict__ flag, int64_t M, int64_t N,
-                                                         int accumulate, Out* __restrict__ C, int64_t ldc,
-                                                         int64_t tiles) {
+                                                         const int* __restrict__ flag, int64_t r0, int64_t r1,
+                                                         int64_t ncols, int accumulate, Out* __restrict__ C,
+                                                         int64_t ldc, int64_t tiles) {
     __shared__ double tile[32][33];
     if (flag && *flag == 0) slices = always;
     int64_t ti, tj;
     if constexpr (SYM) {
-        const int64_t b = blockIdx.x;
+        const int64_t t0 = r0 / 32, b = t0 * (t0 + 1) / 2 + blockIdx.x;
         ti = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
         while ((ti + 1) * (ti + 2) / 2 <= b) ++ti;
         while (ti * (ti + 1) / 2 > b) --ti;
         tj = b - ti * (ti + 1) / 2;
     } else {
-        ti = blockIdx.x / tiles;
+        ti = r0 / 32 + blockIdx.x / tiles;
         tj = blockIdx.x % tiles;
     }
     const int rr = threadIdx.x >> 3, cc = (threadIdx.x & 7) * 4;
-    const int64_t i = ti * 32 + rr, j = tj * 32 + cc;
+    const int64_t i = ti * 32 + rr, j = tj * 32 + cc, stride = (r1 - r0) * ncols;
     double v[4] = {0.0, 0.0, 0.0, 0.0};
-    if (i < M) {
-        const float* p = S + i * N + j;
-        if (N % 4 == 0 && j < N) {
+    if (i < r1) {
+        const float* p = S + (i - r0) * ncols + j;
+        if (ncols % 4 == 0 && j < ncols) {
 #pragma unroll 4
             for (int64_t z = 0; z < slices; ++z) {
-                const f32x4 x = *reinterpret_cast<const f32x4*>(p + z * M * N);
+                const f32x4 x = *reinterpret_cast<const f32x4*>(p + z * stride);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] += (double)x[e];
             }
@@ -185,7 +186,7 @@ __global__ __launch_bounds__(256) void add_slices_kernel(const float* __restrict
             for (int64_t z = 0; z < slices; ++z)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (j + e < N) v[e] += (double)p[z * M * N + e];
+                    if (j + e < ncols) v[e] += (double)p[z * stride + e];
         }
     }
     auto add = [&](int64_t r, int64_t c, double x) {
@@ -205,34 +206,34 @@ __global__ __launch_bounds__(256) void add_slices_kernel(const float* __restrict
             const int64_t mi = tj * 32 + rr, mj = ti * 32 + cc;
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (mi < N && mj + e < M) add(mi, mj + e, tile[cc + e][rr]);
+                if (mi < ncols && mj + e < r1) add(mi, mj + e, tile[cc + e][rr]);
         }
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
-        if (i < M && j + e < N) add(i, j + e, v[e]);
+        if (i < r1 && j + e < ncols) add(i, j + e, v[e]);
 }
 
 template <class Out>
-static hipError_t add_slices_t(const float* S, int64_t always, int64_t slices, const int* flag, int64_t M, int64_t N,
-                               bool symmetric, bool accumulate, Out* C, int64_t ldc, hipStream_t st) {
-    if (M <= 0 || N <= 0) return hipSuccess;
-    const int64_t tm = (M + 31) / 32, tn = (N + 31) / 32;
+static hipError_t add_slices_t(const float* S, int64_t always, int64_t slices, const int* flag, int64_t r0, int64_t r1,
+                               int64_t N, bool symmetric, bool accumulate, Out* C, int64_t ldc, hipStream_t st) {
+    if (r1 <= r0 || N <= 0) return hipSuccess;
+    const int64_t t0 = r0 / 32, t1 = (r1 + 31) / 32, tn = (N + 31) / 32;
     if (symmetric)
-        hipLaunchKernelGGL((add_slices_kernel<true, Out>), dim3((unsigned)(tm * (tm + 1) / 2)), dim3(256), 0, st, S,
-                           always, slices, flag, M, N, (int)accumulate, C, ldc, tn);
+        hipLaunchKernelGGL((add_slices_kernel<true, Out>), dim3((unsigned)((t1 * (t1 + 1) - t0 * (t0 + 1)) / 2)),
+                           dim3(256), 0, st, S, always, slices, flag, r0, r1, r1, (int)accumulate, C, ldc, tn);
     else
-        hipLaunchKernelGGL((add_slices_kernel<false, Out>), dim3((unsigned)(tm * tn)), dim3(256), 0, st, S, always,
-                           slices, flag, M, N, (int)accumulate, C, ldc, tn);
+        hipLaunchKernelGGL((add_slices_kernel<false, Out>), dim3((unsigned)((t1 - t0) * tn)), dim3(256), 0, st, S,
+                           always, slices, flag, r0, r1, N, (int)accumulate, C, ldc, tn);
     return hipGetLastError();
 }
-hipError_t add_slices(const float* S, int64_t always, int64_t slices, const int* flag, int64_t M, int64_t N,
-                      bool symmetric, bool accumulate, double* C, int64_t ldc, hipStream_t st) {
-    return add_slices_t(S, always, slices, flag, M, N, symmetric, accumulate, C, ldc, st);
+hipError_t add_slices(const float* S, int64_t always, int64_t slices, const int* flag, int64_t r0, int64_t r1,
+                      int64_t N, bool symmetric, bool accumulate, double* C, int64_t ldc, hipStream_t st) {
+    return add_slices_t(S, always, slices, flag, r0, r1, N, symmetric, accumulate, C, ldc, st);
 }
-hipError_t add_slices(const float* S, int64_t always, int64_t slices, const int* flag, int64_t M, int64_t N,
-                      bool symmetric, bool accumulate, float* C, int64_t ldc, hipStream_t st) {
-    return add_slices_t(S, always, slices, flag, M, N, symmetric, accumulate, C, ldc, st);
+hipError_t add_slices(const float* S, int64_t always, int64_t slices, const int* flag, int64_t r0, int64_t r1,
+                      int64_t N, bool symmetric, bool accumulate, float* C, int64_t ldc, hipStream_t st) {
+    return add_slices_t(S, always, slices, flag, r0, r1, N, symmetric, accumulate, C, ldc, st);
 }
 
 // Input perturbation of one token chunk, transposed: delta = Xhat - X (rows = tokens), and

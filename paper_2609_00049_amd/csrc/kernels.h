@@ -64,14 +64,14 @@ hipError_t transpose_u16(const uint16_t* in, int64_t ldi, uint16_t* out, int64_t
 // receives the unweighted transpose from the same pass.
 hipError_t transpose_scale_split(const uint16_t* in, int64_t ldi, const float* s, uint16_t* plain, uint16_t* hi,
                                  uint16_t* lo, uint16_t* lo2, int64_t ldo, int64_t rows, int64_t cols, hipStream_t st);
-// C[i*ldc + j] = (accumulate ? C : 0) + sum_z S[z][i][j] (M x N slices, float64 sum, z in order);
-// symmetric (M == N): S holds the tiles on and below the diagonal only and both triangles of C
-// receive them.  flag (device, may be NULL): the slices from `always` on are only read when it is
-// nonzero.
-hipError_t add_slices(const float* S, int64_t always, int64_t slices, const int* flag, int64_t M, int64_t N,
-                      bool symmetric, bool accumulate, double* C, int64_t ldc, hipStream_t st);
-hipError_t add_slices(const float* S, int64_t always, int64_t slices, const int* flag, int64_t M, int64_t N,
-                      bool symmetric, bool accumulate, float* C, int64_t ldc, hipStream_t st);
+// C[i*ldc + j] = (accumulate ? C : 0) + sum_z S[z][i - r0][j] for the rows r0 <= i < r1 of an
+// ... x N matrix (r0 a multiple of 32; float64 sum, z in order); symmetric: C is square, S holds the
+// tiles on and below the diagonal only (its slices have r1 columns) and both triangles of C receive
+// them.  flag (device, may be NULL): the slices from `always` on are only read when it is nonzero.
+hipError_t add_slices(const float* S, int64_t always, int64_t slices, const int* flag, int64_t r0, int64_t r1,
+                      int64_t N, bool symmetric, bool accumulate, double* C, int64_t ldc, hipStream_t st);
+hipError_t add_slices(const float* S, int64_t always, int64_t slices, const int* flag, int64_t r0, int64_t r1,
+                      int64_t N, bool symmetric, bool accumulate, float* C, int64_t ldc, hipStream_t st);
 // hi/lo[i*ld + j] = split(A[i*lda + j] - (Bm ? Bm[i*ldb + j] : 0)) for j < cols (float32 inputs)
 hipError_t split_diff_f32(const float* A, int64_t lda, const float* Bm, int64_t ldb, uint16_t* hi, uint16_t* lo,
                           int64_t ld, int64_t rows, int64_t cols, hipStream_t st);

@@ -55,6 +55,34 @@ int64_t operand_stride(int64_t n) {
     return 64 * (lines | 1);
 }
 
+int64_t panel_rows(int64_t M, int64_t N, bool symmetric, int64_t slices, int64_t r0, int64_t budget) {
+    int64_t lo = 1, hi = (M - r0 + kLargeBM - 1) / kLargeBM;  // tiles
+    if (panel_bytes(N, symmetric, slices, r0, M - r0) <= budget) return M - r0;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi + 1) / 2;
+        if (panel_bytes(N, symmetric, slices, r0, std::min(mid * kLargeBM, M - r0)) <= budget) lo = mid;
+        else hi = mid - 1;
+    }
+    return std::min(lo * kLargeBM, M - r0);
+}
+
+int64_t even_budget(int64_t M, int64_t N, bool symmetric, int64_t slices, int64_t budget) {
+    auto panels = [&](int64_t b) {
+        int64_t k = 0;
+        for (int64_t r0 = 0; r0 < M; ++k) r0 += panel_rows(M, N, symmetric, slices, r0, b);
+        return k;
+    };
+    const int64_t k = panels(budget);
+    if (k == 1) return budget;
+    int64_t lo = 0, hi = budget;
+    while (hi - lo > budget / 100) {
+        const int64_t mid = lo + (hi - lo) / 2;
+        if (panels(mid) <= k) hi = mid;
+        else lo = mid;
+    }
+    return hi;
+}
+
 Places place_tokens(int64_t T, int64_t Tb, int64_t Tc, bool may_part) {
     Places L;
     L.T = T;

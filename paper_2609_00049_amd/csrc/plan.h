@@ -41,6 +41,19 @@ int64_t operand_stride(int64_t n);
 // max_k > 0, at most max_k.
 int64_t choose_acc_splits(int64_t tiles, int64_t K, int passes, int cus, int64_t max_k);
 
+// Rows of the panel from row r0 of an M x N product held as `slices` float32 slices: the most, in whole
+// 256-row tiles, whose slices take at most `budget` bytes, and one tile at least.  A symmetric
+// product's panel holds the columns up to its last row.
+int64_t panel_rows(int64_t M, int64_t N, bool symmetric, int64_t slices, int64_t r0, int64_t budget);
+// The least budget that needs no more panels than `budget` does (within 1%): panels of about equal
+// bytes, since the launches of a last panel of a few rows of tiles leave most of the chip idle
+// (4096 weighted columns over 65536 tokens: 5.6 ms with a last panel of 256 rows, 4.6 ms in one).
+int64_t even_budget(int64_t M, int64_t N, bool symmetric, int64_t slices, int64_t budget);
+// Bytes of the slices of `rows` rows from r0.
+constexpr int64_t panel_bytes(int64_t N, bool symmetric, int64_t slices, int64_t r0, int64_t rows) {
+    return 4 * slices * rows * (symmetric ? r0 + rows : N);
+}
+
 // Places of the T tokens in the token-minor arrays of a Block-GD state (residual base, transposed
 // inputs, token weights).  A chunk's operand rows must start on 16 bytes, 8 tokens: when the chunks of Tc
 // tokens of the batches of Tb do not (`apart`), each chunk starts on the next multiple of 8

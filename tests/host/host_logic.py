@@ -94,6 +94,31 @@ def short_chunks(L):
             assert made <= made_al + 1 and lock == lock_al == 1, (case, got)  # one more: the token weights
 
 
+def slice_memory(L):
+    """Products summed in float64 hold at most 3 GiB of slices whatever their size, give them back
+    when other memory runs out, and take no new memory after a call with more tokens."""
+    staging = 4 * (257 << 20)  # the four bf16 copies of a token chunk
+    for n, T in ((4096, 131072), (14336, 65536), (28672, 32768)):
+        h0 = L.held()
+        L.ok("realq_hessian_accum", buf(1), buf(2), T, n, buf(3))
+        assert L.held() - h0 <= staging + (3 << 30) + (1 << 26), (n, L.held() - h0)
+    full = L.held()
+    L.fake.fake_set_limit(full)  # nothing left: the state's arrays replace the slices
+    st = L.state(1024, 1024, 65536)
+    L.c.realq_bgd_state_destroy(st)
+    L.ok("realq_hessian_accum", buf(1), buf(2), 65536, 14336, buf(3))  # in what is left, or into H itself
+    L.fake.fake_set_limit(L.held())
+    L.ok("realq_hessian_accum", buf(1), buf(2), 65536, 14336, buf(3))
+    L.fake.fake_set_limit(-1)
+    for n in (256, 1024, 3000):
+        for s in (None, buf(2)):
+            L.ok("realq_hessian_accum", buf(1), s, 40000, n, buf(3))
+            L.fake.fake_reset()
+            for T in range(1, 40000, 211):
+                L.ok("realq_hessian_accum", buf(1), s, T, n, buf(3))
+            assert L.fake.fake_mallocs() == 0, (n, s)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[3]](Library(sys.argv[1], sys.argv[2]))
     print("passed")

@@ -97,6 +97,42 @@ int main() {
         CHECK(ld >= n && ld % 64 == 0 && ld / 64 % 2 == 1 && ld < n + 128);
         CHECK(operand_stride(n + 1) >= ld);
     }
+    // Slices of a float64-accumulated product: no float32 sum over more tokens than max_k, 256
+    // tokens a slice at least otherwise, and fewer tokens never take more than 8/7 of the slices
+    // that more tokens do (the room held after a larger call serves a smaller one).
+    for (int64_t nt : {1, 2, 3, 5, 10, 16, 56})
+        for (int64_t max_k : {0, 1024})
+            for (int passes : {1, 2}) {
+                int64_t most = 1;
+                for (int64_t K = 1; K <= 200000; K += K < 4096 ? 5 : K < 32768 ? 64 : 1000) {
+                    const int64_t q = choose_acc_splits(nt * (nt + 1) / 2, K, passes, 256, max_k);
+                    CHECK(q >= 1 && q == effective_splits(K, q));
+                    CHECK(max_k == 0 || k_per_split(K, q) <= max_k);
+                    CHECK(q == 1 || max_k > 0 || k_per_split(K, q) >= 256);
+                    CHECK(7 * most <= 8 * q);
+                    most = std::max(most, q);
+                }
+            }
+    // Panels of such a product: whole tile rows that cover it, within the budget or one tile row
+    for (int64_t M : {1, 255, 256, 257, 1000, 4097, 14336})
+        for (bool sym : {false, true})
+            for (int64_t slices : {1, 3, 34})
+                for (int64_t budget : {int64_t(1) << 10, int64_t(100) << 20, int64_t(2) << 30}) {
+                    const int64_t N = sym ? M : 1352, even = even_budget(M, N, sym, slices, budget);
+                    int64_t r0 = 0, panels = 0, greedy = 0;
+                    for (int64_t r = 0; r < M; ++greedy) r += panel_rows(M, N, sym, slices, r, budget);
+                    CHECK(even <= budget);
+                    for (; r0 < M; ++panels) {
+                        const int64_t rows = panel_rows(M, N, sym, slices, r0, even);
+                        CHECK(rows >= 1 && r0 + rows <= M);
+                        CHECK(r0 + rows == M || rows % kLargeBM == 0);
+                        CHECK(rows <= kLargeBM || panel_bytes(N, sym, slices, r0, rows) <= budget);
+                        CHECK(panel_bytes(N, sym, slices, r0, rows) <=
+                              std::max(budget, panel_bytes(N, false, slices, 0, std::min(M, kLargeBM))));
+                        r0 += rows;
+                    }
+                    CHECK(panels == greedy);
+                }
     // Places: every token has one of its own, in order, that leads back to it; every chunk of a step
     // is contiguous and, where tokens are apart, starts on a multiple of 8; the places without a
     // token say so and are few.

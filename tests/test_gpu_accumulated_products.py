@@ -36,3 +36,33 @@ def test_accumulated_products_at_tile_edges(rq, ctx, n, T, weighted):
         F = H0.cuda()
         rq.fisher_accum(ctx, X.cuda(), F)
         assert torch.equal(F.cpu(), outs[0])
+
+
+@pytest.mark.parametrize("n,T,dominant", [(520, 20000, False), (520, 20000, True), (1030, 6500, True),
+                                          (7001, 18501, False)])
+def test_weighted_sums_over_many_slices(rq, ctx, n, T, dominant):
+    """Weighted sums over many slices of at most 1024 tokens and (7001 columns) over two panels of rows,
+    norm-wise against float64, also where three tokens carry the sums.  A slice adds 1024 / 16 matrix
+    instructions' products for each of the two high terms, each rounding by 2^-24 / sqrt(3) rms at most:
+    sqrt(128) 2^-24 / sqrt(3) = 3.9e-7 (measured 6e-8 to 2.1e-7).  Without the third bf16 term of s x the
+    error is 6.4e-7 to 2.5e-6, which the reference shows on its own sums."""
+    import torch
+    print(f"[gpu-case] weighted sums n={n} T={T} dominant={dominant}", flush=True)
+    g = torch.Generator().manual_seed(n + T)
+    X = (torch.randn((T, n), generator=g) * 2).to(torch.bfloat16).cuda()
+    s = torch.exp(torch.randn(T, generator=g))
+    if dominant:
+        s[torch.randperm(T, generator=g)[:3]] *= 1e5
+    s = s.cuda()
+    H = torch.zeros((n, n), dtype=torch.float64, device="cuda")
+    rq.hessian_accum(ctx, X, s, H)
+    ref, two = torch.zeros_like(H), torch.zeros_like(H)
+    for t in range(0, T, 4096):
+        x, w = X[t:t + 4096], s[t:t + 4096, None]
+        sx = x.float() * w
+        hi = sx.bfloat16().float()
+        lo = (sx - hi).bfloat16()
+        ref += (x.double() * w.double()).T.contiguous() @ x.double()
+        two += (hi.double() + lo.double()).T.contiguous() @ x.double()
+    assert torch.equal(H, H.T)
+    assert float((H - ref).norm()) <= 4e-7 * float(ref.norm()) < float((two - ref).norm())
