@@ -23,6 +23,17 @@ int set_error(realq_ctx* ctx, int code, const std::string& msg) {
     return code;
 }
 
+// Frees the buffer of `slot`, if it has one, once the stream is through with it.
+static int drop_ws(realq_ctx* ctx, const char* slot) {
+    realq_ctx::Buf& b = ctx->ws[slot];
+    if (!b.p) return REALQ_OK;
+    const hipError_t e = hipStreamSynchronize(ctx->stream);
+    if (e != hipSuccess) return set_error(ctx, REALQ_ERR_HIP, std::string("sync: ") + hipGetErrorString(e));
+    (void)hipFree(b.p);
+    b = realq_ctx::Buf();
+    return REALQ_OK;
+}
+
 // Device memory for `slot` (NULL: none of the context's).  The slices of finished products are given
 // back before the memory is said to be out: nothing is kept in them between calls.
 static bool device_alloc(realq_ctx* ctx, const char* slot, size_t bytes, void** p) {
@@ -30,11 +41,8 @@ static bool device_alloc(realq_ctx* ctx, const char* slot, size_t bytes, void** 
         if (hipMalloc(p, bytes) == hipSuccess && *p) return true;
         (void)hipGetLastError();
         *p = nullptr;
-        realq_ctx::Buf& slices = ctx->ws[kSliceSlot];
-        if (!slices.p || (slot && std::strcmp(slot, kSliceSlot) == 0)) return false;
-        if (hipStreamSynchronize(ctx->stream) != hipSuccess) return false;
-        (void)hipFree(slices.p);
-        slices = realq_ctx::Buf();
+        if (!ctx->ws[kSliceSlot].p || (slot && std::strcmp(slot, kSliceSlot) == 0)) return false;
+        if (drop_ws(ctx, kSliceSlot)) return false;
     }
 }
 
@@ -42,13 +50,7 @@ int get_ws(realq_ctx* ctx, const char* slot, size_t bytes, void** out) {
     auto& b = ctx->ws[slot];
     if (bytes == 0) bytes = 16;
     if (b.bytes < bytes) {
-        if (b.p) {
-            hipError_t e = hipStreamSynchronize(ctx->stream);
-            if (e != hipSuccess) return set_error(ctx, REALQ_ERR_HIP, std::string("sync: ") + hipGetErrorString(e));
-            (void)hipFree(b.p);
-            b.p = nullptr;
-            b.bytes = 0;
-        }
+        if (const int rc = drop_ws(ctx, slot)) return rc;
         void* p = nullptr;
         if (!device_alloc(ctx, slot, bytes, &p))
             return set_error(ctx, REALQ_ERR_OOM,
@@ -239,6 +241,14 @@ int realq_ctx_reset_timing(realq_ctx* ctx) {
 
 }  // extern "C"
 
+// Tokens per chunk of the products over tokens (about 256 MB of a transposed chunk), and the bytes
+// of one such chunk.
+static int64_t token_chunk(int64_t n, int64_t T) {
+    const int64_t tc = ((int64_t)128 << 20) / n;
+    return std::min(tc < 256 ? 256 : tc / 256 * 256, (T + 7) / 8 * 8);
+}
+static int64_t gram_staging(int64_t n, int64_t T) { return n * realq::plan::operand_stride(token_chunk(n, T)) * 2; }
+
 static hipError_t acc_direct(const realq::GemmArgs& g, double* C, int64_t ldc, bool, hipStream_t st) {
     return realq::gemm_acc_f64(g, C, ldc, st);
 }
@@ -371,10 +381,7 @@ int realq_hessian_accum(realq_ctx* ctx, const uint16_t* Xhat, const float* s, in
     if (T == 0) return REALQ_OK;
     if (!Xhat || !H_acc) return set_error(ctx, REALQ_ERR_INVALID_ARG, "hessian_accum: NULL Xhat or H_acc");
     // token chunk bounded so the transposed workspace stays near 256 MiB per operand
-    int64_t tc = (int64_t)(128ll << 20) / n;
-    tc = tc < 256 ? 256 : (tc / 256) * 256;
-    if (tc > T) tc = ((T + 7) / 8) * 8;
-    const int64_t ld = realq::plan::operand_stride(tc);
+    const int64_t tc = token_chunk(n, T), ld = realq::plan::operand_stride(tc);
     void *xt = nullptr, *hi = nullptr, *lo = nullptr, *lo2 = nullptr;
     int rc = get_ws(ctx, "h_xt", (size_t)n * ld * 2, &xt);
     if (rc) return rc;
@@ -505,15 +512,13 @@ static int gram_accum(realq_ctx* ctx, const uint16_t* Xhat, const uint16_t* X, c
     hipStream_t s = ctx->stream;
     int rc;
     void *sdh, *sdl, *dh, *dl, *xt;
-    int64_t tc = (int64_t)(128ll << 20) / n;
-    tc = tc < 256 ? 256 : (tc / 256) * 256;
-    if (tc > T) tc = ((T + 7) / 8) * 8;
-    const int64_t ld = realq::plan::operand_stride(tc);
-    if ((rc = get_ws(ctx, "g_sdh", (size_t)n * ld * 2, &sdh))) return rc;
-    if ((rc = get_ws(ctx, "g_sdl", (size_t)n * ld * 2, &sdl))) return rc;
-    if ((rc = get_ws(ctx, "g_dh16", (size_t)n * ld * 2, &dh))) return rc;
-    if ((rc = get_ws(ctx, "g_dl16", (size_t)n * ld * 2, &dl))) return rc;
-    if ((rc = get_ws(ctx, "g_xt", (size_t)n * ld * 2, &xt))) return rc;
+    const int64_t tc = token_chunk(n, T), ld = realq::plan::operand_stride(tc);
+    const size_t staging = (size_t)gram_staging(n, T);
+    if ((rc = get_ws(ctx, "g_sdh", staging, &sdh))) return rc;
+    if ((rc = get_ws(ctx, "g_sdl", staging, &sdl))) return rc;
+    if ((rc = get_ws(ctx, "g_dh16", staging, &dh))) return rc;
+    if ((rc = get_ws(ctx, "g_dl16", staging, &dl))) return rc;
+    if ((rc = get_ws(ctx, "g_xt", staging, &xt))) return rc;
     Timed tm(ctx, "gram");
     RQ_HIP(ctx, realq::fill_f64(Gdh, 0.0, n * n, s));
     RQ_HIP(ctx, realq::fill_f64(Gdd, 0.0, n * n, s));
@@ -600,6 +605,79 @@ static int inc_init(realq_bgd_state* st) {
     return REALQ_OK;
 }
 
+// A device buffer: its slot among the context workspaces, its size and, for the arrays of a state,
+// where its address goes.
+struct Array {
+    const char* slot;
+    int64_t bytes;
+    void (*put)(realq_bgd_state*, void*);
+};
+
+// The arrays of a token-form state (sizes from its tokens' places).
+static std::vector<Array> state_arrays(const realq_bgd_state* st) {
+    using S = realq_bgd_state;
+    const int64_t m = st->m, n = st->n, Tc = st->Tc, ldn = st->ldn, Tp = st->Tp;
+    const bool clip = st->prm.loss_clip > 0.f;
+    std::vector<Array> v{{"s_B", m * Tp * 4, [](S* s, void* p) { s->B = (float*)p; }},
+                         {"s_m", m * n * 4, [](S* s, void* p) { s->mA = (float*)p; }},
+                         {"s_v", m * n * 4, [](S* s, void* p) { s->vA = (float*)p; }},
+                         {"s_Dh", m * ldn * 2, [](S* s, void* p) { s->Dhi = (uint16_t*)p; }},
+                         {"s_Dl", m * ldn * 2, [](S* s, void* p) { s->Dlo = (uint16_t*)p; }},
+                         {"s_XT", n * Tp * 2, [](S* s, void* p) { s->XhT = (uint16_t*)p; }},
+                         // with the clip split(R o s) as two arrays, else one of 128-byte lines (32 tokens'
+                         // hi, then their lo): whole-line stores
+                         {"s_Rh", m * (clip ? q_ld(Tc) : r_ld(Tc)) * 2, [](S* s, void* p) { s->Rhi = (uint16_t*)p; }}};
+    if (clip) {
+        v.push_back({"s_Rl", m * q_ld(Tc) * 2, [](S* s, void* p) { s->Rlo = (uint16_t*)p; }});
+        v.push_back({"s_Rf", m * q_ld(Tc) * 4, [](S* s, void* p) { s->Rf = (float*)p; }});
+        v.push_back({"s_tau", Tc * 4, [](S* s, void* p) { s->tau = (float*)p; }});
+    }
+    if (st->s && st->at.apart) v.push_back({"s_sg", st->at.count * 4, [](S* s, void* p) { s->sg = (float*)p; }});
+    return v;
+}
+
+// Whether a copy of the activations in `bytes` leaves room for what a sweep allocates after it: the
+// state's arrays, the workspaces of its steps and of the final loss (at their largest), 64 MB for
+// the small ones.  The copy only makes products faster; those it cannot do without.
+static bool copy_fits(realq_bgd_state* st, int64_t bytes) {
+    realq_ctx* ctx = st->ctx;
+    const int64_t m = st->m, n = st->n, mp = realq::plan::operand_stride(m), ldn = st->ldn;
+    const bool dense = st->M || st->P;
+    std::vector<Array> v = state_arrays(st);
+    v.push_back({"s_Xg", bytes, nullptr});
+    int64_t gp = 0;
+    for (int64_t nJ = n; nJ > 0; nJ -= 128)  // the split factor falls with the columns, not evenly
+        gp = std::max(gp, realq::plan::choose_splits(m, nJ, st->Tc, ctx->cus) * m * nJ * 4);
+    v.insert(v.end(), {{"b_Gp", gp, nullptr}, {"b_G", m * n * 4, nullptr}, {"q_E", m * 128 * 8, nullptr},
+                       {"l_W", m * n * 8, nullptr}});
+    const int64_t chunk = std::min(st->at.count * ldn * 2, (int64_t)256 << 20);
+    if (st->X != st->Xhat) v.insert(v.end(), {{"i_xh", chunk, nullptr}, {"i_xl", chunk, nullptr}});
+    if (st->prm.resid_increment && st->prm.steps > 1)
+        v.insert(v.end(), {{"s_Dacc", m * n * 4, nullptr}, {"s_Dinc", m * ldn * 2, nullptr}, {"s_G0", m * n * 4, nullptr}});
+    if (dense)
+        v.insert(v.end(), {{"s_Mah", m * mp * 2, nullptr}, {"s_Mal", m * mp * 2, nullptr}, {"b_Gm", m * n * 4, nullptr},
+                           {"b_GTh", mp * n * 2, nullptr}, {"b_GTl", mp * n * 2, nullptr}});
+    if (st->M) {
+        for (const char* slot : {"g_sdh", "g_sdl", "g_dh16", "g_dl16", "g_xt"}) v.push_back({slot, gram_staging(n, st->T), nullptr});
+        for (const char* slot : {"g_A", "g_D", "g_E", "g_MX"}) v.push_back({slot, m * n * 8, nullptr});
+        v.insert(v.end(), {{"g_dh", n * n * 8, nullptr}, {"g_dd", n * n * 8, nullptr}, {"g_M", m * m * 8, nullptr}});
+    }
+    int64_t need = 0;
+    for (const Array& a : v) {  // a buffer that the context holds grows
+        auto it = ctx->ws.find(a.slot);
+        const bool own = st->owns && a.slot[0] == 's';
+        need += std::max<int64_t>(0, a.bytes - (own || it == ctx->ws.end() ? 0 : (int64_t)it->second.bytes));
+    }
+    if (need == 0) return true;
+    need += (int64_t)64 << 20;
+    size_t free_bytes = 0, total = 0;
+    if (hipMemGetInfo(&free_bytes, &total) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return need <= (int64_t)free_bytes + (int64_t)ctx->ws[realq::kSliceSlot].bytes;
+}
+
 static int state_init(realq_bgd_state* st) {
     if (st->prm.form == REALQ_BGD_GRAM) return state_init_gram(st);
     realq_ctx* ctx = st->ctx;
@@ -608,70 +686,45 @@ static int state_init(realq_bgd_state* st) {
     st->gram = false;
     st->Tb = (st->prm.batch > 0 && st->prm.batch < T) ? st->prm.batch : T;
     st->nbatch = (T + st->Tb - 1) / st->Tb;
-    int64_t Tc = st->prm.tok_chunk > 0 ? std::min<int64_t>(st->prm.tok_chunk, st->Tb) : st->Tb;
-    st->Tc = Tc;
+    const int64_t Tc = st->Tc = st->prm.tok_chunk > 0 ? std::min<int64_t>(st->prm.tok_chunk, st->Tb) : st->Tb;
     const int64_t ldn = st->ldn = realq::plan::operand_stride(n);
     int rc;
     void* p;
-    st->at = realq::plan::place_tokens(T, st->Tb, Tc);
+    auto place = [&](bool may_part) {
+        st->at = realq::plan::place_tokens(T, st->Tb, Tc, may_part);
+        st->Tp = realq::plan::operand_stride(st->at.count);
+    };
+    place(true);
     // The activations are copied where their rows or places differ from the caller's.  The copy costs one
-    // read and write of Xhat against a residual product per Block-GD step; without steps, or without
-    // room for it, aligned rows stay where they are.  Without room, tokens keep their order.
+    // read and write of Xhat against a residual product per Block-GD step; without steps aligned
+    // rows stay where they are, and without room for it all rows do, with the tokens in their order.
     st->Xg = st->Xhat;
     st->ldx = n;
     if (st->at.apart || (ldn != n && (n % 8 || st->prm.steps > 0))) {
-        rc = state_alloc(st, &p, (size_t)st->at.count * ldn * 2, "s_Xg");
-        if (rc && (rc != REALQ_ERR_OOM || n % 8)) return rc;
+        const int64_t bytes = st->at.count * ldn * 2;
+        rc = copy_fits(st, bytes) ? state_alloc(st, &p, (size_t)bytes, "s_Xg") : REALQ_ERR_OOM;
+        if (rc && rc != REALQ_ERR_OOM) return rc;
         if (rc) {
-            st->at = realq::plan::place_tokens(T, st->Tb, Tc, false);
+            place(false);
+            if (!st->owns && (rc = realq::drop_ws(ctx, "s_Xg"))) return rc;
         } else {
             st->Xg = (const uint16_t*)p;
             st->ldx = ldn;
         }
     }
+    st->sg = st->s;
+    for (const Array& a : state_arrays(st)) {
+        if ((rc = state_alloc(st, &p, (size_t)a.bytes, a.slot))) return rc;
+        a.put(st, p);
+    }
     const realq::plan::Places& at = st->at;
-    const int64_t Tp = st->Tp = realq::plan::operand_stride(at.count);
-    if ((rc = state_alloc(st, &p, (size_t)m * Tp * 4, "s_B"))) return rc;
-    st->B = (float*)p;
-    if ((rc = state_alloc(st, &p, (size_t)m * n * 4, "s_m"))) return rc;
-    st->mA = (float*)p;
-    if ((rc = state_alloc(st, &p, (size_t)m * n * 4, "s_v"))) return rc;
-    st->vA = (float*)p;
-    if ((rc = state_alloc(st, &p, (size_t)m * ldn * 2, "s_Dh"))) return rc;
-    st->Dhi = (uint16_t*)p;
-    if ((rc = state_alloc(st, &p, (size_t)m * ldn * 2, "s_Dl"))) return rc;
-    st->Dlo = (uint16_t*)p;
-    if ((rc = state_alloc(st, &p, (size_t)n * Tp * 2, "s_XT"))) return rc;
-    st->XhT = (uint16_t*)p;
-    if (st->prm.loss_clip > 0.f) {
-        // the clip writes split(R o s) as two arrays
-        if ((rc = state_alloc(st, &p, (size_t)m * q_ld(Tc) * 2, "s_Rh"))) return rc;
-        st->Rhi = (uint16_t*)p;
-        if ((rc = state_alloc(st, &p, (size_t)m * q_ld(Tc) * 2, "s_Rl"))) return rc;
-        st->Rlo = (uint16_t*)p;
-    } else {
-        // one array of 128-byte lines (32 tokens' hi, then their lo): whole-line stores
-        if ((rc = state_alloc(st, &p, (size_t)m * r_ld(Tc) * 2, "s_Rh"))) return rc;
-        st->Rhi = (uint16_t*)p;
-        st->Rlo = nullptr;
-    }
-    if (st->prm.loss_clip > 0.f) {
-        if ((rc = state_alloc(st, &p, (size_t)m * q_ld(Tc) * 4, "s_Rf"))) return rc;
-        st->Rf = (float*)p;
-        if ((rc = state_alloc(st, &p, (size_t)Tc * 4, "s_tau"))) return rc;
-        st->tau = (float*)p;
-    }
+    const int64_t Tp = st->Tp;
 
     Timed tm(ctx, "init");
     RQ_HIP(ctx, realq::fill_f32(st->mA, 0.f, m * n, s));
     RQ_HIP(ctx, realq::fill_f32(st->vA, 0.f, m * n, s));
     if (st->Xg != st->Xhat) RQ_HIP(ctx, realq::place_rows_u16(st->Xhat, n, const_cast<uint16_t*>(st->Xg), ldn, n, at, s));
-    st->sg = st->s;
-    if (st->s && at.apart) {
-        if ((rc = state_alloc(st, &p, (size_t)at.count * 4, "s_sg"))) return rc;
-        st->sg = (const float*)p;
-        RQ_HIP(ctx, realq::place_f32(st->s, (float*)p, at, s));
-    }
+    if (st->sg != st->s) RQ_HIP(ctx, realq::place_f32(st->s, const_cast<float*>(st->sg), at, s));
     RQ_HIP(ctx, realq::transpose_u16(st->Xg, st->ldx, st->XhT, Tp, at.count, n, s));
     // Residual base before any block is locked: B = W0 (Xhat - X)^T.
     if (st->X == st->Xhat) {
@@ -1257,26 +1310,30 @@ int realq_handoff(realq_ctx* ctx, const float* Wa, const float* Wb, const uint16
     if (T == 0) return REALQ_OK;
     if (!Wa || !X || !Y) return set_error(ctx, REALQ_ERR_INVALID_ARG, "handoff: NULL Wa, X or Y");
     hipStream_t s = ctx->stream;
-    void *hi, *lo, *xg;
+    void *hi, *lo, *xg, *G = nullptr;
     int rc;
     const int64_t ldn = (n + 7) / 8 * 8;  // 16-byte operand rows whatever n is
     if ((rc = get_ws(ctx, "h_wh", (size_t)m * ldn * 2, &hi))) return rc;
     if ((rc = get_ws(ctx, "h_wl", (size_t)m * ldn * 2, &lo))) return rc;
+    if (Wb && (rc = get_ws(ctx, "h_gate", (size_t)T * m * 4, &G))) return rc;
     const uint16_t* Xg = X;
-    if (ldn != n) {
-        if ((rc = get_ws(ctx, "h_xg", (size_t)T * ldn * 2, &xg))) return rc;
-        RQ_HIP(ctx, realq::copy_rows_u16(X, n, (uint16_t*)xg, ldn, T, n, s));
-        Xg = (const uint16_t*)xg;
+    int64_t ldx = n;
+    if (ldn != n) {  // without room for the copy the product takes the caller's rows, slower
+        rc = get_ws(ctx, "h_xg", (size_t)T * ldn * 2, &xg);
+        if (rc && rc != REALQ_ERR_OOM) return rc;
+        if (!rc) {
+            RQ_HIP(ctx, realq::copy_rows_u16(X, n, (uint16_t*)xg, ldn, T, n, s));
+            Xg = (const uint16_t*)xg;
+            ldx = ldn;
+        }
     }
     // acc[i][t] = sum_j W[i][j] X[t][j], stored token-major
-    realq::GemmArgs g{(const uint16_t*)hi, (const uint16_t*)lo, ldn, Xg, ldn, m, T, n, 1};
+    realq::GemmArgs g{(const uint16_t*)hi, (const uint16_t*)lo, ldn, Xg, ldx, m, T, n, 1};
     if (!Wb) {
         RQ_HIP(ctx, realq::split_diff_f32(Wa, n, nullptr, 0, (uint16_t*)hi, (uint16_t*)lo, ldn, m, n, s));
         RQ_HIP(ctx, realq::gemm_store_bf16_t(g, Y, m, s));
         return REALQ_OK;
     }
-    void* G;
-    if ((rc = get_ws(ctx, "h_gate", (size_t)T * m * 4, &G))) return rc;
     RQ_HIP(ctx, realq::split_diff_f32(Wa, n, nullptr, 0, (uint16_t*)hi, (uint16_t*)lo, ldn, m, n, s));
     RQ_HIP(ctx, realq::gemm_store_f32_t(g, (float*)G, m, s));  // gate pre-activation, token-major
     RQ_HIP(ctx, realq::split_diff_f32(Wb, n, nullptr, 0, (uint16_t*)hi, (uint16_t*)lo, ldn, m, n, s));

@@ -13,6 +13,22 @@ class BgdParams(ctypes.Structure):
                 ("batch", I64), ("resid_increment", ctypes.c_int32)]
 
 
+class QParams(ctypes.Structure):
+    _fields_ = [("bits", ctypes.c_int32), ("group", ctypes.c_int32), ("block", ctypes.c_int32), ("grid", ctypes.c_int32),
+                ("damp", ctypes.c_float), ("sym", ctypes.c_int32)]
+
+
+class LayerDesc(ctypes.Structure):
+    _fields_ = [("m", I64), ("n", I64), ("T", I64), ("W0", VP), ("X", VP), ("Xhat", VP), ("s", VP), ("M", VP), ("P", VP),
+                ("window_offset", ctypes.c_int32), ("window_total", ctypes.c_int32), ("q", QParams), ("bgd", BgdParams),
+                ("s_groups", VP), ("n_groups", ctypes.c_int32)]
+
+
+class LayerOut(ctypes.Structure):
+    _fields_ = [("codes", VP), ("scales", VP), ("zeros", VP), ("W_hat", VP), ("H", VP), ("U", VP), ("dead", VP),
+                ("loss_trace", VP), ("loss_final", ctypes.c_double), ("ms_total", ctypes.c_double)]
+
+
 def buf(k):
     """A device address of the caller's; nothing reads it."""
     return VP((1 << 36) + (k << 34))
@@ -28,6 +44,7 @@ class Library:
         self.c = ctypes.CDLL(lib)
         self.c.realq_last_error.restype = ctypes.c_char_p
         self.c.realq_last_error.argtypes = [VP]
+        self.c.realq_ctx_destroy.argtypes = [VP]
         self.ctx = VP()
         assert self.c.realq_ctx_create(ctypes.byref(self.ctx), None) == 0
 
@@ -52,6 +69,26 @@ class Library:
         self.ok("realq_bgd_state_create", ctypes.byref(st), buf(1), buf(2), buf(2) if same else buf(3), s, M, P, m, n, T,
                 ctypes.byref(b))
         return st
+
+    def layer(self, m, n, T, s=False, M=False, P=False, **params):
+        """(code, message) of realq_quantize_layer."""
+        d, o = LayerDesc(), LayerOut()
+        self.c.realq_qparams_default(ctypes.byref(d.q))
+        self.c.realq_bgd_params_default(ctypes.byref(d.bgd))
+        for k, v in params.items():
+            setattr(d.bgd, k, v)
+        d.m, d.n, d.T = m, n, T
+        d.W0, d.X, d.Xhat = buf(1).value, buf(2).value, buf(3).value
+        d.s, d.M, d.P = (buf(4 + i).value if on else None for i, on in enumerate((s, M, P)))
+        d.window_total = -(-n // 128) if P else 0
+        o.codes = o.scales = o.zeros = o.W_hat = o.loss_trace = buf(7).value
+        return self.call("realq_quantize_layer", ctypes.byref(d), ctypes.byref(o))
+
+    def fresh(self):
+        """A new context, the old one's memory given back."""
+        self.c.realq_ctx_destroy(self.ctx)
+        assert self.held() == 0
+        assert self.c.realq_ctx_create(ctypes.byref(self.ctx), None) == 0
 
     def held(self):
         return self.fake.fake_held()
@@ -117,6 +154,33 @@ def slice_memory(L):
             for T in range(1, 40000, 211):
                 L.ok("realq_hessian_accum", buf(1), s, T, n, buf(3))
             assert L.fake.fake_mallocs() == 0, (n, s)
+
+
+def little_room(L):
+    """Calls succeed in the memory that they cannot do without (measured as the least before padded
+    copies of the activations and product slices existed, and 2% for padded rows), and in any larger
+    amount: what is optional leaves room for what is not."""
+    cases = [(5588, dict(m=1024, n=4096, T=262144, steps=8, lr=1e-5)),
+             (6356, dict(m=1024, n=4096, T=262144, steps=8, lr=1e-5, s=True)),
+             (1158, dict(m=1000, n=1352, T=30001, steps=4, M=True, P=True)),
+             (2782, dict(m=4096, n=1353, T=30001, steps=4, M=True, s=True)),
+             (3672, dict(m=512, n=4097, T=200001, steps=2)), (3609, dict(m=512, n=4097, T=200001, steps=0)),
+             (3237, dict(m=512, n=4096, T=200000, steps=2, batch=1001)),
+             (3989, dict(m=512, n=4097, T=200000, steps=2, batch=100, s=True)),
+             (9644, dict(m=512, n=14336, T=65536, steps=2, s=True)),
+             (1301, dict(m=512, n=2048, T=65536, steps=2, loss_clip=0.95, batch=1003))]
+    for mb, case in cases:
+        for room in [int(mb * 1.02) + 64 * k for k in range(120)]:
+            L.fresh()
+            L.fake.fake_set_limit(room << 20)
+            rc, msg = L.layer(**case)
+            assert rc == 0, (case, room, mb, msg)
+        rc, msg = L.layer(**case)  # once more on the buffers held
+        assert rc == 0, (case, msg)
+    for mb in range(272, 1200, 16):
+        L.fresh()
+        L.fake.fake_set_limit(mb << 20)
+        L.ok("realq_handoff", buf(1), buf(2), buf(3), 65536, 4097, 1000, buf(5))
 
 
 if __name__ == "__main__":
