@@ -305,26 +305,57 @@ hipError_t split_f64(const double* in, uint16_t* hi, uint16_t* lo, int64_t ldo, 
     return hipGetLastError();
 }
 
+// Row-wise kernels over activations: 8 columns a thread, a row to 2^row_log2 threads (all TB of them
+// from 8 TB columns on), rows past the launch's in further rounds.  The outputs' rows are 16-byte
+// aligned and padded to whole chunks of 8 columns (the padding is written, with zeros); inputs are
+// loaded 16 bytes at a time where theirs are.
+struct RowSpread {
+    int64_t rows, cols;
+    int row_log2, vec;
+    unsigned grid;
+};
+static RowSpread row_spread(int64_t rows, int64_t cols, bool vec) {
+    RowSpread r{rows, cols, 0, vec, 0};
+    while ((1 << r.row_log2) < std::min<int64_t>((cols + 7) / 8, TB)) ++r.row_log2;
+    const int64_t per = TB >> r.row_log2;
+    // a launch holds less than 2^32 threads: 2^20 blocks at most, whatever the token count
+    r.grid = (unsigned)std::min<int64_t>((rows + per - 1) / per, 1 << 20);
+    return r;
+}
+// f(row, column) for this thread's chunks of 8 columns
+template <class F>
+__device__ __forceinline__ void each_chunk8(const RowSpread& r, const F& f) {
+    const int per = TB >> r.row_log2, wide = 1 << r.row_log2;
+    for (int64_t i = (int64_t)blockIdx.x * per + (threadIdx.x >> r.row_log2); i < r.rows; i += (int64_t)gridDim.x * per)
+        for (int64_t j = (threadIdx.x & (wide - 1)) * 8; j < r.cols; j += wide * 8) f(i, j);
+}
+__device__ __forceinline__ u16x8 chunk8(const uint16_t* p, int64_t j, const RowSpread& r) {
+    u16x8 v = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (r.vec && j + 8 <= r.cols) return *reinterpret_cast<const u16x8*>(p + j);
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        if (j + e < r.cols) v[e] = p[j + e];
+    return v;
+}
+
 // Rows of `cols` bf16 values copied to stride ldo: activations whose rows are not a multiple of 16
 // bytes, or whose tokens have places of their own, laid out once for the GEMMs' direct-to-LDS loads.
-// A block takes every gridDim.x-th row.
-__global__ __launch_bounds__(256) void place_rows_kernel(const uint16_t* __restrict__ in, int64_t ldi,
-                                                         uint16_t* __restrict__ out, int64_t ldo, int64_t cols,
-                                                         plan::Places L) {
-    for (int64_t r = blockIdx.x; r < L.count; r += gridDim.x) {
-        const int64_t t = plan::token_at(L, r);
-        const uint16_t* p = in + t * ldi;
-        uint16_t* q = out + r * ldo;
-        for (int64_t c = threadIdx.x; c < cols; c += 256) q[c] = t >= 0 ? p[c] : 0;
-    }
+__global__ __launch_bounds__(TB) void place_rows_kernel(const uint16_t* __restrict__ in, int64_t ldi,
+                                                        uint16_t* __restrict__ out, int64_t ldo, plan::Places L,
+                                                        RowSpread r) {
+    each_chunk8(r, [&](int64_t i, int64_t j) {
+        const int64_t t = plan::token_at(L, i);
+        const u16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+        *reinterpret_cast<u16x8*>(out + i * ldo + j) = t >= 0 ? chunk8(in + t * ldi, j, r) : zero;
+    });
 }
 
 hipError_t place_rows_u16(const uint16_t* in, int64_t ldi, uint16_t* out, int64_t ldo, int64_t cols,
                           const plan::Places& L, hipStream_t st) {
     if (L.count <= 0 || cols <= 0) return hipSuccess;
-    // a launch holds less than 2^32 threads: 2^20 blocks at most, whatever the token count
-    const int64_t grid = std::min<int64_t>(L.count, 1 << 20);
-    hipLaunchKernelGGL(place_rows_kernel, dim3((unsigned)grid), dim3(256), 0, st, in, ldi, out, ldo, cols, L);
+    if (!rows16(out, ldo)) return hipErrorInvalidValue;
+    const RowSpread r = row_spread(L.count, cols, rows16(in, ldi));
+    hipLaunchKernelGGL(place_rows_kernel, dim3(r.grid), dim3(TB), 0, st, in, ldi, out, ldo, L, r);
     return hipGetLastError();
 }
 
@@ -673,26 +704,35 @@ hipError_t blend_split(const float* M, const float* P, float alpha, int64_t m, u
     return hipGetLastError();
 }
 
-__global__ void split_diff_bf16_kernel(const uint16_t* __restrict__ a, const uint16_t* __restrict__ b,
-                                       uint16_t* __restrict__ hi, uint16_t* __restrict__ lo, int64_t cols, int64_t ldo,
-                                       int64_t total, plan::Places L, int64_t p0) {
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = e / cols, j = e % cols, t = plan::token_at(L, p0 + i), o = i * ldo + j;
-        // exact in float32 for bf16 inputs of similar magnitude
-        const float v = t >= 0 ? bf2f(a[t * cols + j]) - bf2f(b[t * cols + j]) : 0.f;
-        uint16_t h, l;
-        split_bf16(v, h, l);
-        hi[o] = h;
-        lo[o] = l;
-    }
+__global__ __launch_bounds__(TB) void split_diff_bf16_kernel(const uint16_t* __restrict__ a,
+                                                             const uint16_t* __restrict__ b, uint16_t* __restrict__ hi,
+                                                             uint16_t* __restrict__ lo, int64_t ldo, plan::Places L,
+                                                             int64_t p0, RowSpread r) {
+    each_chunk8(r, [&](int64_t i, int64_t j) {
+        const int64_t t = plan::token_at(L, p0 + i);
+        u16x8 x = {0, 0, 0, 0, 0, 0, 0, 0}, y = x, h, l;
+        if (t >= 0) {
+            x = chunk8(a + t * r.cols, j, r);
+            y = chunk8(b + t * r.cols, j, r);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            uint16_t hh, ll;
+            split_bf16(bf2f(x[e]) - bf2f(y[e]), hh, ll);  // exact in float32 for bf16 inputs of similar magnitude
+            h[e] = hh;
+            l[e] = ll;
+        }
+        *reinterpret_cast<u16x8*>(hi + i * ldo + j) = h;
+        *reinterpret_cast<u16x8*>(lo + i * ldo + j) = l;
+    });
 }
 
 hipError_t split_diff_bf16(const uint16_t* a, const uint16_t* b, uint16_t* hi, uint16_t* lo, int64_t ldo, int64_t rows,
                            int64_t cols, const plan::Places& L, int64_t p0, hipStream_t st) {
-    const int64_t total = rows * cols;
-    if (total <= 0) return hipSuccess;
-    hipLaunchKernelGGL(split_diff_bf16_kernel, dim3(grid_for(total, 4)), dim3(TB), 0, st, a, b, hi, lo, cols, ldo,
-                       total, L, p0);
+    if (rows <= 0 || cols <= 0) return hipSuccess;
+    if (!rows16(hi, ldo) || !rows16(lo, ldo)) return hipErrorInvalidValue;
+    const RowSpread r = row_spread(rows, cols, rows16(a, cols) && rows16(b, cols));
+    hipLaunchKernelGGL(split_diff_bf16_kernel, dim3(r.grid), dim3(TB), 0, st, a, b, hi, lo, ldo, L, p0, r);
     return hipGetLastError();
 }
 
