@@ -101,10 +101,10 @@ struct realq_bgd_state {
     int64_t locked = 0;  // columns [0, locked) are folded into the residual base
     bool owns = true;
     // Rows of every GEMM operand start on 16 bytes whatever n and T are (the direct-to-LDS loads need
-    // it; the checked register path is about 6x slower) and are an odd number of 128-byte lines
-    // apart (plan::operand_stride): columns padded to ldn, tokens to Tp.  `at` gives each token's place
-    // in the token-minor arrays (plan::Places).  Xg / sg are padded copies of the caller's activations
-    // and token weights in the order of the places.
+    // it; the checked register path is about 6x slower): columns padded to ldn (plan::row_stride), tokens
+    // to Tp (plan::operand_stride).  `at` gives each token's place in the token-minor arrays
+    // (plan::Places).  Xg / sg are padded copies of the caller's activations and token weights in the
+    // order of the places.
     int64_t ldn = 0, ldx = 0, Tp = 0;
     realq::plan::Places at;
     const uint16_t* Xg = nullptr;  // [at.count,ldx] Xhat as the GEMMs read it (ldx = n: the caller's own)
@@ -139,7 +139,7 @@ struct realq_bgd_state {
     float* C0 = nullptr;      // [m,n] W0 Delta^T S Xhat
     float* Pm = nullptr;      // [m,n] D Xhat^T S Xhat (per step)
     double* cconst = nullptr; // <W0 Delta^T S Delta, W0> (device scalar)
-    // blended metric alpha M + (1 - alpha) P as a bf16 pair [m, operand_stride(m)], formed once per alpha
+    // blended metric alpha M + (1 - alpha) P as a bf16 pair [m, row_stride(m)], formed once per alpha
     uint16_t* Mah = nullptr;
     uint16_t* Mal = nullptr;
     float Ma_alpha = -1.f;
@@ -641,7 +641,7 @@ static std::vector<Array> state_arrays(const realq_bgd_state* st) {
 // the small ones.  The copy only makes products faster; those it cannot do without.
 static bool copy_fits(realq_bgd_state* st, int64_t bytes) {
     realq_ctx* ctx = st->ctx;
-    const int64_t m = st->m, n = st->n, mp = realq::plan::operand_stride(m), ldn = st->ldn;
+    const int64_t m = st->m, n = st->n, mp = realq::plan::row_stride(m), ldn = st->ldn;
     const bool dense = st->M || st->P;
     std::vector<Array> v = state_arrays(st);
     v.push_back({"s_Xg", bytes, nullptr});
@@ -687,7 +687,7 @@ static int state_init(realq_bgd_state* st) {
     st->Tb = (st->prm.batch > 0 && st->prm.batch < T) ? st->prm.batch : T;
     st->nbatch = (T + st->Tb - 1) / st->Tb;
     const int64_t Tc = st->Tc = st->prm.tok_chunk > 0 ? std::min<int64_t>(st->prm.tok_chunk, st->Tb) : st->Tb;
-    const int64_t ldn = st->ldn = realq::plan::operand_stride(n);
+    const int64_t ldn = st->ldn = realq::plan::row_stride(n);
     int rc;
     void* p;
     auto place = [&](bool may_part) {
@@ -763,7 +763,7 @@ static int state_init_gram(realq_bgd_state* st) {
     st->Tc = T;
     st->Tb = T;
     st->nbatch = 1;
-    const int64_t ldn = st->ldn = realq::plan::operand_stride(n);
+    const int64_t ldn = st->ldn = realq::plan::row_stride(n);
     int rc;
     void* p;
     if ((rc = state_alloc(st, &p, (size_t)m * n * 4, "s_m"))) return rc;
@@ -1189,23 +1189,23 @@ int realq_bgd_step(realq_ctx* ctx, realq_bgd_state* st, double* W, int64_t c1, f
         // (the lo*lo term is below float32 rounding of the product).
         if (!st->Mah) {
             void* p;
-            if ((rc = state_alloc(st, &p, (size_t)m * realq::plan::operand_stride(m) * 2, "s_Mah"))) return rc;
+            if ((rc = state_alloc(st, &p, (size_t)m * realq::plan::row_stride(m) * 2, "s_Mah"))) return rc;
             st->Mah = (uint16_t*)p;
-            if ((rc = state_alloc(st, &p, (size_t)m * realq::plan::operand_stride(m) * 2, "s_Mal"))) return rc;
+            if ((rc = state_alloc(st, &p, (size_t)m * realq::plan::row_stride(m) * 2, "s_Mal"))) return rc;
             st->Mal = (uint16_t*)p;
             st->Ma_alpha = -1.f;
         }
         if (st->Ma_alpha != alpha) {
             RQ_HIP(ctx, realq::blend_split(st->M, alpha < 1.f ? st->P : nullptr, alpha, m, st->Mah, st->Mal,
-                                           realq::plan::operand_stride(m), s));
+                                           realq::plan::row_stride(m), s));
             st->Ma_alpha = alpha;
         }
         void *Gm, *gth, *gtl;
         if ((rc = get_ws(ctx, "b_Gm", (size_t)m * nJ * 4, &Gm))) return rc;
-        if ((rc = get_ws(ctx, "b_GTh", (size_t)realq::plan::operand_stride(m) * nJ * 2, &gth))) return rc;
-        if ((rc = get_ws(ctx, "b_GTl", (size_t)realq::plan::operand_stride(m) * nJ * 2, &gtl))) return rc;
+        if ((rc = get_ws(ctx, "b_GTh", (size_t)realq::plan::row_stride(m) * nJ * 2, &gth))) return rc;
+        if ((rc = get_ws(ctx, "b_GTl", (size_t)realq::plan::row_stride(m) * nJ * 2, &gtl))) return rc;
         const float invT = (float)(1.0 / (double)Tn);
-        const int64_t mp = realq::plan::operand_stride(m);
+        const int64_t mp = realq::plan::row_stride(m);
         {
             Timed tm(ctx, "metric");
             RQ_HIP(ctx,

@@ -50,6 +50,8 @@ int64_t choose_splits(int64_t M, int64_t N, int64_t K, int cus) {
     return best;
 }
 
+int64_t row_stride(int64_t n) { return (n + 63) / 64 * 64; }
+
 int64_t operand_stride(int64_t n) {
     const int64_t lines = (n + 63) / 64;
     return 64 * (lines | 1);

@@ -28,7 +28,15 @@ int64_t effective_splits(int64_t K, int64_t splits);
 // every split keeps at least 256 tokens.
 int64_t choose_splits(int64_t M, int64_t N, int64_t K, int cus);
 
-// Row stride (elements) of a bf16 GEMM operand laid out by the library: whole 128-byte lines, an odd
+// Row stride (elements) of a bf16 operand over the columns or rows of a module (activations, weight
+// splits, Gram matrices, metrics): whole 128-byte lines.  Rows that start inside a line cost the residual products 5 to 25% (2048 x
+// 4104 at 65664 tokens 33.2 ms on whole lines, 38.4 at 4104 elements; of an increment 20.1 and
+// 25.6).  An odd number of lines gains nothing here, where K is a few thousand: 1024 x 8192 at 131072
+// tokens 105 ms at 8192 elements, 112 at 8256 (and a copy of the activations to get there); Gram steps
+// of 1024 x 8192 87 and 95 ms.
+int64_t row_stride(int64_t n);
+
+// Row stride (elements) of a bf16 GEMM operand over the tokens: whole 128-byte lines, an odd
 // number of them.  A tile's loads walk 256 rows at one K offset; with a power-of-two stride those
 // lines fall on a few memory channels (gradient product of 2048 x 4096 over 65536 tokens: 1.11 to
 // 1.46 ms from run to run at a stride of 65536 elements, 0.93 ms at 65600).

@@ -97,6 +97,19 @@ class Library:
         return self.fake.fake_launches(b"") + self.fake.fake_copies()
 
 
+def whole_lines(L):
+    """Activations whose rows are whole 128-byte lines are read where they are: the state holds the
+    arrays it needs and no copy of them."""
+    for m, n, T in ((1024, 4096, 262144), (64, 1024, 65536), (512, 8192, 131072)):
+        h0 = L.held()
+        st = L.state(m, n, T, steps=1)
+        Tp = T + 128
+        arrays = m * Tp * 4 + 2 * m * n * 4 + 2 * m * n * 2 + n * Tp * 2 + m * 2 * Tp * 2
+        workspaces = 2 * (256 << 20)  # the difference of the two inputs, a chunk at a time
+        assert L.held() - h0 <= arrays + workspaces + (1 << 20), (m, n, T, L.held() - h0, arrays)
+        L.c.realq_bgd_state_destroy(st)
+
+
 def many_tokens(L):
     """Rows that need a padded copy, 2^24 of them: no launch past the grid limit."""
     T = 1 << 24
@@ -110,8 +123,8 @@ def many_tokens(L):
 
 def short_chunks(L):
     """Batches and token chunks that are not multiples of 8: the state's arrays grow by a sixteenth at most
-    over the aligned case's (besides the inputs' copy, which that case has too), and its set-up and
-    lock take as many launches as that case's."""
+    over the aligned case's, besides a copy of the inputs in the places' order, and its set-up and lock
+    take as many launches as that case's, the two copies' and those of one more piece of the base (3)."""
     m, n, T = 1024, 4096, 262144
     for clip in (0.0, 0.95):
         for case in (dict(batch=9), dict(batch=100), dict(batch=1001), dict(batch=1), dict(tok_chunk=4),
@@ -127,8 +140,8 @@ def short_chunks(L):
                 got.append((L.held() - h0, made, L.launches()))
                 L.c.realq_bgd_state_destroy(st)
             (h_al, made_al, lock_al), (h, made, lock) = got
-            assert h <= 1.07 * h_al, (case, h, h_al)
-            assert made <= made_al + 1 and lock == lock_al == 1, (case, got)  # one more: the token weights
+            assert h <= 1.07 * (h_al + 2 * T * n), (case, h, h_al)
+            assert made <= made_al + 5 and lock == lock_al == 1, (case, got)
 
 
 def slice_memory(L):

@@ -96,6 +96,7 @@ int main() {
         const int64_t ld = operand_stride(n);
         CHECK(ld >= n && ld % 64 == 0 && ld / 64 % 2 == 1 && ld < n + 128);
         CHECK(operand_stride(n + 1) >= ld);
+        CHECK(row_stride(n) >= n && row_stride(n) % 64 == 0 && row_stride(n) < n + 64);
     }
     // Slices of a float64-accumulated product: no float32 sum over more tokens than max_k, 256
     // tokens a slice at least otherwise, and fewer tokens never take more than 8/7 of the slices
