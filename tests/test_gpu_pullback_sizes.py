@@ -2,7 +2,8 @@
 weights (the lower terms of an exact weight are skipped), with and without a (non-symmetric) M,
 stored and accumulated, against float64.  Three bf16 terms carry all 24 bits and the dropped term
 pairs are below 2^-25 of the product; sums of K float32 products round by at most K 2^-24 of the sum
-of absolute values (twice, with M, whose inner product is rounded to float32 once more)."""
+of absolute values (twice, with M, whose inner product is rounded to float32 once more).  That
+bounds every entry at any size; what a lost term leaves is checked norm-wise below."""
 import numpy as np
 import pytest
 
