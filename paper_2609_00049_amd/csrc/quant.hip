@@ -37,6 +37,7 @@ namespace {
 constexpr int QB = 128;          // maximum block width
 constexpr int WAVES = 4;         // rows per workgroup, one wave each
 constexpr int CACHE = 6;         // evaluated batches (64 candidates each) kept for the tie decision
+constexpr int ALL_LEN = 4;       // groups of up to this many values have every candidate scored
 
 __device__ __forceinline__ double bcast(double v, int lane) {
     const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
@@ -153,6 +154,59 @@ __device__ __forceinline__ Range2 value_range(const GroupSrc& g, const WaveMem& 
 
 }  // namespace
 
+// Every candidate of a group scored in one walk over its values: lane l takes zero points
+// (l % 4) * (MAXQ + 1) / 4 and on, and of every 16 shrink factors number l / 4; the quotient of a value
+// and a scale serves all the lane's zeros.  About 130 operations a value for 1280 candidates, where 64
+// candidates a batch take 11.  best: the winner by the tie rule.
+template <int MAXQ, int R>
+__device__ __forceinline__ Best search_all(const GroupSrc& g, WaveMem& wm, int grid, double span, double ss, int znat,
+                                           int lane) {
+#pragma clang fp contract(off)
+    constexpr int ZL = (MAXQ + 1) / 4;
+    const int z0 = (lane & 3) * ZL;
+    double s[R], y[R], e[R][ZL], lo[ZL], hi[ZL];
+#pragma unroll
+    for (int u = 0; u < ZL; ++u) {
+        lo[u] = (double)(-(z0 + u));
+        hi[u] = (double)(MAXQ - (z0 + u));
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int k = 16 * r + (lane >> 2);
+        s[r] = k < grid ? ((1.0 - (double)k / 100.0) * span) / (double)MAXQ : 1.0;
+        y[r] = 1.0 / s[r];
+#pragma unroll
+        for (int u = 0; u < ZL; ++u) e[r][u] = 0.0;
+    }
+    for_values(g, wm, lane, [&](double x) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const double q = rint(div_by(x, s[r], y[r]));
+#pragma unroll
+            for (int u = 0; u < ZL; ++u) {
+                const double d = x - s[r] * fmin(fmax(q, lo[u]), hi[u]);
+                e[r][u] = fma(d, d, e[r][u]);
+            }
+        }
+    });
+    double emin = INFINITY;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int u = 0; u < ZL; ++u)
+            if (16 * r + (lane >> 2) < grid) emin = fmin(emin, e[r][u]);
+    const double thr = wave_min(emin) * (1.0 + TIE_RTOL) + TIE_ATOL * ss;
+    Best best{1 << 30, 1 << 30, 1 << 30};
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int u = 0; u < ZL; ++u) {
+            const Best c{16 * r + (lane >> 2), abs(z0 + u - znat), z0 + u};
+            if (c.k < grid && e[r][u] <= thr && better(c, best)) best = c;
+        }
+    return best;
+}
+
 // Joint (scale, zero) search of one group by one wave; the result is in all lanes.
 //
 // Every candidate's error is the float64 sum over the group's values in order, so the decision is
@@ -164,7 +218,10 @@ __device__ __forceinline__ Range2 value_range(const GroupSrc& g, const WaveMem& 
 // 1280 candidates about 100 to 200 are scored on Gaussian groups.  The tie rule needs every error up to the
 // final threshold: the first CACHE batches are kept in LDS, and a search that needed more goes
 // through the surviving candidates once more.
-template <int MAXQ>
+// ALL: where more than CACHE batches would be scored, and for groups of up to ALL_LEN values, all
+// candidates are, in one walk (search_all): the four extreme values say little about the sum of a long
+// group, and a few values are scored sooner than bounds are formed.
+template <int MAXQ, bool ALL>
 __device__ __forceinline__ void search_group(const GroupSrc& g, WaveMem& wm, int grid, bool sym, int lane,
                                              double& scale, int& zero) {
 #pragma clang fp contract(off)
@@ -236,18 +293,16 @@ __device__ __forceinline__ void search_group(const GroupSrc& g, WaveMem& wm, int
         }
         ++batches;
     };
-    {
-        const int k = sym ? lane : (lane & 31);
-        const int z = lane < 32 ? znat : zalt;
-        batch(k < grid ? (sym ? k : (k << zbits) + z) : -1);
-    }
+    auto survives = [&](int id, bool skip_seeded, double thr) {
+        const int k = k_of(id), z = z_of(id);
+        return id < total && !(skip_seeded && seeded(k, z)) && !(bound(k, z) > thr);
+    };
     // walk the remaining candidates in order and hand full batches of the surviving ones to f
     auto survivors = [&](bool skip_seeded, auto thr, auto f) {
         int n = 0;
         for (int id0 = 0; id0 < total; id0 += 64) {
             const int id = id0 + lane;
-            const int k = k_of(id), z = z_of(id);
-            const bool keep = id < total && !(skip_seeded && seeded(k, z)) && !(bound(k, z) > thr());
+            const bool keep = survives(id, skip_seeded, thr());
             const uint64_t mask = __ballot(keep);
             if (keep) wm.wait[n + __popcll(mask & ((1ull << lane) - 1))] = (uint16_t)id;
             n += __popcll(mask);
@@ -264,23 +319,38 @@ __device__ __forceinline__ void search_group(const GroupSrc& g, WaveMem& wm, int
         }
         if (n > 0) f(lane < n ? (int)wm.wait[lane] : -1);
     };
-    survivors(true, [&] { return threshold(emin); }, batch);
-
-    const double thr = threshold(emin);
     Best best{1 << 30, 1 << 30, 1 << 30};
-    auto offer = [&](double e, int id) {
-        const Best c{k_of(id), abs(z_of(id) - znat), z_of(id)};
-        if (e <= thr && better(c, best)) best = c;
-    };
-    wave_sync();
-    if (batches <= CACHE) {
-        for (int b = 0; b < batches; ++b) offer(wm.err[b * 64 + lane], wm.id[b * 64 + lane]);
+    bool all = ALL && g.len <= ALL_LEN;
+    if (!all) {
+        const int k = sym ? lane : (lane & 31);
+        const int z = lane < 32 ? znat : zalt;
+        batch(k < grid ? (sym ? k : (k << zbits) + z) : -1);
+    }
+    if (ALL && !all) {  // the walk below drops these and, as emin falls, more
+        int n = 0;
+        for (int id0 = 0; id0 < total; id0 += 64) n += __popcll(__ballot(survives(id0 + lane, true, threshold(emin))));
+        all = n > (CACHE - 1) * 64;
+    }
+    if (ALL && all) {
+        best = grid <= 80 ? search_all<MAXQ, 5>(g, wm, grid, span, r.ss, znat, lane)
+                          : search_all<MAXQ, 7>(g, wm, grid, span, r.ss, znat, lane);
     } else {
-        survivors(false, [&] { return thr; }, [&](int id) {
-            const int c = id < 0 ? 0 : id;
-            const double e = score(k_of(c), z_of(c));
-            if (id >= 0) offer(e, c);
-        });
+        survivors(true, [&] { return threshold(emin); }, batch);
+        const double thr = threshold(emin);
+        auto offer = [&](double e, int id) {
+            const Best c{k_of(id), abs(z_of(id) - znat), z_of(id)};
+            if (e <= thr && better(c, best)) best = c;
+        };
+        wave_sync();
+        if (ALL || batches <= CACHE) {
+            for (int b = 0; b < batches; ++b) offer(wm.err[b * 64 + lane], wm.id[b * 64 + lane]);
+        } else {
+            survivors(false, [&] { return thr; }, [&](int id) {
+                const int c = id < 0 ? 0 : id;
+                const double e = score(k_of(c), z_of(c));
+                if (id >= 0) offer(e, c);
+            });
+        }
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
@@ -301,7 +371,7 @@ __device__ __forceinline__ void search_group(const GroupSrc& g, WaveMem& wm, int
 // 4096; now 63 and 141 us).  The row's column loop is a serial chain of about 17 dependent float64
 // operations per column (the quantizer's quotient and the compensation's through precomputed
 // reciprocals, no division in the chain); the block's triangle of U sits in LDS, packed by rows.
-template <int MAXQ>
+template <int MAXQ, bool ALL>
 __global__ __launch_bounds__(WAVES * 64) void quantize_block_kernel(QuantArgs q) {
     __shared__ float sU[QB * (QB + 1) / 2];
     __shared__ double sR[QB];  // 1 / U_jj
@@ -361,7 +431,7 @@ __global__ __launch_bounds__(WAVES * 64) void quantize_block_kernel(QuantArgs q)
                 src.dead = q.dead ? q.dead + c0 : nullptr;
             }
             int zi;
-            search_group<MAXQ>(src, wm, q.grid, q.sym != 0, lane, scale, zi);
+            search_group<MAXQ, ALL>(src, wm, q.grid, q.sym != 0, lane, scale, zi);
             scale = (double)(float)scale;  // the stored float32 scale is the one used
             zf = (double)zi;
             inv = 1.0 / scale;
@@ -431,10 +501,20 @@ __global__ __launch_bounds__(WAVES * 64) void quantize_block_kernel(QuantArgs q)
 hipError_t quantize_block(const QuantArgs& q, hipStream_t st) {
     if (q.m <= 0 || q.bs <= 0) return hipSuccess;
     const unsigned grid = (unsigned)((q.m + WAVES - 1) / WAVES);
+    // In groups of more than two blocks most candidates may survive their bounds, and those of a few
+    // columns are too short for bounds to pay: both may score every candidate in one walk.  Groups
+    // in between keep the kernel without it (161 registers instead of 227; 256 columns a group 5.6 ms and
+    // 5.9 with it, 16 a group 7.6 and 8.9); the symmetric search has one zero point and at most 100
+    // candidates.  Quantizer of plain GPTQ, 4096 x 4096, asymmetric: one group a row 27.5 ms without it,
+    // 8.1 with; 1024 columns a group 15.3 and 8.0; 512 8.3 and 7.2; one column a group 68.8 and 40.5.
+    const bool all = !q.sym && (q.group > 2 * QB || q.group <= ALL_LEN);
     switch (q.bits) {
 #define RQ_CASE(b)                                                                                 \
     case b:                                                                                        \
-        hipLaunchKernelGGL(quantize_block_kernel<(1 << b) - 1>, dim3(grid), dim3(WAVES * 64), 0, st, q); \
+        if (all)                                                                                   \
+            hipLaunchKernelGGL((quantize_block_kernel<(1 << b) - 1, true>), dim3(grid), dim3(WAVES * 64), 0, st, q);  \
+        else                                                                                       \
+            hipLaunchKernelGGL((quantize_block_kernel<(1 << b) - 1, false>), dim3(grid), dim3(WAVES * 64), 0, st, q); \
         break;
         RQ_CASE(2)
         RQ_CASE(3)

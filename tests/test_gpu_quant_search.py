@@ -2,7 +2,7 @@
 over the row shapes that steer which candidates are scored: Gaussian and heavy-tailed rows (few
 survive the clipping bound), uniform rows (hundreds do: more than the kept batches), one-sided rows,
 exact ties, constants, on-grid rows and very small values; groups inside a block, as wide as the
-block, streamed past it, of one column; every bit width and a grid shorter than the first batch."""
+block, streamed past it, of a few columns; every bit width and a grid shorter than the first batch."""
 import numpy as np
 import pytest
 
@@ -25,7 +25,10 @@ def _rows(n, seed):
 @pytest.mark.parametrize("bits,group,sym,grid,n", [
     (4, 128, False, 80, 128), (4, 32, False, 80, 128), (4, 1, False, 80, 3), (4, 0, True, 80, 300),
     (4, 0, False, 80, 129), (4, 256, False, 80, 333), (3, 64, False, 100, 192), (2, 128, True, 1, 77),
-    (2, 128, False, 80, 65), (4, 128, False, 20, 127)])
+    (2, 128, False, 80, 65), (4, 128, False, 20, 127),
+    # every candidate in one walk: long groups (their last one inside a block), a few columns a group
+    (4, 0, False, 80, 700), (3, 0, False, 100, 513), (2, 512, False, 80, 600), (4, 384, False, 20, 900),
+    (4, 2, False, 80, 77), (4, 4, False, 100, 66), (3, 1, False, 80, 5)])
 def test_search_over_row_shapes(rq, ctx, bits, group, sym, grid, n):
     import torch
     W0 = _rows(n, 31 * bits + n)
