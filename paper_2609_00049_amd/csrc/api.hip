@@ -295,6 +295,12 @@ static int sum_products(realq_ctx* ctx, realq::GemmArgs* g, int count, int alway
         total += realq::gemm_effective_splits(g[p].K, g[p].splits);
         if (p + 1 == always) first = total;
     }
+    // a single slice holds the very sums that go into C; the terms of a weighted symmetric product do
+    // not make a symmetric matrix by themselves
+    if (total == 1 && accumulate && (!symmetric || (!g[0].Alo && realq::plan::straight_acc(M, g[0].K, ctx->cus)))) {
+        RQ_HIP(ctx, acc_direct(g[0], C, ldc, false, s));
+        return REALQ_OK;
+    }
     // one row of tiles over all columns; never more than the whole
     const int64_t least = realq::plan::panel_bytes(N, false, total, 0, std::min(M, realq::plan::kLargeBM));
     const int64_t all = realq::plan::panel_bytes(N, symmetric, total, 0, M);

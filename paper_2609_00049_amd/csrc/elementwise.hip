@@ -189,29 +189,45 @@ __global__ __launch_bounds__(256) void add_slices_kernel(const float* __restrict
                     if (j + e < ncols) v[e] += (double)p[z * stride + e];
         }
     }
-    auto add = [&](int64_t r, int64_t c, double x) {
-        Out* p = C + r * ldc + c;
-        *p = (Out)(accumulate ? (double)*p + x : x);
+    // this thread's four values of row r from column c, and for a symmetric product those of the
+    // mirrored tile: all old values are loaded before any is stored (C's loads cannot pass its stores)
+    struct Four {
+        Out* p;
+        int n;
+        double x[4], old[4];
     };
+    auto four = [&](int64_t r, int64_t c, bool in, int64_t end) {
+        Four q;
+        q.p = C + r * ldc + c;
+        q.n = in ? (int)max((int64_t)0, min((int64_t)4, end - c)) : 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q.old[e] = accumulate && e < q.n ? (double)q.p[e] : 0.0;
+        return q;
+    };
+    auto put = [&](const Four& q) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (e < q.n) q.p[e] = (Out)(accumulate ? q.old[e] + q.x[e] : q.x[e]);
+    };
+    Four own = four(i, j, i < r1, ncols);
     if constexpr (SYM) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) tile[rr][cc + e] = v[e];
+        const int64_t mi = tj * 32 + rr, mj = ti * 32 + cc;  // the mirrored tile's row and columns
+        Four mirror = four(mi, mj, ti != tj && mi < ncols, r1);
         __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mirror.x[e] = tile[cc + e][rr];
         if (ti == tj) {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (cc + e > rr) v[e] = tile[cc + e][rr];
-        } else {
-            // the mirrored tile: row tj*32 + rr, columns ti*32 + cc ..
-            const int64_t mi = tj * 32 + rr, mj = ti * 32 + cc;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (mi < ncols && mj + e < r1) add(mi, mj + e, tile[cc + e][rr]);
         }
+        put(mirror);
     }
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
-        if (i < r1 && j + e < ncols) add(i, j + e, v[e]);
+    for (int e = 0; e < 4; ++e) own.x[e] = v[e];
+    put(own);
 }
 
 template <class Out>

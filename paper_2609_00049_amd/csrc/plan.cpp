@@ -57,6 +57,14 @@ int64_t operand_stride(int64_t n) {
     return 64 * (lines | 1);
 }
 
+bool straight_acc(int64_t M, int64_t K, int cus) {
+    if (cus < 1) cus = 1;
+    const int64_t nt = (M + kLargeBM - 1) / kLargeBM, half = nt * (nt + 1) / 2;
+    if (nt > 1 && nt < 8) return false;
+    const int64_t extra = (nt * nt + cus - 1) / cus - (half + cus - 1) / cus;
+    return (double)extra * (double)K * 0.030 <= 0.21 * (double)half;
+}
+
 int64_t panel_rows(int64_t M, int64_t N, bool symmetric, int64_t slices, int64_t r0, int64_t budget) {
     int64_t lo = 1, hi = (M - r0 + kLargeBM - 1) / kLargeBM;  // tiles
     if (panel_bytes(N, symmetric, slices, r0, M - r0) <= budget) return M - r0;

@@ -49,6 +49,13 @@ int64_t operand_stride(int64_t n);
 // max_k > 0, at most max_k.
 int64_t choose_acc_splits(int64_t tiles, int64_t K, int passes, int cus, int64_t max_k);
 
+// Whether such a symmetric product in one slice is as well formed in full, straight into its matrix
+// (the same float32 sums): the other triangle's tiles against the slice's write and read and a launch
+// (about 0.21 us per tile).  Unweighted Hessians, straight and in a slice: 4096 columns over 1024 tokens
+// 103 and 146 us, 14336 over 1024 1.22 and 1.29 ms, over 2048 1.55 and 1.47; 512 over 16 (small
+// tiles, whose launch takes as long as both of the slice's) 37 and 34 us.
+bool straight_acc(int64_t M, int64_t K, int cus);
+
 // Rows of the panel from row r0 of an M x N product held as `slices` float32 slices: the most, in whole
 // 256-row tiles, whose slices take at most `budget` bytes, and one tile at least.  A symmetric
 // product's panel holds the columns up to its last row.

@@ -114,6 +114,9 @@ int main() {
                     most = std::max(most, q);
                 }
             }
+    // in one slice: straight into the matrix where the other triangle costs less than the slice
+    CHECK(straight_acc(1, 16, 256) && straight_acc(4096, 1024, 256) && straight_acc(14336, 1024, 256));
+    CHECK(!straight_acc(512, 16, 256) && !straight_acc(14336, 2048, 256) && !straight_acc(8192, 8192, 256));
     // Panels of such a product: whole tile rows that cover it, within the budget or one tile row
     for (int64_t M : {1, 255, 256, 257, 1000, 4097, 14336})
         for (bool sym : {false, true})

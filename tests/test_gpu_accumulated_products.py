@@ -1,6 +1,7 @@
 """The token contractions accumulated in float64 (Hessian, Fisher) at the edges of their tiles and token
 splits, onto a nonzero accumulator, against float64: one 256-wide tile and less, ragged last tiles,
-tokens below a split, ragged in the 32-token slices, unaligned rows (odd n), many splits.  Products
+tokens below a split, ragged in the 32-token slices, unaligned rows (odd n), many splits, few enough
+tokens to go straight into the matrix (unweighted, one tile row or eight and more).  Products
 of bf16 values are exact and at most L of them are summed in float32 (1024 in a slice of the two high
 terms of a weighted product, a staged chunk in the allocation-free call, else at most all T), so an
 entry is off by at most (L + 2) 2^-24 of its sum of absolute values (the 2 covers the weighted
@@ -15,7 +16,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("weighted", [False, True])
 @pytest.mark.parametrize("n,T", [(1, 1), (5, 33), (64, 700), (255, 4000), (256, 300), (257, 1031), (520, 20000),
-                                 (1030, 2056)])
+                                 (1030, 2056), (2100, 300)])
 def test_accumulated_products_at_tile_edges(rq, ctx, n, T, weighted):
     import torch
     print(f"[gpu-case] accumulated products n={n} T={T} weighted={weighted}", flush=True)
