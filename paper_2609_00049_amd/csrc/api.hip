@@ -1275,6 +1275,12 @@ int realq_pullback_metric(realq_ctx* ctx, const float* W_next, const float* M_ne
         uint16_t *hi, *lo, *lo2;
     };
     int rc;
+    if (realq::plan::pullback_small(m_next, m, M_next != nullptr)) {
+        void* T = nullptr;
+        if (M_next && (rc = get_ws(ctx, "p_T64", (size_t)m_next * m * 8, &T))) return rc;
+        RQ_HIP(ctx, realq::pullback_f64(W_next, M_next, m_next, m, (double*)T, accumulate != 0, P, s));
+        return REALQ_OK;
+    }
     auto terms = [&](const char* slot, int64_t rows, Terms& t) -> int {
         void* p;
         if ((rc = get_ws(ctx, slot, (size_t)3 * rows * kp * 2, &p))) return rc;

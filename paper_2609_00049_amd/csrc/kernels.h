@@ -169,6 +169,8 @@ hipError_t adam_update_dense(const AdamArgs& a, const float* G, hipStream_t st);
 
 // float64 GEMM on the matrix cores: C = A B (accumulate = false) or C += A B; A [M,K] lda, B [K,N] ldb,
 // C [M,N] ldc, all float64 row-major.
+hipError_t pullback_f64(const float* W, const float* Mn, int64_t m_next, int64_t m, double* T1, bool accumulate,
+                        float* P, hipStream_t st);
 hipError_t dgemm(const double* A, int64_t lda, const double* B, int64_t ldb, double* C, int64_t ldc, int64_t M,
                  int64_t N, int64_t K, bool accumulate, hipStream_t st);
 

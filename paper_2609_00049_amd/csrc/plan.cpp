@@ -57,6 +57,13 @@ int64_t operand_stride(int64_t n) {
     return 64 * (lines | 1);
 }
 
+bool pullback_small(int64_t m_next, int64_t m, bool dense) {
+    const double mm = (double)m * (double)m;
+    if (!dense) return m_next <= 512 && mm * (double)m_next <= 0x1p30;
+    // 35 ns per 10^6 products in float64, 12 in six bf16 passes; what the launches and slices cost there
+    return m_next <= 1024 && 2.3e-8 * (double)m * (double)m_next * (double)(m_next + m) <= 130.0 + 8e-6 * mm;
+}
+
 bool straight_acc(int64_t M, int64_t K, int cus) {
     if (cus < 1) cus = 1;
     const int64_t nt = (M + kLargeBM - 1) / kLargeBM, half = nt * (nt + 1) / 2;

@@ -56,6 +56,14 @@ int64_t choose_acc_splits(int64_t tiles, int64_t K, int passes, int cus, int64_t
 // tiles, whose launch takes as long as both of the slice's) 37 and 34 us.
 bool straight_acc(int64_t M, int64_t K, int cus);
 
+// Whether the pulled-back metric of m columns through m_next rows (and a dense metric) is small enough
+// for float64 products straight from the float32 operands (one or two launches, bound by latency) rather
+// than term splits, products and slice sums on the bf16 matrix cores (7 to 14 launches).  Measured,
+// float64 / bf16-exact weights / others: 256 x 256 32 / 43 / 94 us, 512 x 1024 50 / 47 / 106, 64 x
+// 4096 62 / 75 / 153, 1024 x 256 82 / 44 / 98; dense 512 x 512 82 / 177 / 179, 768 x 2048 205 / 287 /
+// 305, 512 x 8192 1235 / 1009 / 1054, 2048 x 256 323 / 215 / 221.
+bool pullback_small(int64_t m_next, int64_t m, bool dense);
+
 // Rows of the panel from row r0 of an M x N product held as `slices` float32 slices: the most, in whole
 // 256-row tiles, whose slices take at most `budget` bytes, and one tile at least.  A symmetric
 // product's panel holds the columns up to its last row.

@@ -1,4 +1,5 @@
-"""The pulled-back metric P = W^T M W at tile edges and odd sizes, for bf16-exact and full float32
+"""The pulled-back metric P = W^T M W at tile edges and odd sizes, in float64 where it is small (up to
+512 rows, or 1024 with a dense M) and in bf16 terms above, for bf16-exact and full float32
 weights (the lower terms of an exact weight are skipped), with and without a (non-symmetric) M,
 stored and accumulated, against float64.  Three bf16 terms carry all 24 bits and the dropped term
 pairs are below 2^-25 of the product; sums of K float32 products round by at most K 2^-24 of the sum
@@ -13,7 +14,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("accumulate", [False, True])
 @pytest.mark.parametrize("exact", [True, False])
 @pytest.mark.parametrize("m_next,m,dense", [(1, 1, False), (37, 65, False), (300, 257, False), (1023, 520, False),
-                                            (65, 37, True), (264, 300, True)])
+                                            (513, 65, False), (700, 257, False), (256, 2049, False),
+                                            (65, 37, True), (264, 300, True), (1030, 37, True), (1025, 257, True)])
 def test_pullback_at_tile_edges(rq, ctx, m_next, m, dense, exact, accumulate):
     import torch
     print(f"[gpu-case] pullback {m_next}x{m} dense={dense} exact={exact} accumulate={accumulate}", flush=True)
@@ -36,7 +38,7 @@ def test_pullback_at_tile_edges(rq, ctx, m_next, m, dense, exact, accumulate):
         assert torch.equal(P, P.T)
 
 
-@pytest.mark.parametrize("m_next,m,dense,accumulate", [(1023, 520, False, False), (1023, 520, True, True),
+@pytest.mark.parametrize("m_next,m,dense,accumulate", [(1023, 520, False, False), (1100, 520, True, True),
                                                        (4000, 300, False, True), (515, 14500, False, True),
                                                        (300, 14500, True, False)])
 def test_pullback_of_full_float32_weights(rq, ctx, m_next, m, dense, accumulate):
