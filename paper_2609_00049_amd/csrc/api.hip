@@ -259,11 +259,25 @@ static hipError_t acc_direct(const realq::GemmArgs& g, float* C, int64_t ldc, bo
 // Most bytes the slices of sum_products hold; larger products are formed in panels of rows.
 static constexpr int64_t kSliceBytes = (int64_t)3 << 30;
 
+// Whether the stream records a graph: no memory can be allocated then.
+static bool capturing(realq_ctx* ctx) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &st) != hipSuccess) (void)hipGetLastError();
+    return st != hipStreamCaptureStatusNone;
+}
+
 // Room for product slices: `want` bytes, or what the context holds when that is at least 7/8 of it
-// (fewer tokens can take up to 1.13 times the slices, and a call takes no new memory after a larger
-// one), or as much as there is, down to `least`; 0 when there is not that.
+// (fewer tokens can take up to 1.13 times the slices) or the stream records a graph (fewer columns can
+// take more of them too), or as much as there is, down to `least`; 0 when there is not that.
 static int64_t slice_room(realq_ctx* ctx, int64_t want, int64_t least, void** S, int* rc) {
     const int64_t held = (int64_t)ctx->ws[realq::kSliceSlot].bytes;
+    if (held < want && capturing(ctx)) {
+        if (held < least) {
+            *rc = REALQ_ERR_OOM;
+            return 0;
+        }
+        want = held;
+    }
     if (held >= least && held >= want / 8 * 7) want = held;
     for (;; want = std::max(least, want / 2)) {
         *rc = get_ws(ctx, realq::kSliceSlot, (size_t)want, S);
@@ -1277,7 +1291,7 @@ int realq_pullback_metric(realq_ctx* ctx, const float* W_next, const float* M_ne
     int rc;
     if (realq::plan::pullback_small(m_next, m, M_next != nullptr)) {
         void* T = nullptr;
-        if (M_next && (rc = get_ws(ctx, "p_T64", (size_t)m_next * m * 8, &T))) return rc;
+        if (M_next && (rc = get_ws(ctx, "p_T1", (size_t)m_next * m * 8, &T))) return rc;
         RQ_HIP(ctx, realq::pullback_f64(W_next, M_next, m_next, m, (double*)T, accumulate != 0, P, s));
         return REALQ_OK;
     }
@@ -1308,7 +1322,8 @@ int realq_pullback_metric(realq_ctx* ctx, const float* W_next, const float* M_ne
     void* T1;
     if ((rc = terms("p_M", m_next, r))) return rc;
     RQ_HIP(ctx, realq::split3_f32(M_next, m_next, r.hi, r.lo, r.lo2, kp, m_next, m_next, nullptr, s));
-    if ((rc = get_ws(ctx, "p_T1", (size_t)m * kp * 4, &T1))) return rc;
+    // float32 here; 8 bytes a value, so that a small call (in float64) after a larger one finds its room
+    if ((rc = get_ws(ctx, "p_T1", (size_t)m * kp * 8, &T1))) return rc;
     if ((rc = product(w, r, m_next, nullptr, false, false, (float*)T1, kp))) return rc;
     if ((rc = terms("p_R", m, r))) return rc;
     RQ_HIP(ctx, realq::split3_f32((const float*)T1, kp, r.hi, r.lo, r.lo2, kp, m, m_next, nullptr, s));
@@ -1331,7 +1346,8 @@ int realq_handoff(realq_ctx* ctx, const float* Wa, const float* Wb, const uint16
     const uint16_t* Xg = X;
     int64_t ldx = n;
     if (ldn != n) {  // without room for the copy the product takes the caller's rows, slower
-        rc = get_ws(ctx, "h_xg", (size_t)T * ldn * 2, &xg);
+        const size_t bytes = (size_t)T * ldn * 2;
+        rc = ctx->ws["h_xg"].bytes < bytes && capturing(ctx) ? REALQ_ERR_OOM : get_ws(ctx, "h_xg", bytes, &xg);
         if (rc && rc != REALQ_ERR_OOM) return rc;
         if (!rc) {
             RQ_HIP(ctx, realq::copy_rows_u16(X, n, (uint16_t*)xg, ldn, T, n, s));

@@ -19,7 +19,7 @@ std::map<std::string, int64_t> copies;
 size_t held = 0, peak = 0, limit = SIZE_MAX;
 uintptr_t next_addr = 1ull << 40;
 double host_value = 0.0;
-int last_error = 0, bad_launches = 0, mallocs = 0;
+int last_error = 0, bad_launches = 0, mallocs = 0, capturing = 0;
 Dim3 cfg_grid, cfg_block;
 size_t cfg_shared;
 void* cfg_stream;
@@ -38,6 +38,7 @@ void fake_set_host_value(double v) { host_value = v; }
 int64_t fake_held() { return (int64_t)held; }
 int64_t fake_peak() { return (int64_t)peak; }
 int64_t fake_mallocs() { return mallocs; }
+void fake_set_capturing(int on) { capturing = on; }
 int64_t fake_bad_launches() { return bad_launches; }
 int64_t fake_copies() {
     int64_t n = 0;
@@ -90,6 +91,11 @@ int hipLaunchKernel(const void* f, Dim3 g, Dim3 b, void**, size_t shared, void*)
 }
 int hipMalloc(void** p, size_t n) {
     *p = nullptr;
+    if (capturing) {
+        std::fprintf(stderr, "hipMalloc of %zu bytes while capturing\n", n);
+        ++mallocs;
+        return last_error = 900;  // hipErrorStreamCaptureUnsupported
+    }
     if (n > limit - held || held > limit) return last_error = 2;  // hipErrorOutOfMemory
     blocks[next_addr] = n;
     *p = reinterpret_cast<void*>(next_addr);
@@ -138,7 +144,11 @@ int hipGetSymbolAddress(void** p, const void* sym) {
     *p = const_cast<void*>(sym);
     return 0;
 }
-int hipStreamSynchronize(void*) { return 0; }
+int hipStreamIsCapturing(void*, int* status) {
+    *status = capturing;
+    return 0;
+}
+int hipStreamSynchronize(void*) { return capturing ? last_error = 900 : 0; }
 int hipEventCreate(void** e) {
     *e = reinterpret_cast<void*>(8);
     return 0;

@@ -196,6 +196,30 @@ def little_room(L):
         L.ok("realq_handoff", buf(1), buf(2), buf(3), 65536, 4097, 1000, buf(5))
 
 
+def under_capture(L):
+    """While the stream records a graph, calls no larger than earlier ones allocate nothing, also where
+    they take another route or more slices than the larger call did."""
+    i32 = ctypes.c_int
+    calls = [("realq_hessian_accum", lambda T, n: (buf(1), None, T, n, buf(3))),
+             ("realq_hessian_accum", lambda T, n: (buf(1), buf(2), T, n, buf(3))),
+             ("realq_fisher_accum", lambda T, n: (buf(1), T, n, buf(3))),
+             ("realq_pullback_metric", lambda T, n: (buf(1), None, T, n, i32(0), buf(3))),
+             ("realq_pullback_metric", lambda T, n: (buf(1), buf(2), T, n, i32(1), buf(3))),
+             ("realq_handoff", lambda T, n: (buf(1), buf(2), buf(3), T, n, 1000, buf(5)))]
+    sizes = [(T, n) for T in (8192, 5000, 4096, 1025, 300, 17) for n in (8192, 4096, 2048, 1001, 512, 133, 16)]
+    for name, args in calls:
+        for T0, n0 in ((8192, 8192), (4096, 2048), (1025, 1001)):
+            L.fresh()
+            L.ok(name, *args(T0, n0))
+            L.fake.fake_reset()
+            L.fake.fake_set_capturing(1)
+            for T, n in sizes:
+                if T <= T0 and n <= n0:
+                    L.ok(name, *args(T, n))
+                    assert L.fake.fake_mallocs() == 0, (name, T0, n0, T, n)
+            L.fake.fake_set_capturing(0)
+
+
 if __name__ == "__main__":
     globals()[sys.argv[3]](Library(sys.argv[1], sys.argv[2]))
     print("passed")

@@ -23,7 +23,7 @@ def fake(tmp_path_factory):
     return str(so)
 
 
-@pytest.mark.parametrize("check", ["whole_lines", "many_tokens", "short_chunks", "slice_memory", "little_room"])
+@pytest.mark.parametrize("check", ["whole_lines", "many_tokens", "short_chunks", "slice_memory", "little_room", "under_capture"])
 def test_on_a_runtime_that_only_books(fake, check):
     res = subprocess.run([sys.executable, os.path.join(HOST, "host_logic.py"), fake, LIB, check], capture_output=True,
                          text=True, timeout=120)
