@@ -187,7 +187,9 @@ int realq_mfma_peak(realq_ctx* ctx, int64_t iters, double* tflops);
  * realq_chol_inverse with the total token count.  s may be NULL (all ones).
  * T == 0 is a no-op.  The full symmetric matrix is written.  Precision: the bf16 products
  * are exact; s_t xhat_t is formed in float32 and carried as three bf16 terms (all of its
- * 24 bits); tiles accumulate in float32 over a token chunk and in float64 across chunks. */
+ * 24 bits).  Products are summed in float32 over ranges of the tokens (with weights at most 1024
+ * tokens of the two high terms) and the ranges in float64, in a fixed order.  Holds up to 3 GiB of such sums in the context (given back when other memory
+ * of the context runs out); while the stream records a graph it takes no new memory for them. */
 int realq_hessian_accum(realq_ctx* ctx, const uint16_t* Xhat /*[T,n]*/, const float* s /*[T]|NULL*/,
                         int64_t T, int64_t n, double* H_acc /*[n,n]*/);
 
@@ -195,8 +197,9 @@ int realq_hessian_accum(realq_ctx* ctx, const uint16_t* Xhat /*[T,n]*/, const fl
  * loops, harnesses that forbid hipMalloc): the same accumulation as realq_hessian_accum, with the
  * token chunks staged in a fixed scratch array of REALQ_NOALLOC_SCRATCH_BYTES that the library
  * holds on each GPU it runs on (from the first call on that GPU until the process ends) instead of
- * context workspaces; it calls no device allocator.  Chunks are shorter than realq_hessian_accum's,
- * so float64 sums across chunks may differ from it in the last bits.  n > REALQ_NOALLOC_MAX_N gives
+ * context workspaces; it calls no device allocator.  A float32 sum holds a staged chunk of tokens
+ * (2^23 / n, a multiple of 256) instead of realq_hessian_accum's ranges, so the two differ at float32
+ * rounding, and with weights the triangles are summed separately.  n > REALQ_NOALLOC_MAX_N gives
  * REALQ_ERR_SHAPE.  Every call on one GPU shares that GPU's scratch array: calls that overlap on one
  * GPU (from several streams or threads) race and must be serialised by the caller.  Nothing in the
  * array needs clearing between calls. */
@@ -222,8 +225,10 @@ int realq_chol_inverse(realq_ctx* ctx, const double* H_acc, int64_t n, int64_t T
  * Per-module state of Block-GD (Sec. 4.3): the residual base
  *   B = W0 (Xhat - X)^T + (W_locked - W0_locked) Xhat_locked^T      ([m,T] float32),
  * the Adam moments (m, v, [m,n] float32), the step counter, a transposed copy of
- * Xhat and the split of W - W0 the GEMMs consume.  W0, X, Xhat, s, M and P are
- * borrowed and must stay valid for the state's lifetime.
+ * Xhat and the split of W - W0 the GEMMs consume, and, where its rows are not whole 128-byte
+ * lines (n not a multiple of 64) or the token chunks do not start on multiples of 8 and memory
+ * allows, a padded copy of Xhat.  W0, X, Xhat, s, M and P are borrowed and must stay valid and
+ * unchanged for the state's lifetime.
  *   X    : inputs of the full-precision model ([T,n] bf16); Xhat: inputs the
  *          partially quantized model feeds this module ([T,n] bf16); X == Xhat
  *          (same pointer) is allowed.
@@ -303,7 +308,8 @@ int realq_bgd_loss(realq_ctx* ctx, realq_bgd_state* st, const double* W /*[m,n]*
  * dy^T P dy with P = W_next^T M_next W_next (M_next = NULL: identity).
  *   W_next : [m_next, m] float32;  M_next : [m_next, m_next] float32 | NULL;
  *   P      : [m, m] float32 output; accumulate != 0 adds to P (several consumers, e.g. gate and up).
- * Computed in float32. */
+ * Float32 operands enter with all their bits; sums in float32 over ranges and in float64 across
+ * them, or in float64 throughout for small modules. */
 int realq_pullback_metric(realq_ctx* ctx, const float* W_next, const float* M_next, int64_t m_next, int64_t m,
                           int accumulate, float* P);
 

@@ -38,12 +38,6 @@ constexpr int NB = 64;        // panel width
 constexpr int OUTER = 4;      // panels per outer panel
 constexpr int SR = NB + 2;    // row stride of a row-major 64 x 64 block in LDS: rows 4 banks apart
 
-__device__ __forceinline__ double bcast(double v, int lane) {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
-    return __hiloint2double(hi, lo);
-}
-
 typedef double (*Blk)[SR];
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
@@ -134,8 +128,8 @@ __global__ __launch_bounds__(256) void chol_fill_kernel(const double* __restrict
 // 8 us of one compute unit and would otherwise be a launch of its own that all others wait for),
 // workgroup 0 stores its inverse, the others their solved block L = P L_kk^{-T}.
 //
-// Bound by latency: per outer panel four dependent launches of about 20 us, half of it the factor's
-// 64 pivots (a reciprocal square root and the next column's update each, in the registers of one
+// Bound by latency: per outer panel four dependent launches of 24 us and more (34 on average), 8 us of each
+// the factor's 64 pivots (a reciprocal square root and the next column's update each, in the registers of one
 // wave, 16 columns at a time with the rest of the block updated by all waves' matrix products).
 __global__ __launch_bounds__(256) void chol_panel_kernel(double* __restrict__ A, int64_t np, int64_t kb, int64_t first,
                                                          double* __restrict__ X, int* flag) {

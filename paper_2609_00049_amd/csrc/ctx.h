@@ -56,7 +56,7 @@ int validate_q(realq_ctx* ctx, const realq_qparams* qp);
 int validate_bgd(realq_ctx* ctx, const realq_bgd_params* p);
 // Token-chunked Hessian accumulation into H_acc with caller-provided staging buffers (n rows of
 // ld >= tc bf16 each; hi, lo, lo2 only used when s is given).  alloc: the products may go through context
-// workspaces (acc_products); false: straight into H_acc, no workspace and no timing events.
+// workspaces (sum_products in api.hip); false: straight into H_acc, no workspace and no timing events.
 int hessian_accum_chunks(realq_ctx* ctx, const uint16_t* Xhat, const float* s, int64_t T, int64_t n, double* H_acc,
                          int64_t tc, int64_t ld, uint16_t* xt, uint16_t* hi, uint16_t* lo, uint16_t* lo2, bool alloc);
 

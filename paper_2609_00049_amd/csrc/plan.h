@@ -43,10 +43,11 @@ int64_t row_stride(int64_t n);
 int64_t operand_stride(int64_t n);
 
 // Split-K factor of a product accumulated in float64 over `tiles` 256x256 tiles and K tokens with
-// `passes` MFMA passes per tile: the cheapest of 1 .. 256 by the time its rounds of `cus` tiles take
-// at the GEMM's rate (about 30 ns per token, tile and pass) plus the write and read of its float32
-// slices (about 0.11 us per tile and slice); every split keeps at least 256 tokens and, with
-// max_k > 0, at most max_k.
+// `passes` MFMA passes per tile: the cheapest by the time its rounds of `cus` tiles take at the GEMM's
+// rate (about 30 ns per token, tile and pass) plus the write and read of its float32 slices (about 0.11
+// us per tile and slice), from 1 or, with max_k > 0, from ceil(K / max_k), so that no split sums more
+// than max_k tokens, up to 256 splits of at least 256 tokens (or that least number, where it is more:
+// 2048 for 2^21 tokens at 1024 a sum).
 int64_t choose_acc_splits(int64_t tiles, int64_t K, int passes, int cus, int64_t max_k);
 
 // Whether such a symmetric product in one slice is as well formed in full, straight into its matrix

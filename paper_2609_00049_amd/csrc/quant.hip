@@ -39,12 +39,6 @@ constexpr int WAVES = 4;         // rows per workgroup, one wave each
 constexpr int CACHE = 6;         // evaluated batches (64 candidates each) kept for the tie decision
 constexpr int ALL_LEN = 4;       // groups of up to this many values have every candidate scored
 
-__device__ __forceinline__ double bcast(double v, int lane) {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
-    return __hiloint2double(hi, lo);
-}
-
 constexpr double TIE_RTOL = 0x1p-40;  // search errors within TIE_RTOL * least + TIE_ATOL * sum x^2
 constexpr double TIE_ATOL = 0x1p-60;  // are one tie
 
