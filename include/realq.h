@@ -65,7 +65,9 @@ typedef struct realq_qparams {
  *   steps     : Adam steps after every column block (0 = plain GPTQ)
  *   lr        : learning rate eta
  *   beta1, beta2, eps : Adam constants [0.9, 0.999, 1e-8]
- *   tok_chunk : tokens per streamed chunk of the residual/gradient GEMMs (0 = all T)
+ *   tok_chunk : tokens per streamed chunk of the residual/gradient GEMMs (0 = all T); chunks (and
+ *               batches) of a multiple of 8 tokens run fastest, those of other lengths below about
+ *               100 tokens slowest per token
  *   form      : REALQ_BGD_TOKENS or REALQ_BGD_GRAM (below) [REALQ_BGD_TOKENS]
  *   loss_clip : output-perturbation clip quantile q in (0, 1], 0 = off [0] (Appendix D.1,
  *               a_loss_clip): each step scales every token's channels whose |R| exceeds

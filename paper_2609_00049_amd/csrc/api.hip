@@ -673,12 +673,14 @@ static bool copy_fits(realq_bgd_state* st, int64_t bytes) {
     const int64_t chunk = std::min(st->at.count * ldn * 2, (int64_t)256 << 20);
     if (st->X != st->Xhat) v.insert(v.end(), {{"i_xh", chunk, nullptr}, {"i_xl", chunk, nullptr}});
     if (st->prm.resid_increment && st->prm.steps > 1)
-        v.insert(v.end(), {{"s_Dacc", m * n * 4, nullptr}, {"s_Dinc", m * ldn * 2, nullptr}, {"s_G0", m * n * 4, nullptr}});
+        v.insert(v.end(), {{"s_Dacc", m * n * 4, nullptr}, {"s_Dinc", m * ldn * 2, nullptr},
+                           {"s_G0", m * n * 4, nullptr}});
     if (dense)
         v.insert(v.end(), {{"s_Mah", m * mp * 2, nullptr}, {"s_Mal", m * mp * 2, nullptr}, {"b_Gm", m * n * 4, nullptr},
                            {"b_GTh", mp * n * 2, nullptr}, {"b_GTl", mp * n * 2, nullptr}});
     if (st->M) {
-        for (const char* slot : {"g_sdh", "g_sdl", "g_dh16", "g_dl16", "g_xt"}) v.push_back({slot, gram_staging(n, st->T), nullptr});
+        for (const char* slot : {"g_sdh", "g_sdl", "g_dh16", "g_dl16", "g_xt"})
+            v.push_back({slot, gram_staging(n, st->T), nullptr});
         for (const char* slot : {"g_A", "g_D", "g_E", "g_MX"}) v.push_back({slot, m * n * 8, nullptr});
         v.insert(v.end(), {{"g_dh", n * n * 8, nullptr}, {"g_dd", n * n * 8, nullptr}, {"g_M", m * m * 8, nullptr}});
     }
@@ -743,7 +745,8 @@ static int state_init(realq_bgd_state* st) {
     Timed tm(ctx, "init");
     RQ_HIP(ctx, realq::fill_f32(st->mA, 0.f, m * n, s));
     RQ_HIP(ctx, realq::fill_f32(st->vA, 0.f, m * n, s));
-    if (st->Xg != st->Xhat) RQ_HIP(ctx, realq::place_rows_u16(st->Xhat, n, const_cast<uint16_t*>(st->Xg), ldn, n, at, s));
+    if (st->Xg != st->Xhat)
+        RQ_HIP(ctx, realq::place_rows_u16(st->Xhat, n, const_cast<uint16_t*>(st->Xg), ldn, n, at, s));
     if (st->sg != st->s) RQ_HIP(ctx, realq::place_f32(st->s, const_cast<float*>(st->sg), at, s));
     RQ_HIP(ctx, realq::transpose_u16(st->Xg, st->ldx, st->XhT, Tp, at.count, n, s));
     // Residual base before any block is locked: B = W0 (Xhat - X)^T.
